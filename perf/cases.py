@@ -1,0 +1,474 @@
+"""Timed cases of the library's main path, through its public Python binding.
+
+A case is a dict of plain values: the call ("kind"), the workload it runs on and its block
+width.  Workloads are the package's own configurations (``inputs.CONFIGS``) or, with
+``system = "box"``, a box of any size with atoms placed like the serving stream's requests.
+
+  listed()            the cases, from the smallest call to the largest
+  draw(rng)           one more case of the same ranges
+  prepare(case, seed) inputs, handle and workspace on the GPU (inputs from the seed alone)
+  run(state)          one pass, returning what the call computes
+  work(case)          bytes and operations one pass cannot do without
+  exact(case, seed)   the same outputs in plain FP64 torch
+"""
+import functools
+import math
+
+import numpy as np
+import torch
+
+from paper_2302_09708_amd import chefsi as cs
+from paper_2302_09708_amd import inputs
+
+
+def listed():
+    return [
+        # one H X on the smallest workload (24^3, 40 orbitals): launches and latency count
+        {"name": "apply_small_fp64", "kind": "apply", "system": "cfg1", "ns": 40, "precision": "fp64", "tuned": False},
+        # whole ten-iteration solve of that workload: many small launches and a small dense stage
+        {"name": "solve_small_fp64", "kind": "solve", "system": "cfg1", "ns": 40, "degree": 20, "n_iter": 10,
+         "tuned": False},
+        # upper spectral bound before a solve: twenty Lanczos steps on one vector
+        {"name": "lanczos_bulk_fp64", "kind": "lanczos", "system": "cfg2", "steps": 20},
+        # filter of one serving request: odd grid, slab, FP32 block, handle as created (the
+        # serving loop does not tune)
+        {"name": "filter_request_mixed", "kind": "filter", "system": "box", "nx": 45, "ny": 45, "nz": 45, "slab": True,
+         "atoms": 52, "ns": 187, "degree": 20, "precision": "mixed", "tuned": False},
+        # subspace problem of the 72^3 workload
+        {"name": "eigh_bulk", "kind": "eigh", "system": "cfg1", "ns": 600},
+        # forces and both stresses of the 72^3 workload, once per molecular-dynamics step
+        {"name": "forces_bulk_fp64", "kind": "forces", "system": "cfg2", "ns": 600},
+        # H_k X at a Bloch wavevector on the 72^3 workload
+        {"name": "kpoint_bulk", "kind": "kpoint", "system": "cfg2", "ns": 600},
+        # rotation of the 60 x 60 x 180 slab's mixed-precision block
+        {"name": "rotate_slab_mixed", "kind": "rotate", "system": "cfg3", "ns": 1200},
+        # filter of the 72^3 workload in FP64 (most of its step)
+        {"name": "filter_bulk_fp64", "kind": "filter", "system": "cfg2", "ns": 600, "degree": 20, "precision": "fp64",
+         "tuned": True},
+        # filter of the slab in mixed precision: Dirichlet in z, overlapping projectors
+        {"name": "filter_slab_mixed", "kind": "filter", "system": "cfg3", "ns": 1200, "degree": 24,
+         "precision": "mixed", "tuned": True},
+        # one whole iteration of the 72^3 workload in FP64 (the benchmark's step)
+        {"name": "step_bulk_fp64", "kind": "step", "system": "cfg2", "ns": 600, "degree": 20, "tuned": True},
+        # mixed-precision projection on the 120^3 grid, a quarter of that workload's orbitals
+        # (the state of the whole block is larger than a third of the card)
+        {"name": "project_large_mixed", "kind": "project", "system": "cfg4", "ns": 1800, "tuned": False},
+    ]
+
+
+def draw(rng):
+    def log_int(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+    kind = rng.choice(["apply", "solve", "lanczos", "filter", "filter", "eigh", "forces", "kpoint", "rotate", "step",
+                       "project"])
+    if kind == "eigh":
+        return {"kind": kind, "system": "cfg1", "ns": log_int(40, 1200)}
+    n = [rng.randint(24, 72) for _ in range(3)]
+    slab = rng.random() < 0.5
+    if slab:
+        n[2] = rng.randint(n[2], 2 * n[2])
+    c = {"kind": kind, "system": "box", "nx": n[0], "ny": n[1], "nz": n[2], "slab": slab, "atoms": log_int(8, 96)}
+    top = min(600, n[0] * n[1] * n[2] // 24)
+    if kind == "lanczos":
+        c["steps"] = rng.randint(8, 20)
+        return c
+    if kind == "solve":
+        c.update(ns=log_int(40, min(top, 120)), degree=rng.choice([16, 20, 24]), n_iter=rng.randint(2, 4), tuned=False)
+    elif kind == "step":
+        c.update(ns=log_int(40, top), degree=rng.choice([16, 20, 24]), tuned=rng.random() < 0.5)
+    elif kind == "filter":
+        c.update(ns=log_int(40, top), degree=rng.choice([16, 20, 24]), precision=rng.choice(["fp64", "mixed"]),
+                 tuned=rng.random() < 0.5)
+    elif kind == "apply":
+        c.update(ns=log_int(8, top), precision=rng.choice(["fp64", "mixed"]), tuned=False)
+    elif kind == "project":
+        c.update(ns=log_int(40, top), tuned=False)
+    else:  # forces, kpoint, rotate
+        c.update(ns=log_int(40, top))
+    return c
+
+
+# ---------------------------------------------------------------------------
+# inputs
+# ---------------------------------------------------------------------------
+@functools.lru_cache(maxsize=8)
+def _box(nx, ny, nz, slab, atoms):
+    """A box at h = 0.3 with s + 3p projectors, atoms uniform (in the central third of z for a slab)."""
+    n, h = (nx, ny, nz), (0.3, 0.3, 0.3)
+    bc = (0, 0, 1) if slab else (0, 0, 0)
+    rng = np.random.Generator(np.random.PCG64([nx, ny, nz, atoms, int(slab)]))
+    size = np.array(n) * 0.3
+    pos = rng.uniform(0.0, 1.0, size=(atoms, 3)) * size
+    if slab:
+        pos[:, 2] = (size[2] + pos[:, 2]) / 3.0
+    veff = inputs.gaussian_wells(n, h, bc, pos)
+    sp, si, npj, chi, gam = inputs.kb_projectors(n, h, bc, pos, 4)
+    return inputs.Problem(n, h, bc, 12, veff, pos, sp, si, npj, chi, gam, name="box")
+
+
+@functools.lru_cache(maxsize=8)
+def _config(name):
+    return inputs.make_problem(inputs.CONFIGS[name])
+
+
+def _problem(case):
+    if case["system"] == "box":
+        return _box(case["nx"], case["ny"], case["nz"], case["slab"], case["atoms"])
+    return _config(case["system"])
+
+
+def _randn(shape, seed, dtype):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(int(seed))
+    return torch.randn(shape, generator=g, device="cuda", dtype=dtype)
+
+
+def _precision(case):
+    """FP64 unless the case says otherwise; projection and rotation cases are the mixed path's."""
+    return case.get("precision", "mixed" if case["kind"] in ("project", "rotate") else "fp64")
+
+
+def _block(case, seed):
+    """The orbital block: (ns, Nd), row j is orbital j."""
+    nd = _problem(case).nd
+    if case["kind"] == "kpoint":
+        return torch.view_as_complex(_randn((case["ns"], nd, 2), seed, torch.float64))
+    dtype = torch.float64 if _precision(case) == "fp64" else torch.float32
+    x = _randn((case["ns"], nd), seed, dtype)
+    if case["kind"] in ("forces", "rotate"):  # orbitals of unit norm, as an iteration leaves them
+        x /= math.sqrt(nd)
+    return x
+
+
+def _pencil(ns, seed):
+    """A subspace problem as a first iteration meets it: an overlap matrix near a scaled
+    identity and a Hamiltonian with a spread spectrum."""
+    a = _randn((ns, 4 * ns), seed, torch.float64) / math.sqrt(4 * ns)
+    d = torch.linspace(0.2, 1.0, ns, device="cuda", dtype=torch.float64)
+    a *= d[:, None]
+    e = torch.linspace(-0.7, 20.0, 4 * ns, device="cuda", dtype=torch.float64)
+    hs = (a * e) @ a.T
+    ms = a @ a.T
+    return 0.5 * (hs + hs.T), 0.5 * (ms + ms.T)
+
+
+def _rotation(ns, seed):
+    return torch.linalg.qr(_randn((ns, ns), seed + 1, torch.float64))[0].contiguous()
+
+
+def _occupations(ns):
+    """Two electrons per orbital with a smooth cutoff over the last sixth of the block."""
+    i = np.arange(ns)
+    return 2.0 / (1.0 + np.exp((i - ns / 1.2) / max(1.0, ns / 60.0)))
+
+
+def _kvec(prob):
+    return tuple(math.pi / (2.0 * prob.n[d] * prob.h[d]) for d in range(3))
+
+
+def prepare(case, seed):
+    prob = _problem(case)
+    kind = case["kind"]
+    ns = case.get("ns", 1)
+    s = {"kind": kind, "ns": ns, "case": case}
+    if kind == "kpoint":
+        s["h"] = h = cs.KPoint(prob, _kvec(prob), inputs.support_images(prob), max_ns=ns)
+        s["ws"] = h.workspace(ns)
+        s["x"] = _block(case, seed)
+        s["y"] = torch.empty_like(s["x"])
+        return s
+    prec = cs.FP64 if _precision(case) == "fp64" else cs.MIXED
+    s["h"] = h = cs.Handle(prob, precision=prec, max_ns=ns)
+    if kind == "lanczos":
+        s["v"] = _randn((prob.nd,), seed, torch.float64)
+        s["ws"] = torch.empty(h.chefsi_lanczos_workspace_bytes(), dtype=torch.uint8, device="cuda")
+        return s
+    if kind == "forces":
+        s["x"] = _block(case, seed)
+        s["ws"] = torch.empty(h.chefsi_forces_workspace_bytes(ns), dtype=torch.uint8, device="cuda")
+        s["occ"] = _occupations(ns)
+        s["disp"] = inputs.support_displacements(prob)
+        return s
+    s["ws"] = cs.workspace(h, ns)
+    if kind == "eigh":
+        s["h0"], s["m0"] = _pencil(ns, seed)
+        s["hs"], s["ms"] = torch.empty_like(s["h0"]), torch.empty_like(s["m0"])
+        s["d"] = torch.empty(ns, dtype=torch.float64, device="cuda")
+        return s
+    s["x0"] = _block(case, seed)
+    s["bounds"] = h.chefsi_spectral_bounds()
+    if case.get("tuned"):
+        h.chefsi_autotune(s["x0"], ns, s["ws"])
+    if kind == "rotate":
+        s["z"] = _rotation(ns, seed)
+    elif kind == "project":
+        s["hs"] = torch.empty((ns, ns), dtype=torch.float64, device="cuda")
+        s["ms"] = torch.empty_like(s["hs"])
+    else:
+        s["x"] = torch.empty_like(s["x0"])
+    return s
+
+
+def run(s):
+    h, ns, kind, case = s["h"], s["ns"], s["kind"], s["case"]
+    if kind == "apply":
+        h.chefsi_apply_h(s["x0"], s["x"], ns, s["ws"])
+        return s["x"]
+    if kind == "kpoint":
+        h.apply_h(s["x"], s["y"], ns, s["ws"])
+        return s["y"]
+    if kind == "lanczos":
+        return list(h.chefsi_lanczos_bound(s["v"], case["steps"], s["ws"]))
+    if kind == "forces":
+        return [h.chefsi_nonlocal_forces(s["x"], ns, s["occ"], s["ws"]),
+                h.chefsi_kinetic_stress(s["x"], ns, s["occ"], s["ws"]),
+                h.chefsi_nonlocal_stress(s["x"], ns, s["occ"], s["disp"], s["ws"])]
+    if kind == "eigh":
+        s["hs"].copy_(s["h0"])
+        s["ms"].copy_(s["m0"])
+        h.chefsi_eigh(s["hs"], s["ms"], s["d"], ns, s["ws"])
+        return [s["d"], s["hs"]]
+    if kind == "project":
+        h.chefsi_project(s["x0"], ns, s["hs"], s["ms"], s["ws"])
+        return [s["hs"], s["ms"]]
+    if kind == "rotate":  # in place by an orthogonal matrix: the block keeps its norms
+        h.chefsi_rotate(s["x0"], s["z"], ns, s["ws"])
+        return s["x0"]
+    # the program keeps its start block: filter, step and solve work on a copy of it
+    s["x"].copy_(s["x0"])
+    lo, cut, hi = s["bounds"]
+    if kind == "filter":
+        h.chefsi_filter(s["x"], ns, case["degree"], lo, cut, hi, s["ws"])
+        return s["x"]
+    if kind == "step":
+        return [h.chefsi_step(s["x"], ns, case["degree"], lo, cut, hi, s["ws"]), s["x"]]
+    # a converged orbital's sign is left to rounding: a solve answers with its Ritz values and
+    # bounds, as the serving loop's requests do (a step's block is compared above)
+    return list(h.chefsi_solve(s["x"], ns, case["degree"], case["n_iter"], lo, cut, hi, s["ws"]))
+
+
+def work(case):
+    prob = _problem(case)
+    kind, ns, nd, r = case["kind"], case.get("ns", 1), prob.nd, prob.fd_order // 2
+    b = 16 if kind == "kpoint" else 8 if _precision(case) == "fp64" else 4
+    c = 2 if kind == "kpoint" else 1                        # real operations per real operation
+    apply_f = c * ns * ((9 * r + 3) * nd + 4.0 * c * len(prob.chi))  # stencil and Veff, projectors both ways
+    fixed = 8 * (nd + len(prob.chi)) + 4 * len(prob.supp_idx)
+    gram_f = 2.0 * nd * ns * (ns + 1)                       # both products, upper triangles
+    rot_f = 2.0 * nd * ns * ns
+    eig_f = (4.0 / 3 + 1.0 / 3 + 2 + 1 + 2 + 4.0 / 3) * ns ** 3  # tridiagonal, Cholesky, reduction, back substitutions
+    block = float(nd) * ns * b
+    if kind in ("apply", "kpoint"):
+        return {"bytes": 2 * block + fixed, "flops": apply_f}
+    if kind == "lanczos":
+        return {"bytes": 8.0 * nd + fixed, "flops": case["steps"] * (apply_f + 8.0 * nd)}
+    if kind == "filter":
+        return {"bytes": 2 * block + fixed, "flops": case["degree"] * (apply_f + 4.0 * nd * ns)}
+    if kind == "forces":
+        grad_f = 9.0 * r * nd * ns
+        return {"bytes": 3 * block + 3 * fixed, "flops": 3 * grad_f + 12.0 * nd * ns + 17 * 2.0 * ns * len(prob.chi)}
+    if kind == "eigh":
+        return {"bytes": 24.0 * ns * ns, "flops": eig_f}
+    if kind == "rotate":
+        return {"bytes": 2 * block + 8.0 * ns * ns, "flops": rot_f}
+    if kind == "project":
+        return {"bytes": block + 16.0 * ns * ns + fixed, "flops": apply_f + gram_f}
+    one = (case["degree"] + 1) * apply_f + case["degree"] * 4.0 * nd * ns + gram_f + eig_f + rot_f
+    return {"bytes": 2 * block + fixed, "flops": case.get("n_iter", 1) * one}
+
+
+# ---------------------------------------------------------------------------
+# the same outputs in plain FP64
+# ---------------------------------------------------------------------------
+def _second_weights(r):
+    f = math.factorial
+    w = [-2.0 * sum(1.0 / (p * p) for p in range(1, r + 1))]
+    return w + [(1.0 if p % 2 else -1.0) * 2.0 * f(r) ** 2 / (p * p * f(r - p) * f(r + p)) for p in range(1, r + 1)]
+
+
+def _first_weights(r):
+    f = math.factorial
+    return [0.0] + [(1.0 if p % 2 else -1.0) * f(r) ** 2 / (p * f(r - p) * f(r + p)) for p in range(1, r + 1)]
+
+
+def _shift(u, p, axis, periodic, phase=None):
+    """u at +p grid points along axis (wrapped, times the cell phase across the face, or zero outside)."""
+    out = torch.roll(u, -p, dims=axis)
+    n = u.shape[axis]
+    edge = [slice(None)] * u.ndim
+    edge[axis] = slice(n - p, n) if p > 0 else slice(0, -p)
+    if not periodic:
+        out[tuple(edge)] = 0.0
+    elif phase is not None:
+        out[tuple(edge)] *= phase if p > 0 else phase.conjugate()
+    return out
+
+
+class _Exact:
+    """H (or H_k) on FP64 blocks, chunked over orbitals."""
+
+    def __init__(self, prob, kvec=None):
+        self.p, self.k = prob, kvec
+        dev = "cuda"
+        self.veff = torch.from_numpy(prob.veff).to(dev)
+        self.r = prob.fd_order // 2
+        self.w = _second_weights(self.r)
+        img = inputs.support_images(prob) if kvec is not None else None
+        self.atoms, c, q = [], 0, 0
+        for j in range(prob.n_atoms):
+            a, b = int(prob.supp_ptr[j]), int(prob.supp_ptr[j + 1])
+            np_j = int(prob.nproj[j])
+            chi = torch.from_numpy(prob.chi[c: c + (b - a) * np_j].reshape(np_j, b - a).copy()).to(dev)
+            if kvec is not None:
+                ph = sum(kvec[d] * prob.n[d] * prob.h[d] * img[a:b, d] for d in range(3))
+                chi = chi * torch.exp(1j * torch.from_numpy(np.asarray(ph, dtype=np.float64))).to(dev)
+            idx = torch.from_numpy(prob.supp_idx[a:b].astype(np.int64)).to(dev)
+            g = torch.from_numpy(prob.gamma[q: q + np_j].copy()).to(dev)
+            self.atoms.append((idx, chi, g, a, b))
+            c += (b - a) * np_j
+            q += np_j
+
+    def apply(self, x):
+        out = torch.empty_like(x)
+        step = max(1, int(4e8 / (self.p.nd * x.element_size() / 8)))
+        for v in range(0, x.shape[0], step):
+            out[v: v + step] = self._apply(x[v: v + step])
+        return out
+
+    def _apply(self, x):
+        nx, ny, nz = self.p.n
+        u = x.reshape(-1, nz, ny, nx)
+        y = u * (-0.5 * self.w[0] * sum(1.0 / h ** 2 for h in self.p.h) + self.veff.reshape(nz, ny, nx))
+        for d in range(3):
+            ph = None if self.k is None else complex(np.exp(1j * self.k[d] * self.p.n[d] * self.p.h[d]))
+            for p in range(1, self.r + 1):
+                f = -0.5 * self.w[p] / self.p.h[d] ** 2
+                for sgn in (p, -p):
+                    y += f * _shift(u, sgn, 3 - d, self.p.bc[d] == 0, ph)
+        y = y.reshape(x.shape)
+        for idx, chi, g, _, _ in self.atoms:
+            a = (x[:, idx] @ chi.conj().T) * (g * self.p.dv)
+            y[:, idx] += a @ chi
+        return y
+
+    def filter(self, x, m, lo, cut, hi):
+        c, e = 0.5 * (hi + cut), 0.5 * (hi - cut)
+        s1 = e / (lo - c)
+        sig = s1
+        y = (self.apply(x) - c * x) * (s1 / e)
+        for _ in range(1, m):
+            nxt = 1.0 / (2.0 / s1 - sig)
+            x, y = y, (self.apply(y) - c * y) * (2.0 * nxt / e) - x * (sig * nxt)
+            sig = nxt
+        return y
+
+    def bounds(self):
+        """The library's start bounds: Gershgorin, min Veff, a tenth of the width."""
+        s = abs(self.w[0]) + 2.0 * sum(abs(w) for w in self.w[1:])
+        kin = sum(0.5 * s / h ** 2 for h in self.p.h)
+        row = torch.zeros(self.p.nd, dtype=torch.float64, device="cuda")
+        for idx, chi, g, _, _ in self.atoms:
+            row[idx] += (g[:, None].abs() * chi.abs() * chi.abs().sum(1, keepdim=True)).sum(0) * self.p.dv
+        lo, hi = float(self.veff.min()), kin + float(self.veff.max()) + float(row.max())
+        return lo, lo + 0.1 * (hi - lo), hi
+
+    def step(self, x, m, lo, cut, hi):
+        y = self.filter(x, m, lo, cut, hi)
+        d, z = _generalized(y @ self.apply(y).T, y @ y.T)
+        return d, z.T @ y
+
+    def gradient(self, x, d):
+        nx, ny, nz = self.p.n
+        u = x.reshape(-1, nz, ny, nx)
+        c = _first_weights(self.r)
+        g = torch.zeros_like(u)
+        for p in range(1, self.r + 1):
+            per = self.p.bc[d] == 0
+            g += c[p] / self.p.h[d] * (_shift(u, p, 3 - d, per) - _shift(u, -p, 3 - d, per))
+        return g.reshape(x.shape)
+
+    def forces(self, x, occ, disp):
+        p = self.p
+        occ = torch.from_numpy(occ).to("cuda")
+        disp = torch.from_numpy(disp).to("cuda")
+        f = torch.zeros((p.n_atoms, 3), dtype=torch.float64, device="cuda")
+        kin = torch.zeros((3, 3), dtype=torch.float64, device="cuda")
+        nl = torch.zeros_like(kin)
+        step = max(1, int(4e8 / p.nd))
+        for v in range(0, x.shape[0], step):
+            xs, o = x[v: v + step], occ[v: v + step]
+            grad = [self.gradient(xs, d) for d in range(3)]
+            for a in range(3):
+                for b in range(a, 3):
+                    t = (o[:, None] * grad[a] * grad[b]).sum()
+                    kin[a, b] -= t / p.nd
+                    if a != b:
+                        kin[b, a] -= t / p.nd
+            for j, (idx, chi, g, s0, s1) in enumerate(self.atoms):
+                al = xs[:, idx] @ chi.T * p.dv
+                w = o[:, None] * g * al
+                nl -= torch.eye(3, dtype=torch.float64, device="cuda") * (w * al).sum() / (p.nd * p.dv)
+                for a in range(3):
+                    ga = grad[a][:, idx]
+                    f[j, a] -= 2.0 * (w * (ga @ chi.T * p.dv)).sum()
+                    for b in range(3):
+                        be = ga @ (chi * disp[s0:s1, b]).T * p.dv
+                        nl[a, b] -= 2.0 * (w * be).sum() / (p.nd * p.dv)
+        return [f.cpu().numpy(), kin.cpu().numpy(), nl.cpu().numpy()]
+
+    def lanczos(self, v, steps):
+        a, b = [], []
+        v = v / v.norm()
+        prev, beta = torch.zeros_like(v), 0.0
+        for _ in range(steps):
+            w = self.apply(v[None])[0] - beta * prev
+            alpha = float(v @ w)
+            w = w - alpha * v
+            beta = float(w.norm())
+            a.append(alpha)
+            b.append(beta)
+            prev, v = v, w / beta
+        t = np.diag(a) + np.diag(b[:-1], 1) + np.diag(b[:-1], -1)
+        d, s = np.linalg.eigh(t)
+        return [float(d[-1] + abs(b[-1] * s[-1, -1])), float(d[-1]), np.array(a), np.array(b)]
+
+
+def _generalized(hs, ms):
+    """Eigenvalues and Ms-orthonormal eigenvectors of the pencil, after a diagonal scaling."""
+    hs, ms = hs.cpu().numpy(), ms.cpu().numpy()
+    s = 1.0 / np.sqrt(np.diag(ms))
+    li = np.linalg.inv(np.linalg.cholesky(ms * s[:, None] * s[None, :]))
+    c = li @ (0.5 * (hs + hs.T) * s[:, None] * s[None, :]) @ li.T
+    d, w = np.linalg.eigh(0.5 * (c + c.T))
+    return d, torch.from_numpy((li.T @ w) * s[:, None]).to("cuda")
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind == "eigh":  # an eigenvector's sign is free
+        return [_generalized(*_pencil(case["ns"], seed))[0], None]
+    prob = _problem(case)
+    e = _Exact(prob, _kvec(prob) if kind == "kpoint" else None)
+    if kind == "lanczos":
+        return e.lanczos(_randn((prob.nd,), seed, torch.float64), case["steps"])
+    x = _block(case, seed)
+    if kind == "kpoint":
+        return e.apply(x)
+    x = x.double()
+    if kind == "apply":
+        return e.apply(x)
+    if kind == "filter":
+        return e.filter(x, case["degree"], *e.bounds())
+    if kind == "forces":
+        return e.forces(x, _occupations(case["ns"]), inputs.support_displacements(prob))
+    if kind == "rotate":
+        return _rotation(case["ns"], seed) @ x  # z is column-major: its row-major view is the transpose
+    if kind == "project":
+        hs, ms = x @ e.apply(x).T, x @ x.T
+        return [0.5 * (hs + hs.T), ms]
+    lo, cut, hi = e.bounds()
+    for _ in range(case.get("n_iter", 1)):
+        d, x = e.step(x, case["degree"], lo, cut, hi)
+        lo, cut = float(d[0]), float(d[-1])
+    return [d, lo, cut] if kind == "solve" else [d, None]  # an orbital's sign is free
