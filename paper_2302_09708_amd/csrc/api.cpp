@@ -153,8 +153,8 @@ struct chefsi_handle {
   int* ent_col = nullptr;
   double* ent_val64 = nullptr;
   float* ent_val32 = nullptr;
-  // pinned host staging for the small device-to-host reads of every step (Ritz values,
-  // dense-stage status, Cholesky pivots): max_ns doubles + 16 status words
+  // pinned host staging for the small device-to-host reads (Ritz values, dense-stage status,
+  // Cholesky pivots: max_ns doubles + 16 status words; force and stress sums: 10 per atom)
   double* pinned = nullptr;
   int n_pts = 0;     // scatter records
   int n_hxrec = 0;   // stencil-pass records
@@ -1483,7 +1483,8 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
     h->hx_plan = plan_hx(h->n[0], h->n[1], h->n[2], 1, h->radius, precision == CHEFSI_FP64 ? 8 : 4, 0, 0);
     check(h->hx_plan.ok, "no stencil tiling fits this grid");
 
-    if (hipHostMalloc((void**)&h->pinned, (size_t)max_ns * sizeof(double) + 64, hipHostMallocDefault) != hipSuccess) {
+    const size_t pinned_doubles = std::max((size_t)max_ns + 8, (size_t)h->n_atoms * 10);
+    if (hipHostMalloc((void**)&h->pinned, pinned_doubles * sizeof(double), hipHostMallocDefault) != hipSuccess) {
       h->pinned = nullptr;
       throw Error{CHEFSI_ERR_OOM, "pinned host allocation failed"};
     }
@@ -1944,42 +1945,31 @@ void lanczos_impl(chefsi_handle* h, const TV* v0, int steps, void* ws, const LzL
 }
 
 // ---------------------------------------------------------------------------
-// Nonlocal forces.  Workspace: one gradient block (FP64, Nd x ns), the two coefficient
-// blocks (np_tot x ns FP64), dV per projector column, occupations, forces.
+// Nonlocal forces and stresses.  Workspace: the partial sums (over atoms and orbitals, or
+// over the blocks of the kinetic stress), occupations, the per-atom or total sums, and the
+// support-point displacements.  The sizes are those the calls have always asked for (an FP64
+// Nd x ns block, two coefficient blocks, three copies of the projector values): the partial
+// sums need less, unless the atoms outnumber a tenth of the grid points.
 // ---------------------------------------------------------------------------
 struct FoLayout {
-  size_t grad = 0, alpha = 0, beta = 0, dvc = 0, occ = 0, forces = 0, spart = 0, disp = 0, chiw = 0, nlsum = 0,
-         total = 0;
+  size_t part = 0, occ = 0, sums = 0, disp = 0, total = 0;
+  int64_t part_doubles = 0;
 };
 
 FoLayout forces_layout(const chefsi_handle* h, int ns) {
   FoLayout L;
-  const size_t np = (size_t)std::max(1, h->np_tot);
-  size_t off = 0;
-  L.grad = off;
-  off += align256((size_t)h->nd * ns * 8);
-  L.alpha = off;
-  off += align256(np * ns * 8);
-  L.beta = off;
-  off += align256(np * ns * 8);
-  L.dvc = off;
-  off += align256(np * 8);
+  const size_t np = (size_t)std::max(1, h->np_tot), na = (size_t)std::max(1, h->n_atoms);
+  const size_t part = align256((size_t)h->nd * ns * 8) + 2 * align256(np * ns * 8) + align256(np * 8);
+  size_t off = std::max(part, align256((size_t)h->n_atoms * ns * 10 * 8));
+  L.part_doubles = (int64_t)(off / 8);
   L.occ = off;
   off += align256((size_t)ns * 8);
-  L.forces = off;
-  off += align256((size_t)std::max(1, h->n_atoms) * 3 * 8);
-  L.spart = off;  // stress block sums (kVecBlocks x 6) and the six totals
-  off += align256(((size_t)kVecBlocks * 6 + 8) * 8);
-  // nonlocal stress: support-point displacements, the three displacement-weighted copies of
-  // the projector values, and per-atom sums (energy + one n_atoms x 3 block per gradient
-  // direction)
-  const size_t nsupp = h->supp_idx_h.size(), nchi = h->chi_h.size();
+  off += align256(na * 3 * 8) + align256(((size_t)kVecBlocks * 6 + 8) * 8);
   L.disp = off;
-  off += align256(std::max<size_t>(1, 3 * nsupp) * 8);
-  L.chiw = off;
-  off += align256(std::max<size_t>(1, 3 * nchi) * 8);
-  L.nlsum = off;
-  off += align256((size_t)std::max(1, h->n_atoms) * 12 * 8);
+  off += align256(std::max<size_t>(1, 3 * h->supp_idx_h.size()) * 8);
+  off += align256(std::max<size_t>(1, 3 * h->chi_h.size()) * 8);
+  L.sums = off;
+  off += align256(na * 12 * 8);
   L.total = off;
   return L;
 }
@@ -1997,153 +1987,12 @@ std::vector<double> first_derivative_weights(int r) {
   return c;
 }
 
-template <typename TV>
-void forces_impl(chefsi_handle* h, const TV* X, int ns, const double* occ_host, void* ws, const FoLayout& L,
-                 hipStream_t s, double* forces_host) {
-  const std::vector<double> dvc(std::max(1, h->np_tot), h->dv);
-  HIP_TRY(hipMemcpyAsync(at<double>(ws, L.dvc), dvc.data(), dvc.size() * 8, hipMemcpyHostToDevice, s));
+// Arguments of the force and stress kernels shared by the three calls: the block, its
+// occupations (copied to the workspace) and the FD first-derivative weights.
+template <typename TA, typename TV>
+void gradient_args(chefsi_handle* h, TA& a, const TV* X, int ns, const double* occ_host, void* ws, const FoLayout& L,
+                   hipStream_t s) {
   HIP_TRY(hipMemcpyAsync(at<double>(ws, L.occ), occ_host, (size_t)ns * 8, hipMemcpyHostToDevice, s));
-  double* alpha = at<double>(ws, L.alpha);
-  double* beta = at<double>(ws, L.beta);
-  double* grad = at<double>(ws, L.grad);
-  const double* dv = at<double>(ws, L.dvc);
-  HIP_TRY((launch_nl_project<TV, double>(nl_args<TV, double>(h, X, ns, h->chi64, dv, alpha), s)));
-  const std::vector<double> c = first_derivative_weights(h->radius);
-  for (int d = 0; d < 3; ++d) {
-    GradArgs<TV> g{};
-    g.x = X;
-    g.out = grad;
-    g.nd = h->nd;
-    g.nx = h->n[0];
-    g.ny = h->n[1];
-    g.nz = h->n[2];
-    g.dir = d;
-    g.r = h->radius;
-    g.periodic = h->bc[d] == 0 ? 1 : 0;
-    for (int p = 0; p <= h->radius; ++p) g.c[p] = c[p];
-    g.inv_h = 1.0 / h->h[d];
-    HIP_TRY(launch_grad<TV>(g, ns, s));
-    HIP_TRY((launch_nl_project<double, double>(nl_args<double, double>(h, grad, ns, h->chi64, dv, beta), s)));
-    ForceArgs f{};
-    f.alpha = alpha;
-    f.beta = beta;
-    f.occ = at<double>(ws, L.occ);
-    f.gdv = h->gdv64;
-    f.nproj = h->nproj;
-    f.poff = h->poff;
-    f.dv = h->dv;
-    f.n_atoms = h->n_atoms;
-    f.np_tot = h->np_tot;
-    f.ns = ns;
-    f.dir = d;
-    f.forces = at<double>(ws, L.forces);
-    HIP_TRY(launch_forces(f, s));
-  }
-  double* pin = nullptr;
-  const size_t fb = (size_t)h->n_atoms * 3 * 8;
-  HIP_TRY(hipHostMalloc((void**)&pin, fb, hipHostMallocDefault));
-  hipError_t e = hipMemcpyAsync(pin, at<double>(ws, L.forces), fb, hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e == hipSuccess) std::memcpy(forces_host, pin, fb);
-  (void)hipHostFree(pin);
-  HIP_TRY(e);
-}
-
-// Nonlocal stress (see chefsi.h): alpha = dV chi^T psi, then per gradient direction a the
-// gathers beta_ab = dV (chi d_b)^T (d psi / dx_a) and the per-atom sums
-// -2 sum_k gamma_k sum_v g_v alpha beta_ab (force_kernel), and the energy's per-atom sums
-// from beta = alpha; the atom sums are added on the host in atom order.
-template <typename TV>
-void nonlocal_stress_impl(chefsi_handle* h, const TV* X, int ns, const double* occ_host, const double* disp_host,
-                          void* ws, const FoLayout& L, hipStream_t s, double* stress_host) {
-  const int na = h->n_atoms;
-  const size_t nsupp = h->supp_idx_h.size(), nchi = h->chi_h.size();
-  const std::vector<double> dvc(std::max(1, h->np_tot), h->dv);
-  HIP_TRY(hipMemcpyAsync(at<double>(ws, L.dvc), dvc.data(), dvc.size() * 8, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(at<double>(ws, L.occ), occ_host, (size_t)ns * 8, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(at<double>(ws, L.disp), disp_host, 3 * nsupp * 8, hipMemcpyHostToDevice, s));
-  double* chiw = at<double>(ws, L.chiw);
-  ChiDispArgs cd{};
-  cd.chi = h->chi64;
-  cd.disp = at<double>(ws, L.disp);
-  cd.supp_off = h->supp_off;
-  cd.chi_off = h->chi_off;
-  cd.nproj = h->nproj;
-  cd.n_atoms = na;
-  cd.nchi = (int64_t)nchi;
-  cd.out = chiw;
-  HIP_TRY(launch_chi_disp(cd, s));
-  double* alpha = at<double>(ws, L.alpha);
-  double* beta = at<double>(ws, L.beta);
-  double* grad = at<double>(ws, L.grad);
-  double* sums = at<double>(ws, L.nlsum);  // [0]: energy, [1 + a]: direction a; n_atoms x 3 each
-  const double* dv = at<double>(ws, L.dvc);
-  HIP_TRY((launch_nl_project<TV, double>(nl_args<TV, double>(h, X, ns, h->chi64, dv, alpha), s)));
-  ForceArgs f{};
-  f.alpha = alpha;
-  f.occ = at<double>(ws, L.occ);
-  f.gdv = h->gdv64;
-  f.nproj = h->nproj;
-  f.poff = h->poff;
-  f.dv = h->dv;
-  f.n_atoms = na;
-  f.np_tot = h->np_tot;
-  f.ns = ns;
-  f.beta = alpha;
-  f.dir = 0;
-  f.forces = sums;
-  HIP_TRY(launch_forces(f, s));
-  const std::vector<double> c = first_derivative_weights(h->radius);
-  for (int a = 0; a < 3; ++a) {
-    GradArgs<TV> g{};
-    g.x = X;
-    g.out = grad;
-    g.nd = h->nd;
-    g.nx = h->n[0];
-    g.ny = h->n[1];
-    g.nz = h->n[2];
-    g.dir = a;
-    g.r = h->radius;
-    g.periodic = h->bc[a] == 0 ? 1 : 0;
-    for (int p = 0; p <= h->radius; ++p) g.c[p] = c[p];
-    g.inv_h = 1.0 / h->h[a];
-    HIP_TRY(launch_grad<TV>(g, ns, s));
-    for (int b = 0; b < 3; ++b) {
-      HIP_TRY((launch_nl_project<double, double>(
-          nl_args<double, double>(h, grad, ns, chiw + (size_t)b * nchi, dv, beta), s)));
-      f.beta = beta;
-      f.dir = b;
-      f.forces = sums + (size_t)(1 + a) * na * 3;
-      HIP_TRY(launch_forces(f, s));
-    }
-  }
-  const size_t nb = (size_t)na * 12 * 8;
-  double* pin = nullptr;
-  HIP_TRY(hipHostMalloc((void**)&pin, nb, hipHostMallocDefault));
-  hipError_t e = hipMemcpyAsync(pin, sums, nb, hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  std::vector<double> hs;
-  if (e == hipSuccess) hs.assign(pin, pin + (size_t)na * 12);
-  (void)hipHostFree(pin);
-  HIP_TRY(e);
-  // energy: force_kernel gave -2 sum gamma g alpha^2 per atom (component 0)
-  double e_nl = 0.0;
-  for (int J = 0; J < na; ++J) e_nl += -0.5 * hs[(size_t)J * 3];
-  const double omega = (double)h->nd * h->dv;
-  for (int a = 0; a < 3; ++a)
-    for (int b = 0; b < 3; ++b) {
-      double t = 0.0;  // -2 sum g gamma alpha beta_ab
-      for (int J = 0; J < na; ++J) t += hs[(size_t)(1 + a) * na * 3 + (size_t)J * 3 + b];
-      stress_host[a * 3 + b] = -((a == b ? e_nl : 0.0) - t) / omega;
-    }
-}
-
-template <typename TV>
-void kinetic_stress_impl(chefsi_handle* h, const TV* X, int ns, const double* occ_host, void* ws, const FoLayout& L,
-                         hipStream_t s, double* stress_host) {
-  HIP_TRY(hipMemcpyAsync(at<double>(ws, L.occ), occ_host, (size_t)ns * 8, hipMemcpyHostToDevice, s));
-  const std::vector<double> c = first_derivative_weights(h->radius);
-  StressArgs<TV> a{};
   a.x = X;
   a.occ = at<double>(ws, L.occ);
   a.nd = h->nd;
@@ -2151,20 +2000,69 @@ void kinetic_stress_impl(chefsi_handle* h, const TV* X, int ns, const double* oc
   a.nx = h->n[0];
   a.ny = h->n[1];
   a.nz = h->n[2];
-  a.r = h->radius;
+  const std::vector<double> c = first_derivative_weights(h->radius);
   for (int d = 0; d < 3; ++d) {
     a.periodic[d] = h->bc[d] == 0 ? 1 : 0;
-    a.inv_h[d] = 1.0 / h->h[d];
+    for (int p = 1; p <= h->radius; ++p) a.c[d][p] = c[p] / h->h[d];
   }
-  for (int p = 0; p <= h->radius; ++p) a.c[p] = c[p];
-  a.partial = at<double>(ws, L.spart);
-  a.out = a.partial + (size_t)kVecBlocks * 6;
-  HIP_TRY(launch_stress_sums<TV>(a, s));
-  double* pin = h->pinned;  // max_ns + 8 doubles; six needed
-  double sums[6];
-  HIP_TRY(hipMemcpyAsync(pin, a.out, 6 * sizeof(double), hipMemcpyDeviceToHost, s));
+}
+
+// n doubles at device address d to the handle's pinned staging, after the stream's work.
+const double* read_pinned(chefsi_handle* h, const double* d, size_t n, hipStream_t s) {
+  HIP_TRY(hipMemcpyAsync(h->pinned, d, n * 8, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  std::memcpy(sums, pin, sizeof(sums));
+  return h->pinned;
+}
+
+// Per-atom sums of the nonlocal forces (3 values per atom, times -2) or, with the support
+// displacements, of the nonlocal stress (10 values per atom: energy, then direction pairs).
+template <typename TV>
+const double* nonlocal_sums(chefsi_handle* h, const TV* X, int ns, const double* occ_host, const double* disp_host,
+                            void* ws, const FoLayout& L, hipStream_t s) {
+  NlGradArgs<TV> a{};
+  gradient_args(h, a, X, ns, occ_host, ws, L, s);
+  if (disp_host != nullptr) {
+    HIP_TRY(hipMemcpyAsync(at<double>(ws, L.disp), disp_host, 3 * h->supp_idx_h.size() * 8, hipMemcpyHostToDevice, s));
+    a.disp = at<double>(ws, L.disp);
+  }
+  a.n_atoms = h->n_atoms;
+  a.supp_off = h->supp_off;
+  a.supp_idx = h->supp_idx;
+  a.chi_off = h->chi_off;
+  a.nproj = h->nproj;
+  a.poff = h->poff;
+  a.chi = h->chi64;
+  a.gdv = h->gdv64;
+  a.dv = h->dv;
+  a.part = at<double>(ws, L.part);
+  double* out = at<double>(ws, L.sums);
+  HIP_TRY((launch_nl_grad<TV>(a, h->radius, out, disp_host != nullptr ? 1.0 : -2.0, s)));
+  return read_pinned(h, out, (size_t)h->n_atoms * (disp_host != nullptr ? 10 : 3), s);
+}
+
+// Nonlocal stress (see chefsi.h): the per-atom sums of the energy and of the nine direction
+// pairs, added on the host in atom order.
+template <typename TV>
+void nonlocal_stress_impl(chefsi_handle* h, const TV* X, int ns, const double* occ_host, const double* disp_host,
+                          void* ws, const FoLayout& L, hipStream_t s, double* stress_host) {
+  const double* sums = nonlocal_sums<TV>(h, X, ns, occ_host, disp_host, ws, L, s);
+  const double omega = (double)h->nd * h->dv;
+  double t[10] = {0.0};
+  for (int J = 0; J < h->n_atoms; ++J)
+    for (int k = 0; k < 10; ++k) t[k] += sums[(size_t)J * 10 + k];
+  for (int a = 0; a < 3; ++a)
+    for (int b = 0; b < 3; ++b) stress_host[a * 3 + b] = -((a == b ? t[0] : 0.0) + 2.0 * t[1 + 3 * a + b]) / omega;
+}
+
+template <typename TV>
+void kinetic_stress_impl(chefsi_handle* h, const TV* X, int ns, const double* occ_host, void* ws, const FoLayout& L,
+                         hipStream_t s, double* stress_host) {
+  StressArgs<TV> a{};
+  gradient_args(h, a, X, ns, occ_host, ws, L, s);
+  a.partial = at<double>(ws, L.part);
+  a.out = at<double>(ws, L.sums);
+  HIP_TRY(launch_stress_sums<TV>(a, h->radius, L.part_doubles / 6, s));
+  const double* sums = read_pinned(h, a.out, 6, s);
   // sigma_ab = -(dV / Omega) sum = -(1 / Nd) sum, Omega = Nd dV
   const int ia[6] = {0, 1, 2, 0, 0, 1}, ib[6] = {0, 1, 2, 1, 2, 2};
   for (int k = 0; k < 6; ++k) {
@@ -2242,10 +2140,12 @@ int chefsi_nonlocal_forces(chefsi_handle_t* h, const void* X, int32_t ns, const 
     const FoLayout L = forces_layout(h, ns);
     if (ws_bytes < L.total) throw Error{CHEFSI_ERR_WORKSPACE, "workspace smaller than chefsi_forces_workspace_bytes"};
     hipStream_t s = (hipStream_t)stream;
+    const double* f;
     if (h->precision == CHEFSI_FP64)
-      forces_impl<double>(h, (const double*)X, ns, occ_host, ws, L, s, forces_host);
+      f = nonlocal_sums<double>(h, (const double*)X, ns, occ_host, nullptr, ws, L, s);
     else
-      forces_impl<float>(h, (const float*)X, ns, occ_host, ws, L, s, forces_host);
+      f = nonlocal_sums<float>(h, (const float*)X, ns, occ_host, nullptr, ws, L, s);
+    std::memcpy(forces_host, f, (size_t)h->n_atoms * 3 * 8);
   });
 }
 
@@ -2867,7 +2767,8 @@ int chefsi_kpoint_create(const chefsi_grid_t* grid, const double* veff_host, con
     HIP_TRY(hipGetDevice(&h->device));
     BLAS_TRY(rocblas_create_handle(&h->blas));
     BLAS_TRY(rocblas_set_atomics_mode(h->blas, rocblas_atomics_not_allowed));
-    if (hipHostMalloc((void**)&h->pinned, (size_t)max_ns * sizeof(double) + 64, hipHostMallocDefault) != hipSuccess) {
+    const size_t pinned_doubles = std::max((size_t)max_ns + 8, (size_t)h->n_atoms * 10);
+    if (hipHostMalloc((void**)&h->pinned, pinned_doubles * sizeof(double), hipHostMallocDefault) != hipSuccess) {
       h->pinned = nullptr;
       throw Error{CHEFSI_ERR_OOM, "pinned host allocation failed"};
     }

@@ -254,67 +254,58 @@ hipError_t launch_rotate_bf16x3(const float* X, const double* Z, void* zsplit, f
                                 hipStream_t s);
 
 // ---------------------------------------------------------------------------
-// Nonlocal forces: out = d x / d x_dir (central FD, c[1..r], periodic or zero ghosts),
-// then forces[J*3 + dir] = -2 sum_k (gdv[q]/dv) sum_v occ[v] alpha[v*np+q] beta[v*np+q].
+// Nonlocal force and stress sums over (atom J, orbital v), a_k = dV chi_k^T psi_v:
+//   forces (disp null), d = 0..2:  part[J, v, d] = occ[v] sum_k gamma_k a_k dV chi_k^T (d psi_v / dx_d)
+//   stress: part[J, v, 0] = occ[v] sum_k gamma_k a_k^2 and, at 1 + 3 a + b,
+//           occ[v] sum_k gamma_k a_k dV (chi_k d_b)^T (d psi_v / dx_a), d_b = disp
+// with the central FD first derivative of radius r (periodic wrap or zero ghosts), then
+// out[J, d] = scale * sum_v part[J, v, d] (fixed order; 3 or 10 values per atom).
 // ---------------------------------------------------------------------------
 template <typename TV>
-struct GradArgs {
+struct NlGradArgs {
   const TV* x;
-  double* out;
-  int64_t nd;
-  int nx, ny, nz;
-  int dir, r, periodic;
-  double c[kMaxRadius + 1];
-  double inv_h;
-};
-
-struct ForceArgs {
-  const double* alpha;
-  const double* beta;
   const double* occ;
-  const double* gdv;
+  int64_t nd;
+  int ns;
+  int nx, ny, nz;
+  int periodic[3];
+  double c[3][kMaxRadius + 1];  // first-derivative weights over h_d
+  int n_atoms;
+  const int* supp_off;     // as NlArgs
+  const int* supp_idx;
+  const int64_t* chi_off;
   const int* nproj;
   const int* poff;
+  const double* chi;
+  const double* disp;      // 3 per support point (stress), null for the forces
+  const double* gdv;       // gamma dV per projector column
   double dv;
-  int n_atoms, np_tot, ns, dir;
-  double* forces;
+  double* part;            // n_atoms * ns * (3 or 10)
+  int ngroups, per_xcd;    // set by the launcher
 };
 
 template <typename TV>
-hipError_t launch_grad(const GradArgs<TV>& a, int ns, hipStream_t s);
+hipError_t launch_nl_grad(const NlGradArgs<TV>& a, int radius, double* out, double scale, hipStream_t s);
 
 // Kinetic stress sums: out[0..5] = sum_v occ[v] sum_i g_a g_b for ab = xx, yy, zz, xy, xz,
-// yz (g = FD gradient of orbital v); partial: kVecBlocks * 6 doubles of scratch.
+// yz (g = FD gradient of orbital v); partial: max_partials * 6 doubles of scratch.
 template <typename TV>
 struct StressArgs {
   const TV* x;
   const double* occ;
   int64_t nd;
   int ns;
-  int nx, ny, nz, r;
+  int nx, ny, nz;
   int periodic[3];
-  double c[kMaxRadius + 1];
-  double inv_h[3];
+  double c[3][kMaxRadius + 1];  // first-derivative weights over h_d
   double* partial;
   double* out;
+  int nyg, ty, nty, zc, nzc, pitch;  // tiling, set by the launcher
+  int64_t nunits;
 };
 
 template <typename TV>
-hipError_t launch_stress_sums(const StressArgs<TV>& a, hipStream_t s);
-// Nonlocal stress weights: out[b * nchi + e] = chi[e] * disp[3 s + b] (b = 0..2) for every
-// projector value e (atom-major, the layout of chi) at its support point s.
-struct ChiDispArgs {
-  const double* chi;
-  const double* disp;     // 3 per support point, support-point order of supp_idx
-  const int* supp_off;    // n_atoms + 1
-  const int64_t* chi_off; // n_atoms
-  const int* nproj;       // n_atoms
-  int n_atoms;
-  int64_t nchi;
-  double* out;            // 3 * nchi
-};
-hipError_t launch_chi_disp(const ChiDispArgs& a, hipStream_t s);
-hipError_t launch_forces(const ForceArgs& a, hipStream_t s);
+hipError_t launch_stress_sums(const StressArgs<TV>& a, int radius, int64_t max_partials, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // Lanczos vector kernels (fixed grid of kVecBlocks x kVecThreads, fixed-order sums).

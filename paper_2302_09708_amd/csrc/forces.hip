@@ -1,179 +1,469 @@
-// Nonlocal Hellmann-Feynman forces (Sec. 2: the filter's stencil and projector routines
-// reused for the force: the gradient operator on the orbitals, then the nonlocal
-// projectors on the result).  With a = dV chi^T psi and b_d = dV chi^T (d psi / dx_d)
-// from the projector gather (nl_project with dV in place of gamma dV),
+// Nonlocal Hellmann-Feynman forces and the kinetic and nonlocal stresses (Sec. 2: the
+// filter's stencil and projector routines reused for the force: the gradient operator on
+// the orbitals, then the nonlocal projectors on the result).
 //
-//   F_J,d = -2 sum_n g_n sum_a gamma_Ja a_Ja,n b_d,Ja,n .
-//
-// grad_kernel: the central FD first derivative of order 2r along one direction, one
-// thread per (point, orbital), periodic wrap or zero ghosts; FP64 output.
-// force_kernel: one thread per atom, fixed summation order (bitwise reproducible).
-#include "common.h"
+// nl_grad_kernel: with a = dV chi^T psi and b_d = dV chi^T (d psi / dx_d), per atom J and
+//   orbital n the sums  sum_k gamma_k a_k b_d,k  of the forces, or  sum_k gamma_k a_k^2  and
+//   sum_k gamma_k a_k dV (chi_k d_b)^T (d psi / dx_a)  of the nonlocal stress, times the
+//   occupation.  The gradient is formed only where a projector reads it, from the 6r
+//   neighbours of each support point, and never leaves registers.  atom_sums_kernel adds
+//   the orbitals of an atom in a fixed order.
+// kinetic_stress_kernel: the six products of the gradient's components summed over the
+//   grid in one z march over each orbital (the layout of the filter's stencil pass).
+// Every sum has a fixed order (bitwise reproducible); FP64 arithmetic.
+#include <algorithm>
+
+#include "stencil.h"
 
 namespace chefsi {
 
 namespace {
 
-template <typename TV>
-__global__ __launch_bounds__(256) void grad_kernel(GradArgs<TV> a) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= a.nd) return;
-  const int64_t v = blockIdx.y;
-  const int x = (int)(i % a.nx), y = (int)((i / a.nx) % a.ny), z = (int)(i / ((int64_t)a.nx * a.ny));
-  const int c = a.dir == 0 ? x : (a.dir == 1 ? y : z);
-  const int n = a.dir == 0 ? a.nx : (a.dir == 1 ? a.ny : a.nz);
-  const int64_t stride = a.dir == 0 ? 1 : (a.dir == 1 ? (int64_t)a.nx : (int64_t)a.nx * a.ny);
-  const TV* col = a.x + v * a.nd;
-  const int64_t base = i - (int64_t)c * stride;
-  double g = 0.0;
-  for (int p = 1; p <= a.r; ++p) {
-    int cp = c + p, cm = c - p;
-    double fp, fm;
-    if (a.periodic) {
-      cp %= n;
-      cm = ((cm % n) + n) % n;
-      fp = double(col[base + cp * stride]);
-      fm = double(col[base + cm * stride]);
-    } else {
-      fp = cp < n ? double(col[base + cp * stride]) : 0.0;
-      fm = cm >= 0 ? double(col[base + cm * stride]) : 0.0;
+// v[i] summed over the 64 lanes for every i < N (N a power of two, at most 64): each of the
+// first log2 N exchanges halves the values a lane keeps, so lane l ends with the sum of
+// value l / (64 / N) in v[0] after N - 1 + log2(64 / N) exchanges (6 N for N plain sums).
+template <int M, int OFF, int N>
+__device__ __forceinline__ void wave_sums_step(double (&v)[N], int lane) {
+  if constexpr (M >= 1) {
+    const bool up = lane & OFF;
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+      const double keep = up ? v[i + M] : v[i];
+      const double give = up ? v[i] : v[i + M];
+      v[i] = keep + __shfl_xor(give, OFF, 64);
     }
-    g += a.c[p] * (fp - fm);
+    wave_sums_step<M / 2, OFF / 2>(v, lane);
+  } else if constexpr (OFF >= 1) {
+    v[0] += __shfl_xor(v[0], OFF, 64);
+    wave_sums_step<0, OFF / 2>(v, lane);
   }
-  a.out[v * a.nd + i] = g * a.inv_h;
+}
+template <int N>
+__device__ __forceinline__ void wave_sums(double (&v)[N], int lane) {
+  wave_sums_step<N / 2, 32>(v, lane);
 }
 
-__global__ __launch_bounds__(256) void force_kernel(ForceArgs a) {
-  const int J = blockIdx.x * 256 + threadIdx.x;
-  if (J >= a.n_atoms) return;
-  double acc = 0.0;
-  for (int k = 0; k < a.nproj[J]; ++k) {
-    const int q = a.poff[J] + k;
-    const double gam = a.gdv[q] / a.dv;
+constexpr int kNgWaves = 4;  // waves per block: one atom, consecutive orbital groups
+constexpr int kNgP = 4;      // projectors per pass
+
+// One wave = one atom x V orbitals; a lane owns every 64th support point.  A point's 6r + 1
+// byte offsets are computed once and serve the V orbitals (Dirichlet ghosts are offsets
+// past the end, which load zero).  Bound by the 6r + 1 cached loads per (support point,
+// orbital), about 58 cycles of a CU each (eight to twelve lines, mostly from L2): 72^3, 128
+// atoms, 600 orbitals, order 12 measured 3.8 ms (forces) and 3.9 ms (stress) where writing
+// and re-reading whole gradients took 11.3 and 18.5 ms (three gradient passes of 2.6 ms,
+// four or ten gathers of 0.26 ms and 0.8 ms of sums after each).
+// The stress keeps 40 sums per orbital, so its waves own one orbital, the forces' two.
+// XCD mapping: each XCD takes a contiguous run of (orbital group, atom), atom fastest, so
+// neighbouring atoms read an orbital's shared points through one L2.
+template <typename TV, int R, bool STRESS>
+__global__ __launch_bounds__(64 * kNgWaves) void nl_grad_kernel(NlGradArgs<TV> a) {
+  constexpr int V = STRESS ? 1 : 2;
+  constexpr int NB = STRESS ? 9 : 3;         // gathers of the gradient per projector
+  constexpr int NS = NB * kNgP;              // their sums; the kNgP sums of psi beside them
+  constexpr int NR = STRESS ? 32 : 16;       // power of two of the first reduction
+  constexpr int NO = STRESS ? 10 : 3;        // results per (atom, orbital)
+  constexpr int NA = kNgP + NS;              // 16 or 40 sums per orbital
+  __shared__ double red[kNgWaves][NA];
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int64_t logical = (int64_t)(blockIdx.x % 8) * a.per_xcd + blockIdx.x / 8;
+  if (logical >= (int64_t)a.n_atoms * a.ngroups) return;
+  const int atom = (int)(logical % a.n_atoms);
+  const int v0 = ((int)(logical / a.n_atoms) * kNgWaves + wave) * V;
+  const int s0 = a.supp_off[atom];
+  const int n = a.supp_off[atom + 1] - s0;
+  const int npj = a.nproj[atom];
+  const double* chi = a.chi + a.chi_off[atom];
+  const int nx = a.nx, ny = a.ny, nz = a.nz, nplane = nx * ny;
+  const bool live = v0 < a.ns;  // waves past the block width only meet the barriers
+  const int nbytes = (int)(a.nd * (int64_t)sizeof(TV));
+  __amdgpu_buffer_rsrc_t rx[V];
+#pragma unroll
+  for (int u = 0; u < V; ++u) rx[u] = make_rsrc(a.x + (int64_t)min(v0 + u, a.ns - 1) * a.nd, nbytes);
+  double tot[V];  // lane d < NO: result d of orbital u
+#pragma unroll
+  for (int u = 0; u < V; ++u) tot[u] = 0.0;
+
+  for (int a0 = 0; a0 < npj; a0 += kNgP) {
+    double acc[V][NA];
+#pragma unroll
+    for (int u = 0; u < V; ++u)
+#pragma unroll
+      for (int k = 0; k < NA; ++k) acc[u][k] = 0.0;
+    if (live) {
+      for (int s = lane; s < n; s += 64) {
+        const int i = a.supp_idx[s0 + s];
+        const int z = i / nplane, yx = i - z * nplane, y = yx / nx, x = yx - y * nx;
+        unsigned off[3][2][R];
+#pragma unroll
+        for (int p = 1; p <= R; ++p) {
+          const int cp[3] = {x + p, y + p, z + p}, cm[3] = {x - p, y - p, z - p};
+          const int ext[3] = {nx, ny, nz}, str[3] = {1, nx, nplane};
+#pragma unroll
+          for (int d = 0; d < 3; ++d) {  // n >= r in a periodic direction: one wrap
+            const int jp = i + p * str[d], jm = i - p * str[d];
+            const bool op = cp[d] >= ext[d], om = cm[d] < 0;
+            off[d][0][p - 1] = lane_off<TV>(!op ? jp : (a.periodic[d] ? jp - ext[d] * str[d] : -1));
+            off[d][1][p - 1] = lane_off<TV>(!om ? jm : (a.periodic[d] ? jm + ext[d] * str[d] : -1));
+          }
+        }
+        double c[kNgP];
+#pragma unroll
+        for (int k = 0; k < kNgP; ++k) c[k] = a0 + k < npj ? chi[(int64_t)(a0 + k) * n + s] : 0.0;
+        double w[3] = {1.0, 1.0, 1.0};
+        if (STRESS) {
+#pragma unroll
+          for (int b = 0; b < 3; ++b) w[b] = a.disp[3 * (int64_t)(s0 + s) + b];
+        }
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+          const double yv = double(bload<TV>(rx[u], lane_off<TV>(i), 0u));
+#pragma unroll
+          for (int k = 0; k < kNgP; ++k) acc[u][k] += c[k] * yv;
+#pragma unroll
+          for (int d = 0; d < 3; ++d) {
+            double g = 0.0;
+#pragma unroll
+            for (int p = 0; p < R; ++p)
+              g += a.c[d][p + 1] * (double(bload<TV>(rx[u], off[d][0][p], 0u)) - double(bload<TV>(rx[u], off[d][1][p], 0u)));
+            if (STRESS) {
+#pragma unroll
+              for (int b = 0; b < 3; ++b)
+#pragma unroll
+                for (int k = 0; k < kNgP; ++k) acc[u][kNgP + (3 * d + b) * kNgP + k] += (c[k] * w[b]) * g;
+            } else {
+#pragma unroll
+              for (int k = 0; k < kNgP; ++k) acc[u][kNgP + d * kNgP + k] += c[k] * g;
+            }
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+      double h[NR];
+#pragma unroll
+      for (int k = 0; k < NR; ++k) h[k] = acc[u][k];
+      wave_sums<NR>(h, lane);
+      if (lane % (64 / NR) == 0) red[wave][lane / (64 / NR)] = h[0];
+      if constexpr (STRESS) {  // the other eight of the forty
+        double g[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) g[k] = acc[u][NR + k];
+        wave_sums<8>(g, lane);
+        if (lane % 8 == 0) red[wave][NR + lane / 8] = g[0];
+      }
+      __syncthreads();
+      if (lane < NO) {
+        // result `lane`: the energy sum gamma a^2 (stress, lane 0), else sum gamma a b
+        const int b = STRESS ? (lane == 0 ? 0 : lane) : lane + 1;  // block of kNgP sums in red
+        for (int k = 0; k < kNgP && a0 + k < npj; ++k)
+          tot[u] += a.gdv[a.poff[atom] + a0 + k] * (red[wave][k] * red[wave][b * kNgP + k]);
+      }
+      __syncthreads();
+    }
+  }
+  if (live && lane < NO) {
+#pragma unroll
+    for (int u = 0; u < V; ++u)  // gdv holds gamma dV: two factors dV, one taken from gdv
+      if (v0 + u < a.ns) a.part[((int64_t)atom * a.ns + v0 + u) * NO + lane] = a.occ[v0 + u] * tot[u] * a.dv;
+  }
+}
+
+// out[J * no + d] = scale * sum over orbitals of part[(J * ns + v) * no + d], one block per
+// atom: thread t adds orbitals t, t + 256, ..., then a tree over the threads.
+__global__ __launch_bounds__(256) void atom_sums_kernel(const double* __restrict__ part, int ns, int no, double scale,
+                                                        double* __restrict__ out) {
+  __shared__ double red[256];
+  const int J = blockIdx.x;
+  for (int d = 0; d < no; ++d) {
     double s = 0.0;
-    for (int v = 0; v < a.ns; ++v) {
-      const int64_t e = (int64_t)v * a.np_tot + q;
-      s += a.occ[v] * a.alpha[e] * a.beta[e];
+    for (int v = threadIdx.x; v < ns; v += 256) s += part[((int64_t)J * ns + v) * no + d];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int off = 128; off > 0; off >>= 1) {
+      if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
+      __syncthreads();
     }
-    acc += gam * s;
-  }
-  a.forces[(int64_t)J * 3 + a.dir] = -2.0 * acc;
-}
-
-// FD gradient of orbital column `col` at point i along `dir` (the same stencil as grad_kernel).
-template <typename TV>
-__device__ __forceinline__ double fd_grad(const StressArgs<TV>& a, const TV* col, int64_t i, int x, int y, int z,
-                                          int dir) {
-  const int c = dir == 0 ? x : (dir == 1 ? y : z);
-  const int n = dir == 0 ? a.nx : (dir == 1 ? a.ny : a.nz);
-  const int64_t stride = dir == 0 ? 1 : (dir == 1 ? (int64_t)a.nx : (int64_t)a.nx * a.ny);
-  const int64_t base = i - (int64_t)c * stride;
-  double g = 0.0;
-  for (int p = 1; p <= a.r; ++p) {
-    int cp = c + p, cm = c - p;
-    double fp, fm;
-    if (a.periodic[dir]) {
-      cp %= n;
-      cm = ((cm % n) + n) % n;
-      fp = double(col[base + cp * stride]);
-      fm = double(col[base + cm * stride]);
-    } else {
-      fp = cp < n ? double(col[base + cp * stride]) : 0.0;
-      fm = cm >= 0 ? double(col[base + cm * stride]) : 0.0;
-    }
-    g += a.c[p] * (fp - fm);
-  }
-  return g * a.inv_h[dir];
-}
-
-// Six sums sum_v occ[v] sum_i g_a g_b (ab = xx, yy, zz, xy, xz, yz) over a fixed grid-stride
-// walk of (orbital, point); per-block partials, reduced by stress_sum_kernel.
-template <typename TV>
-__global__ __launch_bounds__(256) void stress_partial_kernel(StressArgs<TV> a) {
-  __shared__ double red[6][256];
-  double acc[6] = {0, 0, 0, 0, 0, 0};
-  const int64_t total = a.nd * a.ns;
-  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-    const int64_t v = e / a.nd, i = e % a.nd;
-    const int x = (int)(i % a.nx), y = (int)((i / a.nx) % a.ny), z = (int)(i / ((int64_t)a.nx * a.ny));
-    const TV* col = a.x + v * a.nd;
-    const double gx = fd_grad(a, col, i, x, y, z, 0);
-    const double gy = fd_grad(a, col, i, x, y, z, 1);
-    const double gz = fd_grad(a, col, i, x, y, z, 2);
-    const double w = a.occ[v];
-    acc[0] += w * gx * gx;
-    acc[1] += w * gy * gy;
-    acc[2] += w * gz * gz;
-    acc[3] += w * gx * gy;
-    acc[4] += w * gx * gz;
-    acc[5] += w * gy * gz;
-  }
-  for (int k = 0; k < 6; ++k) red[k][threadIdx.x] = acc[k];
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (threadIdx.x < off)
-      for (int k = 0; k < 6; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + off];
+    if (threadIdx.x == 0) out[(int64_t)J * no + d] = scale * red[0];
     __syncthreads();
   }
-  if (threadIdx.x < 6) a.partial[(int64_t)blockIdx.x * 6 + threadIdx.x] = red[threadIdx.x][0];
 }
 
-__global__ __launch_bounds__(64) void stress_sum_kernel(const double* __restrict__ partial, int nblocks,
-                                                        double* __restrict__ out) {
-  if (threadIdx.x >= 6) return;
-  double s = 0.0;
-  for (int b = 0; b < nblocks; ++b) s += partial[(int64_t)b * 6 + threadIdx.x];
-  out[threadIdx.x] = s;
-}
-
-// out[b * nchi + e] = chi[e] * disp[3 s + b], b = 0, 1, 2, for every projector value e of
-// atom J (block J) at its support point s: the projectors weighted by the components of the
-// displacement of the point from the atom, for the nonlocal stress's strain derivative.
-__global__ __launch_bounds__(256) void chi_disp_kernel(ChiDispArgs a) {
-  const int J = blockIdx.x;
-  const int s0 = a.supp_off[J], nj = a.supp_off[J + 1] - s0;
-  const int64_t c0 = a.chi_off[J];
-  const int nv = nj * a.nproj[J];
-  for (int e = threadIdx.x; e < nv; e += 256) {
-    const int s = e % nj;
-    const double v = a.chi[c0 + e];
-#pragma unroll
-    for (int b = 0; b < 3; ++b) a.out[(int64_t)b * a.nchi + c0 + e] = v * a.disp[3 * (int64_t)(s0 + s) + b];
+// Kinetic stress: sum_v occ[v] sum_i g_a g_b (ab = xx, yy, zz, xy, xz, yz).  A unit is one
+// orbital x a tile of whole x rows x a z chunk, marched as in the filter's stencil pass (z
+// neighbours in a register queue, the plane and its halo in double-buffered LDS, one
+// barrier per plane, the next plane's values one iteration ahead); block b takes units b,
+// b + grid, ... and writes its six sums.  Reads the block once: bound by LDS reads and
+// memory latency like the stencil pass.  72^3, 600 orbitals FP64 measured 1.16 ms; one
+// thread per point with every neighbour through the caches took 9.7 ms.
+template <typename TV, int R, int PY, int KH>
+__global__ __launch_bounds__(hx_max_threads(PY)) void kinetic_stress_kernel(StressArgs<TV> a) {
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  constexpr int Q = 2 * R + 1;
+  const int nx = a.nx, ny = a.ny, nz = a.nz, nplane = nx * ny;
+  const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
+  const int pitch = a.pitch;
+  const int tile_elems = (a.ty + 2 * R) * pitch;
+  const int tile_buf = tile_elems + kHxDummy;
+  TV* s_tile = reinterpret_cast<TV*>(lds_raw);
+  const bool active = tid < nx * a.nyg;
+  const int x = active ? tid % nx : 0;
+  const int ly0 = active ? (tid / nx) * PY : 0;
+  const int nbytes = (int)(a.nd * (int64_t)sizeof(TV));
+  const unsigned plane_bytes = (unsigned)nplane * (unsigned)sizeof(TV);
+  if (!a.periodic[0]) {  // Dirichlet x: the halo columns of both tile buffers hold zeros
+    const int nrows = 2 * (a.ty + 2 * R);
+    for (int i = tid; i < nrows * 2 * R; i += nthr) {
+      const int row = i / (2 * R), c = i % (2 * R);
+      const int buf = row / (a.ty + 2 * R), rr = row % (a.ty + 2 * R);
+      s_tile[buf * tile_buf + rr * pitch + (c < R ? c : nx + c)] = TV(0);
+    }
   }
+  double tot[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  const int per_vec = a.nty * a.nzc;
+  for (int64_t unit = blockIdx.x; unit < a.nunits; unit += gridDim.x) {
+    const int vec = (int)(unit / per_vec), rem = (int)(unit % per_vec);
+    const int y0 = (rem % a.nty) * a.ty, z0 = (rem / a.nty) * a.zc;
+    const int nzl = min(a.zc, nz - z0);
+    const TV* xv = a.x + (int64_t)vec * a.nd;
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(xv, nbytes);
+    const __amdgpu_buffer_rsrc_t rz = make_rsrc(xv, 0);
+    unsigned vq[PY];
+    int sown[PY];
+    bool valid[PY];
+#pragma unroll
+    for (int j = 0; j < PY; ++j) {
+      const int gy = y0 + ly0 + j;
+      vq[j] = lane_off<TV>(active ? row_offset(x, gy, nx, ny, a.periodic[1]) : -1);
+      valid[j] = active && gy < ny;
+      sown[j] = active ? (R + ly0 + j) * pitch + R + x : tile_elems + lane;
+    }
+    int sdst[KH];
+    unsigned vh[KH];
+    const int nslots = hx_halo_slots(nx, a.ty, R, a.periodic[0]);
+#pragma unroll
+    for (int k = 0; k < KH; ++k) {
+      const int e = tid + k * nthr;
+      int dst = tile_elems + lane, src = -1;
+      if (e < nslots) halo_slot(e, nx, ny, a.ty, y0, R, pitch, a.periodic[0], a.periodic[1], dst, src);
+      sdst[k] = dst;
+      vh[k] = lane_off<TV>(src);
+    }
+    TV q[Q][PY], pf[PY], hp[KH];
+#pragma unroll
+    for (int j = 0; j < PY; ++j) q[0][j] = TV(0);
+#pragma unroll
+    for (int s = 1; s < Q; ++s) {
+      const int po = plane_offset(z0 - R - 1 + s, nplane, nz, a.periodic[2]);
+#pragma unroll
+      for (int j = 0; j < PY; ++j) q[s][j] = pload<TV>(xv, nbytes, vq[j], po);
+    }
+    {
+      const int po = plane_offset(z0 + R, nplane, nz, a.periodic[2]);
+#pragma unroll
+      for (int j = 0; j < PY; ++j) pf[j] = pload<TV>(xv, nbytes, vq[j], po);
+      const int ph = plane_offset(z0, nplane, nz, a.periodic[2]);
+#pragma unroll
+      for (int k = 0; k < KH; ++k) hp[k] = pload<TV>(xv, nbytes, vh[k], ph);
+    }
+    int pb = z0 + R + 1, ph = z0 + 1;
+    if (a.periodic[2]) {
+      pb %= nz;
+      ph %= nz;
+    }
+    double sum[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    // the previous unit's last plane may still be read by slower waves
+    __syncthreads();
+    for (int zl = 0; zl < nzl; ++zl) {
+      TV* tl = s_tile + (zl & 1) * tile_buf;
+      const bool more = zl + 1 < nzl;
+#pragma unroll
+      for (int s = 0; s < Q - 1; ++s)
+#pragma unroll
+        for (int j = 0; j < PY; ++j) q[s][j] = q[s + 1][j];
+#pragma unroll
+      for (int j = 0; j < PY; ++j) q[Q - 1][j] = pf[j];
+      {
+        const bool ok = more && pb < nz;
+        const __amdgpu_buffer_rsrc_t r = ok ? rx : rz;
+        const unsigned so = ok ? (unsigned)pb * plane_bytes : 0u;
+#pragma unroll
+        for (int j = 0; j < PY; ++j) pf[j] = bload<TV>(r, vq[j], so);
+      }
+#pragma unroll
+      for (int j = 0; j < PY; ++j) tl[sown[j]] = q[R][j];
+#pragma unroll
+      for (int k = 0; k < KH; ++k) tl[sdst[k]] = hp[k];
+      {
+        const bool ok = more && ph < nz;
+        const __amdgpu_buffer_rsrc_t r = ok ? rx : rz;
+        const unsigned so = ok ? (unsigned)ph * plane_bytes : 0u;
+#pragma unroll
+        for (int k = 0; k < KH; ++k) hp[k] = bload<TV>(r, vh[k], so);
+      }
+      ++pb;
+      ++ph;
+      if (a.periodic[2]) {
+        pb = pb == nz ? 0 : pb;
+        ph = ph == nz ? 0 : ph;
+      }
+      __syncthreads();
+      double gx[PY], gy[PY], gz[PY];
+#pragma unroll
+      for (int j = 0; j < PY; ++j) {
+        gx[j] = gy[j] = gz[j] = 0.0;
+#pragma unroll
+        for (int p = 1; p <= R; ++p) gz[j] += a.c[2][p] * (double(q[R + p][j]) - double(q[R - p][j]));
+      }
+#pragma unroll
+      for (int t = 0; t < PY + 2 * R; ++t) {  // each LDS row of the column feeds every row it neighbours
+        const double v = double(tl[(ly0 + t) * pitch + R + x]);
+#pragma unroll
+        for (int j = 0; j < PY; ++j) {
+          const int p = t - R - j;
+          if (p > 0 && p <= R) gy[j] += a.c[1][p] * v;
+          if (p < 0 && p >= -R) gy[j] -= a.c[1][-p] * v;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < PY; ++j) {
+        const TV* row = tl + (R + ly0 + j) * pitch + R + x;
+#pragma unroll
+        for (int p = 1; p <= R; ++p) gx[j] += a.c[0][p] * (double(row[p]) - double(row[-p]));
+        if (!valid[j]) gx[j] = gy[j] = gz[j] = 0.0;  // idle lanes and rows past ny
+        sum[0] += gx[j] * gx[j];
+        sum[1] += gy[j] * gy[j];
+        sum[2] += gz[j] * gz[j];
+        sum[3] += gx[j] * gy[j];
+        sum[4] += gx[j] * gz[j];
+        sum[5] += gy[j] * gz[j];
+      }
+    }
+    const double w = a.occ[vec];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) tot[k] += w * sum[k];
+  }
+  __syncthreads();
+  double* red = reinterpret_cast<double*>(lds_raw);  // [waves][6]; the tile is larger
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    double v = tot[k];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    if (lane == 0) red[(tid >> 6) * 6 + k] = v;
+  }
+  __syncthreads();
+  if (tid < 6) {
+    double s = 0.0;
+    for (int wv = 0; wv < nthr / 64; ++wv) s += red[wv * 6 + tid];
+    a.partial[(int64_t)blockIdx.x * 6 + tid] = s;
+  }
+}
+
+// out[k] = sum over nblocks of partial[b * 6 + k], one block per k (fixed order).
+__global__ __launch_bounds__(256) void stress_sum_kernel(const double* __restrict__ partial, int nblocks,
+                                                         double* __restrict__ out) {
+  __shared__ double red[256];
+  double s = 0.0;
+  for (int b = threadIdx.x; b < nblocks; b += 256) s += partial[(int64_t)b * 6 + blockIdx.x];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int off = 128; off > 0; off >>= 1) {
+    if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) out[blockIdx.x] = red[0];
+}
+
+template <typename TV, int R, int PY>
+hipError_t launch_stress_kh(const StressArgs<TV>& a, int kh, int grid, int threads, size_t lds, hipStream_t s) {
+  switch (kh) {
+    case 2: hipLaunchKernelGGL((kinetic_stress_kernel<TV, R, PY, 2>), dim3(grid), dim3(threads), lds, s, a); break;
+    case 3: hipLaunchKernelGGL((kinetic_stress_kernel<TV, R, PY, 3>), dim3(grid), dim3(threads), lds, s, a); break;
+    case 4: hipLaunchKernelGGL((kinetic_stress_kernel<TV, R, PY, 4>), dim3(grid), dim3(threads), lds, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <typename TV, int R>
+hipError_t launch_stress_r(const StressArgs<TV>& a, const HxPlan& p, int grid, size_t lds, hipStream_t s) {
+  if (p.py == 1) return launch_stress_kh<TV, R, 1>(a, p.kh, grid, p.threads, lds, s);
+  if (p.py == 2) return launch_stress_kh<TV, R, 2>(a, p.kh, grid, p.threads, lds, s);
+  return hipErrorInvalidValue;
+}
+
+template <typename TV, int R>
+hipError_t launch_ng(const NlGradArgs<TV>& a, hipStream_t s) {
+  const dim3 grid((unsigned)(a.per_xcd * 8)), block(64 * kNgWaves);
+  if (a.disp != nullptr)
+    hipLaunchKernelGGL((nl_grad_kernel<TV, R, true>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((nl_grad_kernel<TV, R, false>), grid, block, 0, s, a);
+  return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_chi_disp(const ChiDispArgs& a, hipStream_t s) {
-  if (a.n_atoms <= 0) return hipSuccess;
-  hipLaunchKernelGGL(chi_disp_kernel, dim3((unsigned)a.n_atoms), dim3(256), 0, s, a);
+template <typename TV>
+hipError_t launch_nl_grad(const NlGradArgs<TV>& a0, int radius, double* out, double scale, hipStream_t s) {
+  if (a0.n_atoms <= 0 || a0.ns <= 0) return hipSuccess;
+  NlGradArgs<TV> a = a0;
+  const int per_block = kNgWaves * (a.disp != nullptr ? 1 : 2);
+  const int no = a.disp != nullptr ? 10 : 3;
+  a.ngroups = (a.ns + per_block - 1) / per_block;
+  a.per_xcd = (int)(((int64_t)a.n_atoms * a.ngroups + 7) / 8);
+  hipError_t e;
+  switch (radius) {
+    case 1: e = launch_ng<TV, 1>(a, s); break;
+    case 2: e = launch_ng<TV, 2>(a, s); break;
+    case 3: e = launch_ng<TV, 3>(a, s); break;
+    case 4: e = launch_ng<TV, 4>(a, s); break;
+    case 5: e = launch_ng<TV, 5>(a, s); break;
+    case 6: e = launch_ng<TV, 6>(a, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(atom_sums_kernel, dim3((unsigned)a.n_atoms), dim3(256), 0, s, a.part, a.ns, no, scale, out);
   return hipGetLastError();
 }
 
 template <typename TV>
-hipError_t launch_stress_sums(const StressArgs<TV>& a, hipStream_t s) {
-  hipLaunchKernelGGL((stress_partial_kernel<TV>), dim3(kVecBlocks), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(stress_sum_kernel, dim3(1), dim3(64), 0, s, a.partial, kVecBlocks, a.out);
+hipError_t launch_stress_sums(const StressArgs<TV>& a0, int radius, int64_t max_partials, hipStream_t s) {
+  StressArgs<TV> a = a0;
+  // FP64 queue values at two rows per thread and more cost occupancy here as in the filter:
+  // the planner's default tiling (one or two rows) serves
+  const HxPlan p = plan_hx(a.nx, a.ny, a.nz, a.ns, radius, (int)sizeof(TV), 0, 0);
+  if (!p.ok) return hipErrorInvalidConfiguration;
+  a.nyg = p.nyg;
+  a.ty = p.ty;
+  a.nty = p.nty;
+  a.zc = p.zc;
+  a.nzc = p.nzc;
+  a.nunits = (int64_t)p.nty * p.nzc * a.ns;
+  a.pitch = hx_pitch(a.nx, radius, (int)sizeof(TV), p.py);
+  const int grid = (int)std::min<int64_t>({a.nunits, std::max<int64_t>(1, max_partials), 65535});
+  const size_t lds = std::max<size_t>(hx_lds_bytes(p, a.nx, radius, (int)sizeof(TV), -1, 8), 16 * 6 * sizeof(double));
+  hipError_t e;
+  switch (radius) {
+    case 1: e = launch_stress_r<TV, 1>(a, p, grid, lds, s); break;
+    case 2: e = launch_stress_r<TV, 2>(a, p, grid, lds, s); break;
+    case 3: e = launch_stress_r<TV, 3>(a, p, grid, lds, s); break;
+    case 4: e = launch_stress_r<TV, 4>(a, p, grid, lds, s); break;
+    case 5: e = launch_stress_r<TV, 5>(a, p, grid, lds, s); break;
+    case 6: e = launch_stress_r<TV, 6>(a, p, grid, lds, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(stress_sum_kernel, dim3(6), dim3(256), 0, s, a.partial, grid, a.out);
   return hipGetLastError();
 }
 
-template hipError_t launch_stress_sums<double>(const StressArgs<double>&, hipStream_t);
-template hipError_t launch_stress_sums<float>(const StressArgs<float>&, hipStream_t);
-
-template <typename TV>
-hipError_t launch_grad(const GradArgs<TV>& a, int ns, hipStream_t s) {
-  if (ns <= 0 || a.nd <= 0) return hipSuccess;
-  hipLaunchKernelGGL((grad_kernel<TV>), dim3((unsigned)((a.nd + 255) / 256), (unsigned)ns), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_forces(const ForceArgs& a, hipStream_t s) {
-  if (a.n_atoms <= 0) return hipSuccess;
-  hipLaunchKernelGGL(force_kernel, dim3((unsigned)((a.n_atoms + 255) / 256)), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-template hipError_t launch_grad<double>(const GradArgs<double>&, int, hipStream_t);
-template hipError_t launch_grad<float>(const GradArgs<float>&, int, hipStream_t);
+template hipError_t launch_stress_sums<double>(const StressArgs<double>&, int, int64_t, hipStream_t);
+template hipError_t launch_stress_sums<float>(const StressArgs<float>&, int, int64_t, hipStream_t);
+template hipError_t launch_nl_grad<double>(const NlGradArgs<double>&, int, double*, double, hipStream_t);
+template hipError_t launch_nl_grad<float>(const NlGradArgs<float>&, int, double*, double, hipStream_t);
 
 }  // namespace chefsi

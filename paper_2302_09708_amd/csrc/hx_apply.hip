@@ -34,55 +34,11 @@
 //     prefetch;
 //   * global reads are buffer loads: a Dirichlet ghost is an out-of-range offset,
 //     which returns zero without touching memory, so the loads need no branches.
-#include "common.h"
-
 #include <algorithm>
 
+#include "stencil.h"
+
 namespace chefsi {
-
-constexpr unsigned kOOB = 0x80000000u;  // any buffer offset at or past the end reads as zero
-
-__device__ __forceinline__ int wrap_index(int v, int n) {
-  v %= n;
-  return v < 0 ? v + n : v;
-}
-
-// Offset of row gy inside a plane (x added), or -1 for a Dirichlet zero row.
-__device__ __forceinline__ int row_offset(int x, int gy, int nx, int ny, int per_y) {
-  if (per_y) return x + nx * wrap_index(gy, ny);
-  return (gy < 0 || gy >= ny) ? -1 : x + nx * gy;
-}
-
-// Offset of plane pz, or -1 for a Dirichlet zero plane.
-__device__ __forceinline__ int plane_offset(int pz, int nplane, int nz, int per_z) {
-  if (per_z) return nplane * wrap_index(pz, nz);
-  return (pz < 0 || pz >= nz) ? -1 : nplane * pz;
-}
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, int64_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-
-// Buffer loads take a per-lane byte offset (voff) and a wave-uniform one (soff, a scalar
-// register): the per-thread part of an address is computed once, the per-plane part on
-// the scalar unit, so a load costs no vector instructions.  A lane whose voff is kOOB
-// reads zero (kOOB + soff stays at or past the end because every buffer is below 2^31
-// bytes and so is soff).
-template <typename T>
-__device__ __forceinline__ unsigned lane_off(int a) {
-  return a < 0 ? kOOB : (unsigned)a * (unsigned)sizeof(T);
-}
-
-template <typename T>
-__device__ __forceinline__ T bload(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff);
-template <>
-__device__ __forceinline__ double bload<double>(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
-}
-template <>
-__device__ __forceinline__ float bload<float>(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
-}
 
 // The previous iterate and the output are each touched once per pass: in FP64 they are
 // loaded and stored non-temporally (nt), which leaves more of the L2 to the halo rows and
@@ -114,26 +70,6 @@ __device__ __forceinline__ void bstore_stream<float>(__amdgpu_buffer_rsrc_t r, f
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, kStreamPolicy<float>);
 }
 
-template <typename T>
-__device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, T v, unsigned voff, unsigned soff);
-template <>
-__device__ __forceinline__ void bstore<double>(__amdgpu_buffer_rsrc_t r, double v, unsigned voff, unsigned soff) {
-  typedef unsigned u32x2 __attribute__((__vector_size__(8)));
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, 0);
-}
-template <>
-__device__ __forceinline__ void bstore<float>(__amdgpu_buffer_rsrc_t r, float v, unsigned voff, unsigned soff) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, 0);
-}
-
-// element at lane offset voff of plane po (element offset, uniform) of the nbytes-long
-// array at p; po = -1 (a zero plane) selects a resource with no records: reads give zero
-template <typename T>
-__device__ __forceinline__ T pload(const T* p, int nbytes, unsigned voff, int po) {
-  const __amdgpu_buffer_rsrc_t r = make_rsrc(p, po < 0 ? 0 : nbytes);
-  return bload<T>(r, voff, po < 0 ? 0u : (unsigned)po * (unsigned)sizeof(T));
-}
-
 // one projector record (zeros when voff is kOOB): 32 bytes for FP32 values, 48 for FP64
 template <typename TC>
 __device__ __forceinline__ void load_rec(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, int (&hdr)[3],
@@ -160,38 +96,6 @@ __device__ __forceinline__ void load_rec(__amdgpu_buffer_rsrc_t r, unsigned voff
     v[2] = __builtin_bit_cast(double, (unsigned long long)u[0] | ((unsigned long long)u[1] << 32));
     v[3] = __builtin_bit_cast(double, (unsigned long long)u[2] | ((unsigned long long)u[3] << 32));
   }
-}
-
-// Number of LDS slots a block stages per plane besides its own body elements: the r halo
-// rows above and below the tile (nx + 2r columns when x is periodic, the nx interior
-// columns when it is not) and, when x is periodic, the r wrapped copies on each side of
-// every body row.  (Dirichlet x halo columns are zeros written once.)
-__host__ __device__ inline int hx_halo_slots(int nx, int ty, int radius, int per_x) {
-  return 2 * radius * (per_x ? nx + 2 * radius : nx) + (per_x ? ty * 2 * radius : 0);
-}
-
-// Slot e of a plane's staged set: LDS destination (row-major with the given pitch, element
-// x of a row at column r + x) and source row offset inside the plane (x added; -1 for a
-// zero value).
-__device__ __forceinline__ void halo_slot(int e, int nx, int ny, int ty, int y0, int radius, int pitch, int per_x,
-                                          int per_y, int& dst, int& src) {
-  const int w = per_x ? nx + 2 * radius : nx;
-  int yy, c;
-  if (e < 2 * radius * w) {  // halo rows: local rows [0, r) and [r + ty, ty + 2r)
-    const int hr = e / w;
-    c = e % w + (per_x ? 0 : radius);
-    yy = hr < radius ? hr : hr + ty;
-  } else {  // periodic x copies of the body rows: columns [0, r) and [r + nx, nx + 2r)
-    const int f = e - 2 * radius * w;
-    const int cc = f % (2 * radius);
-    c = cc < radius ? cc : nx + cc;
-    yy = radius + f / (2 * radius);
-  }
-  int gx = c - radius;
-  if (gx < 0) gx += nx;  // only reached with periodic x (nx >= r: one wrap)
-  if (gx >= nx) gx -= nx;
-  dst = yy * pitch + c;
-  src = row_offset(gx, y0 - radius + yy, nx, ny, per_y);
 }
 
 // one row per thread fits 128 VGPRs, so its blocks may hold 1024 threads (taller tiles,
