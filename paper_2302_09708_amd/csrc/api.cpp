@@ -288,6 +288,7 @@ struct WsLayout {
   GramPlan gram;
   BlasGram bgram;   // FP64 handles: Gram products of FP64 blocks
   PanelPlan pan;    // mixed handles: FP64 products of the FP32 block
+  PairPlan pair;    // mixed handles: both split-bf16 Gram products at once
 };
 
 // status words in the pinned staging buffer, after max_ns doubles
@@ -380,8 +381,10 @@ WsLayout layout(chefsi_handle* h, int ns) {
   L.bgram = plan_blas_gram(h->nd, ns);
   L.pan = plan_panels(h->nd, ns);
   L.partial = off;
-  off += align256(std::max(L.gram.partial_bytes,
-                           h->precision == CHEFSI_FP64 ? L.bgram.bytes : 2 * L.pan.part_bytes));
+  const size_t part_bytes =
+      std::max(L.gram.partial_bytes, h->precision == CHEFSI_FP64 ? L.bgram.bytes : 2 * L.pan.part_bytes);
+  if (h->precision == CHEFSI_MIXED) L.pair = plan_gram_pair(h->nd, ns, L.gram, part_bytes);
+  off += align256(part_bytes);
   L.zsplit = off;
   if (h->precision == CHEFSI_MIXED) off += align256(zsplit_bytes(ns));
   L.panel = off;
@@ -797,6 +800,14 @@ void panel_rotate(chefsi_handle* h, const float* X, const double* Z, float* O, i
   ps.done();
 }
 
+// The 256 x (128 + 128) units of the split-bf16 products run one block per CU; where they
+// leave more of the chip idle, or form more lower-triangle waste, than this allows, the
+// 128 x 128 tiles (two blocks per CU) are faster.  Both products measured, tiles / units, by
+// that share: 0.85 (60x60x180, Ns 1200) 11.95 / 6.83 ms; 0.68 (60^3, Ns 900) 2.30 / 1.73;
+// 0.67 (72^3, Ns 600) 1.94 / 1.62, (64^3, Ns 520) 1.27 / 1.22; 0.67 (60^3, Ns 400) 0.66 / 0.71;
+// 0.41 (60^3, Ns 257) 0.59 / 0.68; 0.09 (45^3, Ns 187) 0.21 / 0.58.
+constexpr double kPairMinFill = 0.668;
+
 // Hs = X^T Y, Ms = X^T X (full symmetric, FP64), via split-K partial tiles.
 template <typename TX, typename TY>
 void gram_pair(chefsi_handle* h, const TX* X, const TY* Y, int ns, const WsLayout& L, void* ws, double* Hs,
@@ -809,6 +820,14 @@ void gram_pair(chefsi_handle* h, const TX* X, const TY* Y, int ns, const WsLayou
     }
   }
   double* part = at<double>(ws, L.partial);
+  if constexpr (std::is_same<TX, float>::value && std::is_same<TY, float>::value) {
+    if (g == Gemm::BF16X3 && L.pair.fill >= kPairMinFill) {
+      ProfScope ps(h, P_GRAM, s);
+      HIP_TRY(launch_gram_pair_bf16x3(X, Y, h->nd, ns, L.pair, part, Hs, Ms, s));
+      ps.done();
+      return;
+    }
+  }
   {
     ProfScope ps(h, P_GRAM, s);
     HIP_TRY((gram_launch<TX, TY>(g, X, Y, h->nd, ns, L.gram, part, s)));

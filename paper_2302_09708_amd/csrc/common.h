@@ -249,6 +249,18 @@ hipError_t launch_rotate_f64(const TX* X, const double* Z, TO* O, int64_t nd, in
 // rotate: Z (FP64) is first split into the zsplit scratch (zsplit_bytes(ns) bytes).
 hipError_t launch_gram_bf16x3(const float* A, const float* B, int64_t nd, int ns, const GramPlan& p,
                               double* partial, hipStream_t s);
+// gram_pair: both products X^T X and X^T Y over units of 256 x (128 + 128) results and groups
+// of rows, with the FP32 sums of launch_gram_bf16x3 under the plan gp.
+struct PairPlan {
+  int nj = 0;       // column blocks of 128
+  int nunits = 0;
+  int groups = 0;   // groups of rows (0: the partial results do not fit)
+  int64_t kchunk = 0;
+  double fill = 0;  // share of the CUs' time spent on tiles that the 128-wide kernel forms too
+};
+PairPlan plan_gram_pair(int64_t nd, int ns, const GramPlan& gp, size_t partial_bytes);
+hipError_t launch_gram_pair_bf16x3(const float* X, const float* Y, int64_t nd, int ns, const PairPlan& p,
+                                   double* partial, double* Hs, double* Ms, hipStream_t s);
 size_t zsplit_bytes(int ns);
 hipError_t launch_rotate_bf16x3(const float* X, const double* Z, void* zsplit, float* O, int64_t nd, int ns,
                                 hipStream_t s);

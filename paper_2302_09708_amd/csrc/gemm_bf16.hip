@@ -30,6 +30,9 @@
 namespace chefsi {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // rows of odd length are only 4-byte aligned
@@ -244,6 +247,277 @@ hipError_t launch_gram_bf16x3(const float* A, const float* B, int64_t nd, int ns
   if (p.tile != kT) return hipErrorInvalidValue;
   dim3 grid((unsigned)(p.ntiles * p.splits));
   hipLaunchKernelGGL(gram_bf16x3_kernel, grid, dim3(256), 0, s, A, B, nd, ns, p.nt, p.ntiles, p.kchunk, partial);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Both products of the projection at once: a unit is 256 rows of X (block I) against 128
+// columns of X and the same 128 columns of Y (block J >= 2 I), i.e. 256 x 128 elements of Ms
+// and of Hs.
+//
+// The 128 x 128 kernel above is bound by its operand stream, not by MFMA: at 120^3, Ns 1800
+// its two products read 424 GB through L2 with 80 % misses (3.9 TB/s of them) while MFMA was
+// busy 24 % of the cycles.  The unit stages 512 rows for 256 x 256 results where four of the
+// 128-wide tiles stage 1024, and splits each staged value half as often.
+//
+// One block per CU (512 threads, 128 KB of LDS, 256 registers a lane).  Wave (wm, wn) holds
+// 64 rows x 128 columns, wn = 0 the columns of X, wn = 1 those of Y.  A 32-wide K stage lies
+// in LDS as 64-byte rows of hi and of lo; 16-byte chunk c of row r sits at chunk
+// c ^ (r / 4) % 4, so the eight rows that a read covers at a time fall on distinct banks.
+// Measured, both products with their sums: 120^3, Ns 1800: 77.3 -> 36.7 ms (1185 TF/s executed
+// bf16, MFMA busy 68 % of the cycles at the 1.65 GHz the power limit leaves, L2 hits 67 %);
+// 60x60x180, Ns 1200: 11.95 -> 6.83 ms; 72^3, Ns 600: 1.94 -> 1.62 ms.
+// During stage t a thread splits its eight row pieces of stage t + 1 into the other buffer,
+// six MFMAs apart, and refetches each piece for stage t + 2 as soon as it is split: every
+// global load has a whole stage to arrive and the splits run under the MFMAs.
+// ---------------------------------------------------------------------------
+namespace {
+constexpr int kPI = 256, kPJ = 128;
+constexpr int kPairThreads = 512;
+constexpr int kPairRows = kPI + 2 * kPJ;  // staged rows: X(:, I), X(:, J), Y(:, J)
+constexpr int kPairPasses = 8;            // row pieces a thread stages: rows 64 q + tid / 8
+constexpr int kPairSub = kSubStages * kKS;  // rows summed in FP32 before an FP64 flush
+
+__device__ __forceinline__ void pair_unit_of(int u, int nj, int& bi, int& bj) {
+  bi = 0;
+  int row = nj;
+  while (u >= row) {
+    u -= row;
+    ++bi;
+    row -= 2;
+  }
+  bj = 2 * bi + u;
+}
+
+__device__ __forceinline__ void pair_flush(f32x16 (&acc)[2][4], double* __restrict__ pt, int wm, int wn, int g, int r32,
+                                           bool add) {
+  int64_t zero = 0;  // keeps the 128 addresses from being formed ahead of the K loop
+  asm volatile("" : "+s"(zero));
+  pt += zero;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int ii = wm * 64 + i * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
+        const int jj = wn * kPJ + j * 32 + r32;
+        double* q = pt + ii * (2 * kPJ) + jj;
+        *q = add ? *q + (double)acc[i][j][v] : (double)acc[i][j][v];
+        acc[i][j][v] = 0.f;
+      }
+}
+
+// hi and lo of two values at once (one packed conversion each), as split_bf16
+__device__ __forceinline__ void split2(f32x2 x, bf16x2& hi, bf16x2& lo) {
+  hi = __builtin_convertvector(x, bf16x2);
+  lo = __builtin_convertvector(x - __builtin_convertvector(hi, f32x2), bf16x2);
+}
+
+__device__ __forceinline__ void pair_split_store(const f32x4u& x, __bf16* ph, __bf16* pl) {
+  bf16x2 h0, h1, l0, l1;
+  split2(f32x2{x[0], x[1]}, h0, l0);
+  split2(f32x2{x[2], x[3]}, h1, l1);
+  *reinterpret_cast<bf16x4*>(ph) = __builtin_shufflevector(h0, h1, 0, 1, 2, 3);
+  *reinterpret_cast<bf16x4*>(pl) = __builtin_shufflevector(l0, l1, 0, 1, 2, 3);
+}
+}  // namespace
+
+// First row of group g of `groups`: near g / groups of the rows, at a place where the FP32
+// sums of the 128 x 128 kernel end too (a multiple of kPairSub rows inside a K chunk, or a
+// chunk's end), so both kernels form the same FP32 sums.
+__device__ __forceinline__ int64_t pair_bound(int g, int groups, int64_t nd, int64_t kchunk) {
+  if (g <= 0) return 0;
+  if (g >= groups) return nd;
+  const int64_t r = nd / groups * g, c0 = r / kchunk * kchunk;
+  const int64_t in = (r - c0 + kPairSub / 2) / kPairSub * kPairSub;
+  return min(nd, min(c0 + in, c0 + kchunk));
+}
+
+__global__ __launch_bounds__(kPairThreads, 2) void gram_pair_kernel(const float* __restrict__ X,
+                                                                    const float* __restrict__ Y, int64_t nd, int ns,
+                                                                    int nj, int nunits, int nblocks, int per_xcd,
+                                                                    int groups, int64_t kchunk,
+                                                                    double* __restrict__ partial) {
+  __shared__ __attribute__((aligned(16))) __bf16 lds[2][2][kPairRows * kKS];  // [buffer][hi, lo][row][32]
+  const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (logical >= nblocks) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int wm = wave & 3, wn = wave >> 2;
+  const int unit = logical % nunits, group = logical / nunits;
+  int bi, bj;
+  pair_unit_of(unit, nj, bi, bj);
+
+  const int lr = tid >> 3, lc = tid & 7;
+  const float* col[kPairPasses];
+#pragma unroll
+  for (int q = 0; q < kPairPasses; ++q) {
+    const int row = 64 * q + lr;
+    const int c = q < 4 ? bi * kPI + row : bj * kPJ + (row - kPI) % kPJ;
+    col[q] = (q < 6 ? X : Y) + (int64_t)min(c, ns - 1) * nd + 4 * lc;
+  }
+  const int st_off = lr * kKS + ((((lc >> 1) ^ (lr >> 2)) & 3) << 3) + 4 * (lc & 1);
+
+  f32x16 acc[2][4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+  const int r32 = lane & 31, g = lane >> 5, key = (r32 >> 2) & 3;
+  const int oa = (wm * 64 + r32) * kKS, ob = (kPI + wn * kPJ + r32) * kKS;
+  // partial results, row-major 256 x (128 of Ms, 128 of Hs)
+  double* pt = partial + ((int64_t)group * nunits + unit) * (kPI * 2 * kPJ);
+  const int64_t r1 = pair_bound(group + 1, groups, nd, kchunk);
+  bool flushed = false;
+  f32x4u st[kPairPasses];
+  for (int64_t kb = pair_bound(group, groups, nd, kchunk); kb < r1;) {
+    // one FP32 sum: rows kb .. ke
+    const int64_t c0 = kb / kchunk * kchunk;
+    const int64_t ke = min(min(c0 + kchunk, nd), kb + kPairSub);
+    const int nfull = (int)((ke - kb) / kKS);
+    const float* src[kPairPasses];
+#pragma unroll
+    for (int q = 0; q < kPairPasses; ++q) src[q] = col[q] + kb;
+    if (nfull > 0) {
+#pragma unroll
+      for (int q = 0; q < kPairPasses; ++q) st[q] = *reinterpret_cast<const f32x4u*>(src[q]);
+#pragma unroll
+      for (int q = 0; q < kPairPasses; ++q)
+        pair_split_store(st[q], lds[0][0] + st_off + 64 * q * kKS, lds[0][1] + st_off + 64 * q * kKS);
+      const int64_t k1 = (int64_t)min(1, nfull - 1) * kKS;
+#pragma unroll
+      for (int q = 0; q < kPairPasses; ++q) st[q] = *reinterpret_cast<const f32x4u*>(src[q] + k1);
+    }
+    __syncthreads();
+    for (int t = 0; t < nfull; ++t) {
+      const __bf16* lh = lds[t & 1][0];
+      const __bf16* ll = lds[t & 1][1];
+      __bf16* nh = lds[(t & 1) ^ 1][0];
+      __bf16* nl = lds[(t & 1) ^ 1][1];
+      // past the last full stage the pieces are refetched and staged again, unread
+      const int64_t kn = (int64_t)min(t + 2, nfull - 1) * kKS;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int ch = ((2 * s + g) ^ key) << 3;
+        bf16x8 ah[2], al[2], bh[4], bl[4];
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+          ah[f] = as_bf8(*reinterpret_cast<const u32x4*>(lh + oa + f * 32 * kKS + ch));
+          al[f] = as_bf8(*reinterpret_cast<const u32x4*>(ll + oa + f * 32 * kKS + ch));
+        }
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+          bh[f] = as_bf8(*reinterpret_cast<const u32x4*>(lh + ob + f * 32 * kKS + ch));
+          bl[f] = as_bf8(*reinterpret_cast<const u32x4*>(ll + ob + f * 32 * kKS + ch));
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {  // MFMAs 6 c .. 6 c + 5 of the 24, then one staged piece
+#pragma unroll
+          for (int m = 6 * c; m < 6 * c + 6; ++m) {
+            const int p = m / 8, i = (m % 8) / 4, j = m % 4;
+            acc[i][j] = p == 0 ? mfma_bf16(al[i], bh[j], acc[i][j])
+                               : (p == 1 ? mfma_bf16(ah[i], bl[j], acc[i][j]) : mfma_bf16(ah[i], bh[j], acc[i][j]));
+          }
+          const int q = 4 * s + c;
+          pair_split_store(st[q], nh + st_off + 64 * q * kKS, nl + st_off + 64 * q * kKS);
+          st[q] = *reinterpret_cast<const f32x4u*>(src[q] + kn);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      __syncthreads();
+    }
+    if (kb + (int64_t)nfull * kKS < ke) {  // rows past the last full stage (zeros beyond ke)
+      const int64_t k0 = (int64_t)nfull * kKS;
+#pragma unroll
+      for (int q = 0; q < kPairPasses; ++q) {
+        f32x4u x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = kb + k0 + 4 * lc + e < ke ? src[q][k0 + e] : 0.f;
+        pair_split_store(x, lds[0][0] + st_off + 64 * q * kKS, lds[0][1] + st_off + 64 * q * kKS);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int ch = ((2 * s + g) ^ key) << 3;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const bf16x8 ah = as_bf8(*reinterpret_cast<const u32x4*>(lds[0][0] + oa + i * 32 * kKS + ch));
+          const bf16x8 al = as_bf8(*reinterpret_cast<const u32x4*>(lds[0][1] + oa + i * 32 * kKS + ch));
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const bf16x8 bh = as_bf8(*reinterpret_cast<const u32x4*>(lds[0][0] + ob + j * 32 * kKS + ch));
+            const bf16x8 bl = as_bf8(*reinterpret_cast<const u32x4*>(lds[0][1] + ob + j * 32 * kKS + ch));
+            acc[i][j] = mfma_bf16(al, bh, acc[i][j]);
+            acc[i][j] = mfma_bf16(ah, bl, acc[i][j]);
+            acc[i][j] = mfma_bf16(ah, bh, acc[i][j]);
+          }
+        }
+      }
+      __syncthreads();  // the next sum stages into the same buffer
+    }
+    pair_flush(acc, pt, wm, wn, g, r32, flushed);
+    flushed = true;
+    kb = ke;
+  }
+  if (!flushed) pair_flush(acc, pt, wm, wn, g, r32, false);  // a group without rows: zeros
+}
+
+// Hs(i, j) = Hs(j, i) and Ms(i, j) = Ms(j, i): the units' partial results of element (i, j),
+// i <= j, summed over the K chunks in a fixed order.
+__global__ __launch_bounds__(256) void gram_pair_reduce_kernel(const double* __restrict__ partial, int ns, int nj,
+                                                               int nunits, int splits, double* __restrict__ Hs,
+                                                               double* __restrict__ Ms) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  int bi, bj;
+  pair_unit_of(blockIdx.y, nj, bi, bj);
+  const int i = bi * kPI + e / (2 * kPJ), jj = e % (2 * kPJ), j = bj * kPJ + jj % kPJ;
+  if (i > j || j >= ns) return;
+  double s = 0.0;
+  for (int q = 0; q < splits; ++q) s += partial[((int64_t)q * nunits + blockIdx.y) * (kPI * 2 * kPJ) + e];
+  double* C = jj < kPJ ? Ms : Hs;
+  C[(int64_t)j * ns + i] = s;
+  C[(int64_t)i * ns + j] = s;
+}
+
+PairPlan plan_gram_pair(int64_t nd, int ns, const GramPlan& gp, size_t bytes) {
+  PairPlan p;
+  p.nj = (ns + kPJ - 1) / kPJ;
+  p.nunits = 0;
+  for (int j = p.nj; j > 0; j -= 2) p.nunits += j;
+  // groups of rows: whole rounds of one block per CU, no shorter than the FP32 sums allow,
+  // partial results within the given bytes.  The longest group decides a round's length.
+  const size_t unit_bytes = (size_t)kPI * 2 * kPJ * sizeof(double);
+  const int64_t seg = std::min<int64_t>(gp.kchunk, kPairSub);
+  const int64_t most = std::min<int64_t>((int64_t)(bytes / (unit_bytes * p.nunits)), (nd + seg - 1) / seg);
+  for (int64_t s = 1; s <= most && s * p.nunits <= 1024; ++s) {
+    const int64_t rounds = (s * p.nunits + 255) / 256;
+    const int64_t longest = ((nd + s - 1) / s + seg - 1) / seg * seg;  // whole FP32 sums
+    const double fill = (double)nd * p.nunits / ((double)rounds * 256.0 * longest);
+    if (fill > p.fill + 0.02) {
+      p.fill = fill;
+      p.groups = (int)s;
+    }
+  }
+  p.kchunk = gp.kchunk;
+  p.fill *= (2.0 * gp.ntiles * kT * kT) / ((double)p.nunits * kPI * 2 * kPJ);
+  return p;
+}
+
+hipError_t launch_gram_pair_bf16x3(const float* X, const float* Y, int64_t nd, int ns, const PairPlan& p,
+                                   double* partial, double* Hs, double* Ms, hipStream_t s) {
+  const int nblocks = p.nunits * p.groups;
+  const int per_xcd = (nblocks + 7) / 8;
+  hipLaunchKernelGGL(gram_pair_kernel, dim3((unsigned)(per_xcd * 8)), dim3(kPairThreads), 0, s, X, Y, nd, ns, p.nj,
+                     p.nunits, nblocks, per_xcd, p.groups, p.kchunk, partial);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(gram_pair_reduce_kernel, dim3(kPI * 2 * kPJ / 256, (unsigned)p.nunits), dim3(256), 0, s, partial,
+                     ns, p.nj, p.nunits, p.groups, Hs, Ms);
   return hipGetLastError();
 }
 
