@@ -235,11 +235,20 @@ hipError_t launch_narrow_rows(const double* P, int64_t ldw, int64_t r, int ns, f
                               hipStream_t s);
 
 // Diagonal scaling of the pencil (Hs, Ms) by sc_i = Ms_ii^-1/2 (sc: ns doubles, written),
-// and the matching back-transformation Z(i, j) <- sc_i Z(i, j).
+// and the matching back-transformation Z(i, j) = sc_i W(i, j) (W may be Z).
 hipError_t launch_pencil_scale(double* Hs, double* Ms, double* sc, int ns, hipStream_t s);
-hipError_t launch_row_scale(double* Z, const double* sc, int ns, hipStream_t s);
+hipError_t launch_row_scale(const double* W, double* Z, const double* sc, int ns, hipStream_t s);
 // d[i] = A(i, i) for an ns x ns column-major matrix
 hipError_t launch_copy_diag(const double* A, double* d, int ns, hipStream_t s);
+
+// Householder tridiagonalisation of the symmetric A (n x n, ld n, upper triangle read; its
+// columns receive the reflectors, D, E and tau the rest, as LAPACK's dsytrd leaves them with
+// uplo U) and C <- Q C.  tridiag_groups is 0 where n is outside the kernels' range; msg:
+// tridiag_msg_bytes(n) of scratch; info is set to n + 1 when the launch could not finish.
+int tridiag_groups(int n);
+size_t tridiag_msg_bytes(int n);
+hipError_t launch_tridiag(double* A, int n, double* D, double* E, double* tau, void* msg, int* info, hipStream_t s);
+hipError_t launch_backtransform(const double* A, const double* tau, int n, double* C, hipStream_t s);
 
 template <typename TX, typename TO>
 hipError_t launch_rotate_f64(const TX* X, const double* Z, TO* O, int64_t nd, int ns, hipStream_t s);

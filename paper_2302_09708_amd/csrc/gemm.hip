@@ -271,11 +271,11 @@ __global__ void pencil_diag_kernel(const double* __restrict__ Ms, double* __rest
   sc[i] = d > 0.0 ? 1.0 / sqrt(d) : 1.0;
 }
 
-// Z(i, j) <- sc_i Z(i, j)
-__global__ void row_scale_kernel(double* __restrict__ Z, const double* __restrict__ sc, int ns) {
+// Z(i, j) = sc_i W(i, j)
+__global__ void row_scale_kernel(const double* W, double* Z, const double* __restrict__ sc, int ns) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= (int64_t)ns * ns) return;
-  Z[e] *= sc[(int)(e % ns)];
+  Z[e] = W[e] * sc[(int)(e % ns)];
 }
 
 hipError_t launch_pencil_scale(double* Hs, double* Ms, double* sc, int ns, hipStream_t s) {
@@ -295,9 +295,9 @@ hipError_t launch_copy_diag(const double* A, double* d, int ns, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_row_scale(double* Z, const double* sc, int ns, hipStream_t s) {
+hipError_t launch_row_scale(const double* W, double* Z, const double* sc, int ns, hipStream_t s) {
   const int64_t n2 = (int64_t)ns * ns;
-  hipLaunchKernelGGL(row_scale_kernel, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, s, Z, sc, ns);
+  hipLaunchKernelGGL(row_scale_kernel, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, s, W, Z, sc, ns);
   return hipGetLastError();
 }
 
