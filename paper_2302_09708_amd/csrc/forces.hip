@@ -13,35 +13,12 @@
 // Every sum has a fixed order (bitwise reproducible); FP64 arithmetic.
 #include <algorithm>
 
+#include "reduce.h"
 #include "stencil.h"
 
 namespace chefsi {
 
 namespace {
-
-// v[i] summed over the 64 lanes for every i < N (N a power of two, at most 64): each of the
-// first log2 N exchanges halves the values a lane keeps, so lane l ends with the sum of
-// value l / (64 / N) in v[0] after N - 1 + log2(64 / N) exchanges (6 N for N plain sums).
-template <int M, int OFF, int N>
-__device__ __forceinline__ void wave_sums_step(double (&v)[N], int lane) {
-  if constexpr (M >= 1) {
-    const bool up = lane & OFF;
-#pragma unroll
-    for (int i = 0; i < M; ++i) {
-      const double keep = up ? v[i + M] : v[i];
-      const double give = up ? v[i] : v[i + M];
-      v[i] = keep + __shfl_xor(give, OFF, 64);
-    }
-    wave_sums_step<M / 2, OFF / 2>(v, lane);
-  } else if constexpr (OFF >= 1) {
-    v[0] += __shfl_xor(v[0], OFF, 64);
-    wave_sums_step<0, OFF / 2>(v, lane);
-  }
-}
-template <int N>
-__device__ __forceinline__ void wave_sums(double (&v)[N], int lane) {
-  wave_sums_step<N / 2, 32>(v, lane);
-}
 
 constexpr int kNgWaves = 4;  // waves per block: one atom, consecutive orbital groups
 constexpr int kNgP = 4;      // projectors per pass
@@ -145,13 +122,13 @@ __global__ __launch_bounds__(64 * kNgWaves) void nl_grad_kernel(NlGradArgs<TV> a
       double h[NR];
 #pragma unroll
       for (int k = 0; k < NR; ++k) h[k] = acc[u][k];
-      wave_sums<NR>(h, lane);
+      wave_sums(h, lane);
       if (lane % (64 / NR) == 0) red[wave][lane / (64 / NR)] = h[0];
       if constexpr (STRESS) {  // the other eight of the forty
         double g[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) g[k] = acc[u][NR + k];
-        wave_sums<8>(g, lane);
+        wave_sums(g, lane);
         if (lane % 8 == 0) red[wave][NR + lane / 8] = g[0];
       }
       __syncthreads();

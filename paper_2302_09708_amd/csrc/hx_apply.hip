@@ -118,9 +118,9 @@ __global__ __launch_bounds__(hx_max_threads(PY)) void hx_apply_kernel(HxArgs<TI,
   // hardware deals consecutive block ids to the 8 XCDs in turn
   const int64_t logical = (int64_t)(blockIdx.x % 8) * a.per_xcd + blockIdx.x / 8;
   if (logical >= a.nblocks) return;
-  const int per_vec = a.nty * a.nzc;
-  const int64_t vec = logical / per_vec;
-  const int rem = (int)(logical % per_vec);
+  const unsigned per_vec = (unsigned)(a.nty * a.nzc);  // block ids are 32 bits wide
+  const int64_t vec = (unsigned)logical / per_vec;
+  const int rem = (int)((unsigned)logical % per_vec);
   const int tile = rem % a.nty;
   const int zchunk = rem / a.nty;
   const int y0 = tile * a.ty;
@@ -429,10 +429,16 @@ HxPlan plan_hx(int nx, int ny, int nz, int ns, int radius, int elem_bytes, int p
       }
     }
   }
-  // z chunks: enough blocks to fill 256 CUs several times over, chunks no thinner than 2r planes
+  // z chunks.  With 512 or more (tile, orbital) pairs: enough blocks to fill 256 CUs several
+  // times over, chunks no thinner than 2r planes (a chunk fetches 2r planes beside its own).
+  // With fewer the march itself is what takes the time (about 0.8 us a plane with one or two
+  // blocks on a CU), so chunks go down to 4 planes: 24^3, 40 orbitals FP64 at 12 / 4 planes
+  // 17.8 / 14.1 us, 72^3, one orbital 20.5 / 12.6 (2 planes 13.1, 1 18.9), 16 orbitals at 12 /
+  // 8 planes 64.7 / 64.0 (4 planes 75.5).
   const int64_t xyblocks = (int64_t)best.nty * ns;
-  int nzc = (int)std::max<int64_t>(1, (2048 + xyblocks - 1) / xyblocks);
-  nzc = std::min(nzc, std::max(1, nz / std::max(1, 2 * radius)));
+  const int want = xyblocks >= 512 ? 2048 : 1536, thinnest = xyblocks >= 512 ? std::max(1, 2 * radius) : 4;
+  int nzc = (int)std::max<int64_t>(1, (want + xyblocks - 1) / xyblocks);
+  nzc = std::min(nzc, std::max(1, nz / thinnest));
   best.zc = (nz + nzc - 1) / nzc;
   best.nzc = (nz + best.zc - 1) / best.zc;
   return best;
