@@ -155,7 +155,8 @@ struct chefsi_handle {
   double* ent_val64 = nullptr;
   float* ent_val32 = nullptr;
   // pinned host staging for the small device-to-host reads (Ritz values, dense-stage status,
-  // Cholesky pivots: max_ns doubles + 16 status words; force and stress sums: 10 per atom)
+  // Cholesky pivots: max_ns doubles + 16 status words; force and stress sums: 10 per atom;
+  // Lanczos coefficients)
   double* pinned = nullptr;
   int n_pts = 0;     // scatter records
   int n_hxrec = 0;   // stencil-pass records
@@ -1530,7 +1531,7 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
     h->hx_plan = plan_hx(h->n[0], h->n[1], h->n[2], 1, h->radius, precision == CHEFSI_FP64 ? 8 : 4, 0, 0);
     check(h->hx_plan.ok, "no stencil tiling fits this grid");
 
-    const size_t pinned_doubles = std::max((size_t)max_ns + 8, (size_t)h->n_atoms * 10);
+    const size_t pinned_doubles = std::max({(size_t)max_ns + 8, (size_t)h->n_atoms * 10, (size_t)kVecBlocks});
     if (hipHostMalloc((void**)&h->pinned, pinned_doubles * sizeof(double), hipHostMallocDefault) != hipSuccess) {
       h->pinned = nullptr;
       throw Error{CHEFSI_ERR_OOM, "pinned host allocation failed"};
@@ -1953,41 +1954,51 @@ void tridiagonal_top(const std::vector<double>& a, const std::vector<double>& b,
   *s_last = x[k - 1];
 }
 
+// The coefficients of up to kLzBatch steps are left on the device, behind the two sets of block
+// sums, and read together: the host only waits for a batch.  After an early stop (beta = 0)
+// the rest of a batch runs on non-finite vectors and is not looked at.
+constexpr int kLzScalars = kVecBlocks - 2 * kLzBlocks + 32;  // partial's rest and the out region behind it
+constexpr int kLzBatch = (kLzScalars - 1) / 2;
+
 template <typename TV>
 void lanczos_impl(chefsi_handle* h, const TV* v0, int steps, void* ws, const LzLayout& L, hipStream_t s,
                   std::vector<double>& a, std::vector<double>& b) {
   TV* vb[2] = {at<TV>(ws, L.v0), at<TV>(ws, L.v1)};
   double* w = at<double>(ws, L.w);
-  double* part = at<double>(ws, L.partial);
-  double* out = at<double>(ws, L.out);
-  double* pin = h->pinned;
-  auto read_scalar = [&]() {
-    HIP_TRY(hipMemcpyAsync(pin, out, sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    return pin[0];
-  };
+  double* dots = at<double>(ws, L.partial);
+  double* squares = dots + kLzBlocks;
+  double* scal = squares + kLzBlocks;  // |v0|, then alpha, beta of each step of the batch
+  double host[kLzScalars];
   // v_1 = v0 / ||v0||
   HIP_TRY(launch_widen<TV>(v0, h->nd, w, s));
-  HIP_TRY(launch_lanczos_norm<TV>(w, nullptr, 0.0, h->nd, part, out, s));
-  const double n0 = std::sqrt(read_scalar());
-  check(std::isfinite(n0) && n0 > 0.0, "the start vector must be finite and nonzero");
-  HIP_TRY(launch_lanczos_scale<TV>(w, 1.0 / n0, h->nd, vb[0], s));
+  HIP_TRY(launch_lanczos_norm<TV>(w, nullptr, nullptr, h->nd, squares, nullptr, s));
+  HIP_TRY(launch_lanczos_scale<TV>(w, squares, h->nd, vb[0], scal, s));
   int cur = 0;
-  double beta = 0.0;
-  for (int j = 0; j < steps; ++j) {
-    const TV* v = vb[cur];
-    TV* vprev = vb[cur ^ 1];
-    apply_fused<TV, double, double>(h, v, nullptr, w, 1, 1.0, 0.0, 0.0, at<double>(ws, L.alpha), s);
-    HIP_TRY(launch_lanczos_dot<TV>(w, v, j > 0 ? vprev : nullptr, beta, h->nd, part, out, s));
-    const double alpha = read_scalar();
-    HIP_TRY(launch_lanczos_norm<TV>(w, v, alpha, h->nd, part, out, s));
-    beta = std::sqrt(read_scalar());
-    if (!std::isfinite(alpha) || !std::isfinite(beta)) throw Error{CHEFSI_ERR_NONFINITE, "non-finite Lanczos coefficient"};
-    a.push_back(alpha);
-    b.push_back(beta);
-    if (beta == 0.0) break;
-    HIP_TRY(launch_lanczos_scale<TV>(w, 1.0 / beta, h->nd, vprev, s));  // v_{j+1} over v_{j-1}
-    cur ^= 1;
+  const double* beta = nullptr;  // the previous step's, on the device
+  for (int j0 = 0; j0 < steps; j0 += kLzBatch) {
+    const int nb = std::min(kLzBatch, steps - j0);
+    for (int i = 0; i < nb; ++i) {
+      const TV* v = vb[cur];
+      TV* vprev = vb[cur ^ 1];
+      double* alpha = scal + 1 + 2 * i;
+      apply_fused<TV, double, double>(h, v, nullptr, w, 1, 1.0, 0.0, 0.0, at<double>(ws, L.alpha), s);
+      HIP_TRY(launch_lanczos_dot<TV>(w, v, beta != nullptr ? vprev : nullptr, beta, h->nd, dots, s));
+      HIP_TRY(launch_lanczos_norm<TV>(w, v, dots, h->nd, squares, alpha, s));
+      HIP_TRY(launch_lanczos_scale<TV>(w, squares, h->nd, vprev, alpha + 1, s));  // v_{j+1} over v_{j-1}
+      beta = alpha + 1;
+      cur ^= 1;
+    }
+    HIP_TRY(hipMemcpyAsync(h->pinned, scal, (size_t)(1 + 2 * nb) * sizeof(double), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    std::memcpy(host, h->pinned, (size_t)(1 + 2 * nb) * sizeof(double));
+    check(std::isfinite(host[0]) && host[0] > 0.0, "the start vector must be finite and nonzero");
+    for (int i = 0; i < nb; ++i) {
+      const double al = host[1 + 2 * i], be = host[2 + 2 * i];
+      if (!std::isfinite(al) || !std::isfinite(be)) throw Error{CHEFSI_ERR_NONFINITE, "non-finite Lanczos coefficient"};
+      a.push_back(al);
+      b.push_back(be);
+      if (be == 0.0) return;
+    }
   }
 }
 
@@ -2814,7 +2825,7 @@ int chefsi_kpoint_create(const chefsi_grid_t* grid, const double* veff_host, con
     HIP_TRY(hipGetDevice(&h->device));
     BLAS_TRY(rocblas_create_handle(&h->blas));
     BLAS_TRY(rocblas_set_atomics_mode(h->blas, rocblas_atomics_not_allowed));
-    const size_t pinned_doubles = std::max((size_t)max_ns + 8, (size_t)h->n_atoms * 10);
+    const size_t pinned_doubles = std::max({(size_t)max_ns + 8, (size_t)h->n_atoms * 10, (size_t)kVecBlocks});
     if (hipHostMalloc((void**)&h->pinned, pinned_doubles * sizeof(double), hipHostMallocDefault) != hipSuccess) {
       h->pinned = nullptr;
       throw Error{CHEFSI_ERR_OOM, "pinned host allocation failed"};

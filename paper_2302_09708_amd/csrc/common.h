@@ -10,8 +10,9 @@
 namespace chefsi {
 
 constexpr int kMaxRadius = 6;  // finite-difference order up to 12
-constexpr int kVecThreads = 256;   // fixed-grid reductions (Lanczos sums, stress sums)
-constexpr int kVecBlocks = 1024;
+constexpr int kVecThreads = 256;   // fixed-grid reductions (Lanczos sums)
+constexpr int kVecBlocks = 1024;   // doubles of their block sums and scalars
+constexpr int kLzBlocks = 448;     // blocks: two sets of block sums leave room for the scalars
 constexpr int kHxMaxThreads = 512;  // widest supported x row (one thread per x point)
 // stencil threads per block for PY rows per thread (1024 keeps 128 VGPRs per lane, 512 keeps 256)
 constexpr int hx_max_threads(int py) { return py == 1 ? 1024 : 512; }
@@ -329,21 +330,22 @@ template <typename TV>
 hipError_t launch_stress_sums(const StressArgs<TV>& a, int radius, int64_t max_partials, hipStream_t s);
 
 // ---------------------------------------------------------------------------
-// Lanczos vector kernels (fixed grid of kVecBlocks x kVecThreads, fixed-order sums).
-// dot:   w -= beta vp (vp may be null); out[0] = v . w
-// norm:  w -= alpha v (v may be null);  out[0] = w . w
-// scale: out = TV(w * inv);  widen: w = double(x)
-// partial: kVecBlocks doubles of scratch.
+// Lanczos vector kernels (fixed grid of kLzBlocks x kVecThreads, fixed-order sums); partial,
+// dots, squares: kLzBlocks block sums, written by one kernel and added up by the next.
+// dot:   w -= *beta vp (vp may be null);  partial of v . w
+// norm:  *alpha_out = sum dots, w -= it v (v may be null: w as it is);  partial of w . w
+// scale: *norm_out = sqrt(sum squares);  out = TV(w / it);  widen: w = double(x)
 // ---------------------------------------------------------------------------
 
 template <typename TV>
-hipError_t launch_lanczos_dot(double* w, const TV* v, const TV* vp, double beta, int64_t n, double* partial,
-                              double* out, hipStream_t s);
+hipError_t launch_lanczos_dot(double* w, const TV* v, const TV* vp, const double* beta, int64_t n, double* partial,
+                              hipStream_t s);
 template <typename TV>
-hipError_t launch_lanczos_norm(double* w, const TV* v, double alpha, int64_t n, double* partial, double* out,
-                               hipStream_t s);
+hipError_t launch_lanczos_norm(double* w, const TV* v, const double* dots, int64_t n, double* partial,
+                               double* alpha_out, hipStream_t s);
 template <typename TV>
-hipError_t launch_lanczos_scale(const double* w, double inv, int64_t n, TV* out, hipStream_t s);
+hipError_t launch_lanczos_scale(const double* w, const double* squares, int64_t n, TV* out, double* norm_out,
+                                hipStream_t s);
 template <typename TV>
 hipError_t launch_widen(const TV* x, int64_t n, double* w, hipStream_t s);
 
