@@ -141,6 +141,7 @@ struct chefsi_handle {
   int64_t* chi_off = nullptr;
   int* nproj = nullptr;
   int* poff = nullptr;
+  int* supp_box = nullptr;  // 6 per atom; null when an atom's support is too large for the LDS gradient
   double* chi64 = nullptr;
   float* chi32 = nullptr;
   double* gdv64 = nullptr;
@@ -1389,9 +1390,52 @@ void build_scatter_records(chefsi_handle* h) {
   h->n_pts = (int)recs.size();
 }
 
+// The box of every atom's support (first grid index and length in each direction; the shortest
+// wrapped interval in a periodic one), or nothing when an atom's points or its box, longer by
+// r at both ends of a direction, exceed what the force kernel keeps in registers and LDS.
+std::vector<int> support_boxes(const chefsi_handle* h) {
+  std::vector<int> box(6 * (size_t)h->n_atoms, 0);
+  std::vector<char> seen;
+  for (int J = 0; J < h->n_atoms; ++J) {
+    const int64_t s0 = h->supp_ptr_h[J], s1 = h->supp_ptr_h[J + 1];
+    if (s1 - s0 > kGradBoxPoints) return {};
+    int* b = box.data() + 6 * (size_t)J;
+    for (int d = 0; d < 3; ++d) {
+      const int n = h->n[d], div = d == 0 ? 1 : (d == 1 ? h->n[0] : h->n[0] * h->n[1]);
+      seen.assign(n, 0);
+      for (int64_t s = s0; s < s1; ++s) seen[h->supp_idx_h[s] / div % n] = 1;
+      int first = 0, last = n - 1;
+      while (first < n && !seen[first]) ++first;
+      if (first == n) {  // no points
+        b[d] = 0;
+        b[3 + d] = 1;
+        continue;
+      }
+      while (!seen[last]) --last;
+      b[d] = first;
+      b[3 + d] = last - first + 1;
+      if (h->bc[d] == 0) {  // the longest run of unseen points between two seen ones, if longer
+        for (int i = first, gap = 0; i <= last; ++i) {
+          gap = seen[i] ? 0 : gap + 1;
+          if (gap > 0 && n - gap < b[3 + d]) {
+            b[d] = i + 1;
+            b[3 + d] = n - gap;
+          }
+        }
+      }
+    }
+    for (int d = 0; d < 3; ++d) {
+      int64_t v = 1;
+      for (int e = 0; e < 3; ++e) v *= b[3 + e] + (e == d ? 2 * h->radius : 0);
+      if (v > kGradBoxValues) return {};
+    }
+  }
+  return box;
+}
+
 void release(chefsi_handle* h) {
   free_band_tables(h);
-  void* ptrs[] = {h->veff64, h->veff32, h->supp_off, h->supp_idx, h->chi_off,  h->nproj,    h->poff,
+  void* ptrs[] = {h->veff64, h->veff32, h->supp_off, h->supp_idx, h->chi_off,  h->nproj,    h->poff,     h->supp_box,
                   h->chi64,  h->chi32,  h->gdv64,    h->gdv32,    h->rec,      h->ent_col,  h->hx_rec_ptr,
                   h->hx_rec64, h->hx_rec32,
                   h->ent_val64,
@@ -1598,6 +1642,8 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
       h->chi_off = upload(h, coff.data(), coff.size());
       h->nproj = upload(h, h->nproj_h.data(), h->nproj_h.size());
       h->poff = upload(h, poff.data(), poff.size());
+      const std::vector<int> box = support_boxes(h);
+      if (!box.empty()) h->supp_box = upload(h, box.data(), box.size());
       h->chi64 = upload(h, h->chi_h.data(), h->chi_h.size());
       std::vector<float> chi32(h->chi_h.begin(), h->chi_h.end());
       h->chi32 = upload(h, chi32.data(), chi32.size());
@@ -2092,6 +2138,7 @@ const double* nonlocal_sums(chefsi_handle* h, const TV* X, int ns, const double*
   a.chi = h->chi64;
   a.gdv = h->gdv64;
   a.dv = h->dv;
+  a.box = h->supp_box;
   a.part = at<double>(ws, L.part);
   double* out = at<double>(ws, L.sums);
   HIP_TRY((launch_nl_grad<TV>(a, h->radius, out, disp_host != nullptr ? 1.0 : -2.0, s)));

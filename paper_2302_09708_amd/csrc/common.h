@@ -283,6 +283,11 @@ hipError_t launch_rotate_bf16x3(const float* X, const double* Z, void* zsplit, f
 // with the central FD first derivative of radius r (periodic wrap or zero ghosts), then
 // out[J, d] = scale * sum_v part[J, v, d] (fixed order; 3 or 10 values per atom).
 // ---------------------------------------------------------------------------
+// Support points and staged values (the box of the support, longer by r at both ends of one
+// direction) of an atom that the kernel working from LDS takes.
+constexpr int kGradBoxPoints = 1536;
+constexpr int kGradBoxValues = 5120;
+
 template <typename TV>
 struct NlGradArgs {
   const TV* x;
@@ -303,7 +308,9 @@ struct NlGradArgs {
   const double* gdv;       // gamma dV per projector column
   double dv;
   double* part;            // n_atoms * ns * (3 or 10)
-  int ngroups, per_xcd;    // set by the launcher
+  const int* box;          // per atom the support's box: first index and length in each direction
+                           // (wrapped when periodic); null when some atom exceeds the limits above
+  int ngroups, per_xcd, gpo;  // set by the launcher
 };
 
 template <typename TV>

@@ -148,6 +148,181 @@ __global__ __launch_bounds__(64 * kNgWaves) void nl_grad_kernel(NlGradArgs<TV> a
   }
 }
 
+// The same results with the gradient's neighbourhood in LDS.  One block = one atom x kBoxOrb
+// orbitals, one orbital after the other.  The atom's support lies in a box of grid points
+// (wrapped in periodic directions); for each direction the block stages the box, longer by r
+// at both ends of that direction, and every thread forms the derivative at its (at most
+// kBoxPts) support points from LDS.  The staged values' source offsets, the points' places
+// in the box and their projector values stay in registers for all orbitals; the next
+// direction's values are in flight while one is summed.  Where the support or the box is
+// larger than the registers hold, nl_grad_kernel above does the work.
+// The wave sums of all the block's orbitals wait in LDS and are combined at its end: combined
+// orbital by orbital they were a third of the time (2.36 and 2.95 ms).
+// 72^3, 128 atoms (905 points, a box of 13^3), 600 orbitals, order 12, FP64: forces 3.8 ->
+// 1.95 ms, stress 3.9 -> 2.5 ms; bound by latency at one block per CU (LDS busy 32 % of the
+// cycles, VALU 30 %): the registers leave no room for a second.
+constexpr int kBoxThreads = 512;
+constexpr int kBoxWaves = kBoxThreads / 64;
+constexpr int kBoxPts = kGradBoxPoints / kBoxThreads;    // support points per thread
+constexpr int kBoxStage = kGradBoxValues / kBoxThreads;  // staged values per thread and direction
+constexpr int kBoxOrb = 16;
+
+template <typename TV, int R, bool STRESS>
+__global__ __launch_bounds__(kBoxThreads, 2) void nl_grad_box_kernel(NlGradArgs<TV> a) {
+  constexpr int NO = STRESS ? 10 : 3;
+  constexpr int NR = STRESS ? 3 : 1;  // reductions of 16 sums per orbital
+  __shared__ TV box[2][kGradBoxValues];
+  __shared__ double red[kBoxOrb][kBoxWaves][16 * NR];  // every orbital's sums, combined at the end
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t logical = (int64_t)(blockIdx.x % 8) * a.per_xcd + blockIdx.x / 8;
+  if (logical >= (int64_t)a.n_atoms * a.ngroups) return;
+  const int atom = (int)(logical % a.n_atoms);
+  const int v0 = (int)(logical / a.n_atoms) * a.gpo, v1 = min(v0 + a.gpo, a.ns);
+  const int s0 = a.supp_off[atom], n = a.supp_off[atom + 1] - s0;
+  const int npj = a.nproj[atom];
+  const double* chi = a.chi + a.chi_off[atom];
+  const int ext[3] = {a.nx, a.ny, a.nz}, str[3] = {1, a.nx, a.nx * a.ny};
+  int lo[3], len[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    lo[d] = a.box[6 * atom + d];
+    len[d] = a.box[6 * atom + 3 + d];
+  }
+  // source offset of every staged value (past the end: a zero)
+  unsigned off[3][kBoxStage];
+  int count[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const int e0 = len[0] + (d == 0 ? 2 * R : 0), e1 = len[1] + (d == 1 ? 2 * R : 0), e2 = len[2] + (d == 2 ? 2 * R : 0);
+    count[d] = e0 * e1 * e2;
+#pragma unroll
+    for (int i = 0; i < kBoxStage; ++i) {
+      const int e = tid + i * kBoxThreads;
+      int src = -1;
+      if (e < count[d]) {
+        const int q = e / e0;
+        int c[3] = {lo[0] + e - q * e0, lo[1] + q % e1, lo[2] + q / e1};
+        c[d] -= R;
+        src = 0;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          if (a.periodic[b]) {  // the box is no longer than the period, r no longer than it
+            c[b] = c[b] < 0 ? c[b] + ext[b] : c[b];
+            c[b] = c[b] >= ext[b] ? c[b] - ext[b] : c[b];
+            c[b] = c[b] >= ext[b] ? c[b] - ext[b] : c[b];
+          }
+          src = c[b] < 0 || c[b] >= ext[b] || src < 0 ? -1 : src + c[b] * str[b];
+        }
+      }
+      off[d][i] = lane_off<TV>(src);
+    }
+  }
+  // the thread's support points: place in the box, displacement
+  int place[kBoxPts][3];
+  double w[kBoxPts][3];
+#pragma unroll
+  for (int t = 0; t < kBoxPts; ++t) {
+    const int s = tid + t * kBoxThreads;
+    const int i = s < n ? a.supp_idx[s0 + s] : 0;
+    const int z = i / str[2], yx = i - z * str[2], y = yx / a.nx;
+    int c[3] = {yx - y * a.nx, y, z};
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      c[b] -= lo[b];
+      c[b] = c[b] < 0 ? c[b] + ext[b] : c[b];
+      place[t][b] = s < n ? c[b] : 0;
+      w[t][b] = STRESS && s < n ? a.disp[3 * (int64_t)(s0 + s) + b] : 0.0;
+    }
+  }
+  const int nbytes = (int)(a.nd * (int64_t)sizeof(TV));
+  TV st[kBoxStage];
+  auto fetch = [&](int v, int d) {
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(a.x + (int64_t)v * a.nd, v < v1 ? nbytes : 0);
+#pragma unroll
+    for (int i = 0; i < kBoxStage; ++i)
+      st[i] = bload<TV>(r, d == 0 ? off[0][i] : (d == 1 ? off[1][i] : off[2][i]), 0u);
+  };
+
+  for (int a0 = 0; a0 < npj; a0 += kNgP) {
+    double c[kBoxPts][kNgP];
+#pragma unroll
+    for (int t = 0; t < kBoxPts; ++t)
+#pragma unroll
+      for (int k = 0; k < kNgP; ++k) {
+        const int s = tid + t * kBoxThreads;
+        c[t][k] = s < n && a0 + k < npj ? chi[(int64_t)(a0 + k) * n + s] : 0.0;
+      }
+    auto stage = [&](int d, int buf) {
+      const int cnt = d == 0 ? count[0] : (d == 1 ? count[1] : count[2]);
+#pragma unroll
+      for (int i = 0; i < kBoxStage; ++i)
+        if (wave * 64 + i * kBoxThreads < cnt) box[buf][tid + i * kBoxThreads] = st[i];
+    };
+    fetch(v0, 0);
+    stage(0, 0);
+    fetch(v0, 1);
+    int buf = 0;
+    for (int v = v0; v < v1; ++v) {
+      double acc[16];  // forces: four sums of psi, then of each derivative; stress: those of one direction
+#pragma unroll
+      for (int k = 0; k < 16; ++k) acc[k] = 0.0;
+#pragma unroll
+      for (int d = 0; d < 3; ++d, buf ^= 1) {
+        __syncthreads();  // this direction's box is staged, the other buffer is no longer read
+        stage(d < 2 ? d + 1 : 0, buf ^ 1);
+        fetch(d < 1 ? v : v + 1, d < 1 ? 2 : d - 1);
+        const int e0 = len[0] + (d == 0 ? 2 * R : 0), e1 = len[1] + (d == 1 ? 2 * R : 0);
+        const int step = d == 0 ? 1 : (d == 1 ? e0 : e0 * e1);
+#pragma unroll
+        for (int t = 0; t < kBoxPts; ++t) {
+          if (wave * 64 + t * kBoxThreads >= n) continue;
+          const TV* p0 = box[buf] + place[t][0] + e0 * (place[t][1] + e1 * place[t][2]) + R * step;
+          double g = 0.0;
+#pragma unroll
+          for (int p = 1; p <= R; ++p) g += a.c[d][p] * (double(p0[p * step]) - double(p0[-p * step]));
+          if (d == 0) {
+            const double yv = double(p0[0]);
+#pragma unroll
+            for (int k = 0; k < kNgP; ++k) acc[k] += c[t][k] * yv;
+          }
+          if (STRESS) {
+#pragma unroll
+            for (int b = 0; b < 3; ++b)
+#pragma unroll
+              for (int k = 0; k < kNgP; ++k) acc[kNgP + b * kNgP + k] += (c[t][k] * w[t][b]) * g;
+          } else {
+#pragma unroll
+            for (int k = 0; k < kNgP; ++k) acc[kNgP + d * kNgP + k] += c[t][k] * g;
+          }
+        }
+        if (STRESS || d == 2) {
+          wave_sums(acc, lane);
+          if (lane % 4 == 0) red[v - v0][wave][(STRESS ? 16 * d : 0) + lane / 4] = acc[0];
+#pragma unroll
+          for (int k = 0; k < 16; ++k) acc[k] = 0.0;
+        }
+      }
+    }
+    __syncthreads();
+    for (int e = tid; e < (v1 - v0) * NO; e += kBoxThreads) {
+      const int v = e / NO, i = e % NO;
+      auto sum = [&](int k) {
+        double r = red[v][0][k];
+        for (int j = 1; j < kBoxWaves; ++j) r += red[v][j][k];
+        return r;
+      };
+      // result i: the energy (stress, 0), else direction pair 3 d + b = i - 1; forces: direction i
+      const int at = !STRESS ? kNgP * (i + 1) : (i == 0 ? 0 : 16 * ((i - 1) / 3) + kNgP * (1 + (i - 1) % 3));
+      double tot = 0.0;
+      for (int k = 0; k < kNgP && a0 + k < npj; ++k) tot += a.gdv[a.poff[atom] + a0 + k] * (sum(k) * sum(at + k));
+      double* out = a.part + ((int64_t)atom * a.ns + v0 + v) * NO + i;
+      tot *= a.occ[v0 + v] * a.dv;
+      *out = a0 == 0 ? tot : *out + tot;
+    }
+    __syncthreads();  // the sums are read before another pass of projectors writes its own
+  }
+}
+
 // out[J * no + d] = scale * sum over orbitals of part[(J * ns + v) * no + d], one block per
 // atom: thread t adds orbitals t, t + 256, ..., then a tree over the threads.
 __global__ __launch_bounds__(256) void atom_sums_kernel(const double* __restrict__ part, int ns, int no, double scale,
@@ -375,6 +550,13 @@ hipError_t launch_stress_r(const StressArgs<TV>& a, const HxPlan& p, int grid, s
 template <typename TV, int R>
 hipError_t launch_ng(const NlGradArgs<TV>& a, hipStream_t s) {
   const dim3 grid((unsigned)(a.per_xcd * 8)), block(64 * kNgWaves);
+  if (a.box != nullptr) {
+    if (a.disp != nullptr)
+      hipLaunchKernelGGL((nl_grad_box_kernel<TV, R, true>), grid, dim3(kBoxThreads), 0, s, a);
+    else
+      hipLaunchKernelGGL((nl_grad_box_kernel<TV, R, false>), grid, dim3(kBoxThreads), 0, s, a);
+    return hipGetLastError();
+  }
   if (a.disp != nullptr)
     hipLaunchKernelGGL((nl_grad_kernel<TV, R, true>), grid, block, 0, s, a);
   else
@@ -391,6 +573,10 @@ hipError_t launch_nl_grad(const NlGradArgs<TV>& a0, int radius, double* out, dou
   const int per_block = kNgWaves * (a.disp != nullptr ? 1 : 2);
   const int no = a.disp != nullptr ? 10 : 3;
   a.ngroups = (a.ns + per_block - 1) / per_block;
+  if (a.box != nullptr) {  // as many orbitals per block as leave about four blocks per CU
+    a.gpo = (int)std::max<int64_t>(1, std::min<int64_t>(kBoxOrb, (int64_t)a.n_atoms * a.ns / 1024));
+    a.ngroups = (a.ns + a.gpo - 1) / a.gpo;
+  }
   a.per_xcd = (int)(((int64_t)a.n_atoms * a.ngroups + 7) / 8);
   hipError_t e;
   switch (radius) {
