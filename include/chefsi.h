@@ -112,11 +112,14 @@ typedef struct {
  * arithmetic of filtering/projection/rotation; the dense stage is always FP64.
  * Returns CHEFSI_ERR_INVALID_ARG on inconsistent input (including a support
  * index outside the grid or not strictly increasing), or with more than 65535
- * projectors in all.  The projector term starts in the stencil pass (records; see
- * chefsi_set_projector_pass) unless the projectors are too many for the block's
- * coefficient row to fit in LDS beside the default tile (in FP64 about 5000 on a grid
- * 120 points wide): the handle then starts on the band pass, and is refused only when a
- * grid point also lies in more than 128 projector supports. */
+ * projectors in all.  Where the projector term is added (see chefsi_set_projector_pass) until
+ * a call chooses: a handle for at least 8 orbitals and 2^20 values (Nd max_ns) takes the band
+ * pass, a mixed one only in the filter (its single applications keep the records); smaller
+ * handles, and those with a grid point in more than 128 projector supports, take the records.
+ * When the projectors are too many for the block's coefficient row to fit in LDS beside the
+ * default tile (in FP64 about 5000 on a grid 120 points wide) the handle is on the band pass
+ * whatever its size, and is refused only when a grid point also lies in more than 128
+ * projector supports. */
 int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chefsi_nonlocal_t* nl,
                   int32_t precision, int32_t max_ns, chefsi_handle_t** out);
 
@@ -156,7 +159,7 @@ int chefsi_handle_bytes(const chefsi_handle_t* h, size_t* bytes);
  * per thread} to tiling[0..3]. */
 int chefsi_set_stencil_tiling(chefsi_handle_t* h, int32_t rows_per_thread, int32_t row_groups);
 /* Where the projector term of H X is added (Sec. 2.1, third bullet; results agree to
- * rounding).  in_stencil = 1 (default): points inside at most four projector entries
+ * rounding).  in_stencil = 1: points inside at most four projector entries
  * take it inside the stencil pass from per-point records, the others in a separate
  * scatter pass, after a gather of the coefficients over each atom's support.
  * in_stencil = 0 (band pass): the stencil pass runs without records, and one pass over
@@ -168,16 +171,18 @@ int chefsi_set_stencil_tiling(chefsi_handle_t* h, int32_t rows_per_thread, int32
  * pass is then refused with CHEFSI_ERR_INVALID_ARG and the handle stays on the record
  * route; the record route is refused, the handle staying on the band pass, when the
  * current tiling leaves no LDS for its records.  Rebuilds the handle's tables (the band
- * pass holds partial sums for max_ns orbitals on the device); for tuning and tests, not
- * while calls on the handle are in flight. */
+ * pass holds partial sums, 256 MiB or 64 orbitals' worth at most: in the call's workspace on a
+ * handle that chefsi_create put on it, on the device beside the tables otherwise); for tuning
+ * and tests, not while calls on the handle are in flight.  What chefsi_create chose for a
+ * filter is replaced too. */
 int chefsi_set_projector_pass(chefsi_handle_t* h, int32_t in_stencil);
 
 /* Picks the stencil tiling and the projector split by timing them (the planner's
  * tilings of at least r + 1 rows with 1 to 4 rows per thread, each with the projector term
  * in the stencil pass for points inside at most four entries, where the records fit in LDS,
  * and with every term in the band pass): three
- * filter-form H applications per candidate on the first min(ns, 1024) orbitals of the
- * device block X (read only; the workspace block takes the results), on `stream`, which
+ * filter-form H applications per candidate on the first min(ns, 1024) orbitals, the four
+ * best of the faster route again on min(ns, 2048), of the device block X (read only; the workspace block takes the results), on `stream`, which
  * the call synchronises.  Keeps the fastest and, when choice is not NULL, writes
  * {rows per thread, row groups, in_stencil} to choice[0..2] (the band pass is skipped
  * when chefsi_set_projector_pass would refuse it).  Results after tuning agree

@@ -186,6 +186,7 @@ struct NbArgs {
   const int* gent_loc;  // point of each gather entry, relative to its region's first point
   const TC* gent_chi;
   const TC* alpha;      // scatter: projector-major coefficients (the region's staged in LDS)
+  int lda;              // orbitals per projector in alpha (ns of the whole block)
   TC sa;
   TC* partial;          // nslots x ns, projector slot major
   int ngroups;          // orbital groups (set by the launcher)
@@ -198,7 +199,7 @@ template <typename TY, typename TC>
 hipError_t launch_nl_band(const NbArgs<TY, TC>& a, bool scatter, bool gather, hipStream_t s);
 template <typename TC>
 hipError_t launch_nl_band_reduce(const TC* partial, const int* q_slot_ptr, const int* q_slot, const TC* gdv,
-                                 int np_tot, int ns, TC* alpha, hipStream_t s);
+                                 int np_tot, int ns, int lda, TC* alpha, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // Dense products on MFMA.

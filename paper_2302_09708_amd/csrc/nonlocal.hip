@@ -87,8 +87,10 @@ __global__ __launch_bounds__(256) void nl_project_kernel(NlArgs<TI, TC> a) {
 
 // The same sums for few (atom, orbital) pairs: a block owns one atom and V orbitals, its
 // four waves every fourth 64 support points, kNlU of them fetched at once, so an atom's
-// serial chain of dependent gathers is 4 kNlU times shorter.  Used below kNlFewBlocks blocks
-// of the other kernel, where those waves leave the chip idle: 24^3, 8 atoms, 40 orbitals 8.6
+// serial chain of dependent gathers is 4 kNlU times shorter.  Used in FP64 below kNlFewBlocks
+// blocks of the other kernel, where those waves leave the chip idle (FP32 coefficients keep
+// the other kernel's order of summation: the split-bf16 projection built on them is compared
+// in FP64 with what it was): 24^3, 8 atoms, 40 orbitals 8.6
 // -> 4.1 us; 72^3, 128 atoms, one orbital 15.8 -> 4.6.
 constexpr int kNlU = 4;
 constexpr int kNlFewBlocks = 512;
@@ -154,7 +156,7 @@ hipError_t launch_nl_project(const NlArgs<TI, TC>& a, hipStream_t s) {
   NlArgs<TI, TC> b = a;
   b.ngroups = (a.ns + per_block - 1) / per_block;
   const int64_t nb = (int64_t)a.n_atoms * b.ngroups;
-  if (nb < kNlFewBlocks) {
+  if (sizeof(TC) == 8 && nb < kNlFewBlocks) {
     const dim3 block(64 * kNlWaves);
     if (a.ns < 4)
       hipLaunchKernelGGL((nl_project_few_kernel<TI, TC, 1>), dim3((unsigned)(a.n_atoms * a.ns)), block, 0, s, a);
@@ -289,7 +291,7 @@ __global__ __launch_bounds__(kBandThreads) void nl_band_kernel(NbArgs<TY, TC> a,
 #pragma unroll
     for (int j = 0; j < AJ; ++j) {
       const int it = tid + j * kBandThreads, ls = it / G, u = it % G;
-      an[j] = it < nitem && v0 + u < a.ns ? a.alpha[(int64_t)sq[ls] * a.ns + v0 + u] : TC(0);
+      an[j] = it < nitem && v0 + u < a.ns ? a.alpha[(int64_t)sq[ls] * a.lda + v0 + u] : TC(0);
     }
   };
   auto stage_alpha = [&](const TC (&an)[AJ]) {
@@ -391,32 +393,32 @@ template <typename TC>
 __global__ __launch_bounds__(256) void nl_band_reduce_kernel(const TC* __restrict__ partial,
                                                              const int* __restrict__ q_slot_ptr,
                                                              const int* __restrict__ q_slot,
-                                                             const TC* __restrict__ gdv, int np_tot, int ns,
+                                                             const TC* __restrict__ gdv, int np_tot, int ns, int lda,
                                                              TC* __restrict__ alpha) {
   const int q = blockIdx.y;
   const int v = blockIdx.x * 256 + threadIdx.x;
   if (q >= np_tot || v >= ns) return;
   TC sum = TC(0);
   for (int k = q_slot_ptr[q]; k < q_slot_ptr[q + 1]; ++k) sum += partial[(int64_t)q_slot[k] * ns + v];
-  alpha[(int64_t)q * ns + v] = gdv[q] * sum;
+  alpha[(int64_t)q * lda + v] = gdv[q] * sum;
 }
 
 template <typename TC>
 hipError_t launch_nl_band_reduce(const TC* partial, const int* q_slot_ptr, const int* q_slot, const TC* gdv,
-                                 int np_tot, int ns, TC* alpha, hipStream_t s) {
+                                 int np_tot, int ns, int lda, TC* alpha, hipStream_t s) {
   if (np_tot <= 0 || ns <= 0) return hipSuccess;
   const dim3 grid((unsigned)((ns + 255) / 256), (unsigned)np_tot);
   hipLaunchKernelGGL(nl_band_reduce_kernel<TC>, grid, dim3(256), 0, s, partial, q_slot_ptr, q_slot, gdv, np_tot, ns,
-                     alpha);
+                     lda, alpha);
   return hipGetLastError();
 }
 
 template hipError_t launch_nl_band<double, double>(const NbArgs<double, double>&, bool, bool, hipStream_t);
 template hipError_t launch_nl_band<float, float>(const NbArgs<float, float>&, bool, bool, hipStream_t);
 template hipError_t launch_nl_band<float, double>(const NbArgs<float, double>&, bool, bool, hipStream_t);
-template hipError_t launch_nl_band_reduce<double>(const double*, const int*, const int*, const double*, int, int,
+template hipError_t launch_nl_band_reduce<double>(const double*, const int*, const int*, const double*, int, int, int,
                                                   double*, hipStream_t);
-template hipError_t launch_nl_band_reduce<float>(const float*, const int*, const int*, const float*, int, int,
+template hipError_t launch_nl_band_reduce<float>(const float*, const int*, const int*, const float*, int, int, int,
                                                  float*, hipStream_t);
 
 template hipError_t launch_nl_scatter<double, double>(const NsArgs<double, double>&, hipStream_t);
