@@ -264,6 +264,14 @@ BlasGram plan_blas_gram(int64_t nd, int ns) {
   return b;
 }
 
+// gram_f64.hip forms both products in one launch and is the faster of the two everywhere but
+// on columns a multiple of 2 MiB apart: there the columns' lines of one row all fall into one
+// set of the L2, the 64-wide tiles lose their reuse, and rocBLAS's 128-wide ones win from
+// about 512 orbitals.  Both products, own / rocBLAS (us): 64^3 500 orbitals 2860 / 3053, 600
+// 4771 / 4343, 900 11.7 / 10.5 ms; 64x64x63 600 3617 / 4282; 72^3 600 5329 / 6239, 1200 20.9 /
+// 25.1 ms; 24^3 40 17 / 274.
+bool blas_gram_faster(int64_t nd, int ns) { return ns > 512 && nd % (1 << 18) == 0; }
+
 // FP64 products of the FP32 block of a mixed handle (its FP64 Rayleigh-Ritz pass): the
 // block is widened to FP64 one row panel at a time and each panel goes to rocBLAS dgemm.
 // A panel is `splits` chunks of kc rows; the Gram partials of chunk q of every panel
@@ -299,6 +307,7 @@ struct WsLayout {
   size_t bufB_bytes = 0, solver_bytes = 0, band_bytes = 0;
   GramPlan gram;
   BlasGram bgram;   // FP64 handles: Gram products of FP64 blocks
+  GramBothPlan both;  // the same in one launch
   PanelPlan pan;    // mixed handles: FP64 products of the FP32 block
   PairPlan pair;    // mixed handles: both split-bf16 Gram products at once
 };
@@ -368,7 +377,7 @@ size_t solver_workspace(chefsi_handle* h, int ns) {
     });
   if (h->precision == CHEFSI_FP64) {
     const BlasGram b = plan_blas_gram(h->nd, ns);
-    query([&] {
+    if (blas_gram_faster(h->nd, ns)) query([&] {
       rocblas_dgemm_strided_batched(h->blas, rocblas_operation_transpose, rocblas_operation_none, ns, ns,
                                     (rocblas_int)b.kc, &one, nullptr, (rocblas_int)h->nd, b.kc, nullptr,
                                     (rocblas_int)h->nd, b.kc, &one, nullptr, ns, (rocblas_stride)ns * ns, b.splits);
@@ -419,10 +428,14 @@ WsLayout layout(chefsi_handle* h, int ns) {
   off += align256(tridiag_msg_bytes(ns));
   L.gram = plan_gram(h->nd, ns);
   L.bgram = plan_blas_gram(h->nd, ns);
+  L.both = plan_gram_both(h->nd, ns);
   L.pan = plan_panels(h->nd, ns);
   L.partial = off;
-  const size_t part_bytes =
-      std::max(L.gram.partial_bytes, h->precision == CHEFSI_FP64 ? L.bgram.bytes : 2 * L.pan.part_bytes);
+  // (the eigensolve also keeps ns^2 values there)
+  const size_t part_bytes = h->precision == CHEFSI_FP64
+                                ? std::max({L.both.bytes, blas_gram_faster(h->nd, ns) ? L.bgram.bytes : 0,
+                                            (size_t)ns * ns * sizeof(double)})
+                                : std::max(L.gram.partial_bytes, 2 * L.pan.part_bytes);
   if (h->precision == CHEFSI_MIXED) {
     auto it = h->pair_cache.find(ns);
     if (it == h->pair_cache.end())
@@ -890,8 +903,14 @@ void gram_pair(chefsi_handle* h, const TX* X, const TY* Y, int ns, const WsLayou
                double* Ms, hipStream_t s, Gemm g) {
   if constexpr (std::is_same<TX, double>::value && std::is_same<TY, double>::value) {
     if (h->precision == CHEFSI_FP64) {
-      blas_gram(h, X, Y, ns, L, ws, Hs, s);
-      blas_gram(h, X, X, ns, L, ws, Ms, s);
+      if (blas_gram_faster(h->nd, ns)) {
+        blas_gram(h, X, Y, ns, L, ws, Hs, s);
+        blas_gram(h, X, X, ns, L, ws, Ms, s);
+        return;
+      }
+      ProfScope ps(h, P_GRAM, s);
+      HIP_TRY(launch_gram_both(X, Y, h->nd, ns, L.both, at<double>(ws, L.partial), Hs, Ms, s));
+      ps.done();
       return;
     }
   }

@@ -216,6 +216,17 @@ struct GramPlan {
   size_t partial_bytes = 0;
 };
 
+// Both FP64 Gram products of a projection at once (gram_f64.hip): t tiles of nf 16-column
+// fragments, t^2 units, each over `splits` chunks of `steps` 16-row steps.
+struct GramBothPlan {
+  int t = 0, nf = 0, units = 0, frags = 0, splits = 0;
+  int64_t steps = 0;
+  size_t bytes = 0;  // partial fragments
+};
+GramBothPlan plan_gram_both(int64_t nd, int ns);
+hipError_t launch_gram_both(const double* X, const double* Y, int64_t nd, int ns, const GramBothPlan& p,
+                            double* partial, double* Hs, double* Ms, hipStream_t s);
+
 GramPlan plan_gram(int64_t nd, int ns);
 
 template <typename TA, typename TB>
