@@ -113,9 +113,12 @@ typedef struct {
  * Returns CHEFSI_ERR_INVALID_ARG on inconsistent input (including a support
  * index outside the grid or not strictly increasing), or with more than 65535
  * projectors in all.  Where the projector term is added (see chefsi_set_projector_pass) until
- * a call chooses: a handle for at least 8 orbitals and 2^20 values (Nd max_ns) takes the band
- * pass, a mixed one only in the filter (its single applications keep the records); smaller
- * handles, and those with a grid point in more than 128 projector supports, take the records.
+ * a call chooses: an FP64 handle for at least 8 orbitals takes the band pass from 2^20 values
+ * (Nd max_ns) on, or from 2^18 where 512 or more points lie in more than four projector
+ * entries; a mixed one takes it in the filter only (its single applications keep the records),
+ * from 8 orbitals and 2^20 values on, or from 4 orbitals where any point lies in more than
+ * four entries.  Other handles, and those with a grid point in more than 128 projector
+ * supports, take the records.
  * When the projectors are too many for the block's coefficient row to fit in LDS beside the
  * default tile (in FP64 about 5000 on a grid 120 points wide) the handle is on the band pass
  * whatever its size, and is refused only when a grid point also lies in more than 128

@@ -1737,11 +1737,20 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
       // coefficients through a filter.  One filter application, records / band pass (us):
       // 24^3, 40 orbitals FP64 20.2 / 28.6; 72^3, one orbital 23.4 / 26.2; 30x33x28, 60 FP32
       // 53.9 / 32.4; 72^3, 16 FP64 87 / 79; 45^3 slab, 187 FP32 136 / 102; 64^3, 100 FP64 273 /
-      // 210; 40x52x90 slab, 300 FP64 560 / 406.
+      // 210; 40x52x90 slab, 300 FP64 560 / 406.  Where supports overlap the records leave the
+      // points in more than four entries to a scatter pass, and smaller blocks gain too: FP64 from
+      // 512 such points and 2^18 values (30x33x28, 8 orbitals 36.7 / 26.8, one H X 40.6 / 32.0;
+      // with 345 points, 24^3, 40 orbitals 29.7 / 28.8 and 30.2 / 33.1), filters of mixed handles
+      // from four orbitals (24^3, 4 orbitals 26.4 / 22.4, 40 35.0 / 26.2).
       // A mixed handle keeps the records for single applications, whose FP32 rounding the FP64
       // matrices of chefsi_project show, and takes the band pass in filters.
       const bool fits = hx_records_fit(h, h->hx_plan);
-      const bool large = max_ns >= 8 && nd * max_ns >= (int64_t)1 << 20;
+      int64_t scattered = 0;
+      for (int64_t i = 0; i < nd; ++i) scattered += h->pt_cnt[i + 1] - h->pt_cnt[i] > 4;
+      const bool many = max_ns >= 8 && nd * max_ns >= (int64_t)1 << 20;
+      const bool large = precision == CHEFSI_MIXED
+                             ? many || (max_ns >= 4 && scattered > 0)
+                             : many || (max_ns >= 8 && nd * max_ns >= (int64_t)1 << 18 && scattered >= 512);
       const bool both = fits && large && precision == CHEFSI_MIXED;
       std::future<BandTables> tables;
       if (both) tables = std::async([h] { return band_tables(h); });

@@ -23,11 +23,19 @@ def cs():
 
 
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
-@pytest.mark.parametrize("max_ns", [7, 8, 60])
-def test_start_route(cs, prec, max_ns):
-    """27 x 30 x 26 points: below and above 8 orbitals, below and above 2^20 values."""
-    print(f"start route {prec} max_ns {max_ns}", flush=True)
-    prob = inputs.small_problem(n=(27, 30, 26), h=(0.3, 0.3, 0.3), bc=(0, 0, 1), n_atoms=9, nproj_per_atom=4, seed=17)
+@pytest.mark.parametrize("n_atoms", [1, 4, 20])
+@pytest.mark.parametrize("max_ns", [3, 4, 7, 8, 13, 60])
+def test_start_route(cs, prec, max_ns, n_atoms):
+    """27 x 30 x 26 points: both sides of 4 and 8 orbitals, of 2^18 and 2^20 values, and of 0 and
+    512 points in more than four projector entries."""
+    print(f"start route {prec} max_ns {max_ns} atoms {n_atoms}", flush=True)
+    prob = inputs.small_problem(n=(27, 30, 26), h=(0.3, 0.3, 0.3), bc=(0, 0, 1), n_atoms=n_atoms, nproj_per_atom=4,
+                                seed=17)
+    entries = np.zeros(prob.nd, dtype=int)
+    for k in range(n_atoms):
+        np.add.at(entries, prob.supp_idx[prob.supp_ptr[k]:prob.supp_ptr[k + 1]], prob.nproj[k])
+    scattered = int((entries > 4).sum())
+    print(f"  points in more than four entries: {scattered}", flush=True)
     ns, degree = min(max_ns, 6), 7
     dt = "float64" if prec == "fp64" else "float32"
     p = cs.FP64 if prec == "fp64" else cs.MIXED
@@ -58,6 +66,10 @@ def test_start_route(cs, prec, max_ns):
         else:
             band = (y, f)
     large = max_ns >= 8 and prob.nd * max_ns >= 1 << 20
+    if prec == "mixed":
+        large = large or (max_ns >= 4 and scattered > 0)
+    else:
+        large = large or (max_ns >= 8 and prob.nd * max_ns >= 1 << 18 and scattered >= 512)
     # the handle as created: records when small, band pass when large, a mixed one in filters only
     assert np.array_equal(f0, band[1] if large else rec[1])
     assert np.array_equal(y0, band[0] if large and prec == "fp64" else rec[0])
