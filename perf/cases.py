@@ -60,10 +60,11 @@ def draw(rng):
     def log_int(lo, hi):
         return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
 
-    kind = rng.choice(['filter', 'apply', 'solve', 'step'])
+    kind = rng.choice(["apply", "solve", "lanczos", "filter", "filter", "eigh", "forces", "kpoint", "rotate", "step",
+                       "project"])
     if kind == "eigh":
         return {"kind": kind, "system": "cfg1", "ns": log_int(40, 1200)}
-    n = [rng.randint(24, 36) for _ in range(3)]
+    n = [rng.randint(24, 72) for _ in range(3)]
     slab = rng.random() < 0.5
     if slab:
         n[2] = rng.randint(n[2], 2 * n[2])
@@ -75,16 +76,16 @@ def draw(rng):
     if kind == "solve":
         c.update(ns=log_int(40, min(top, 120)), degree=rng.choice([16, 20, 24]), n_iter=rng.randint(2, 4), tuned=False)
     elif kind == "step":
-        c.update(ns=log_int(40, min(top, 70)), degree=rng.choice([16, 20, 24]), tuned=rng.random() < 0.5)
+        c.update(ns=log_int(40, top), degree=rng.choice([16, 20, 24]), tuned=rng.random() < 0.5)
     elif kind == "filter":
-        c.update(ns=log_int(40, min(top, 70)), degree=rng.choice([16, 20, 24]), precision=rng.choice(["fp64", "mixed"]),
+        c.update(ns=log_int(40, top), degree=rng.choice([16, 20, 24]), precision=rng.choice(["fp64", "mixed"]),
                  tuned=rng.random() < 0.5)
     elif kind == "apply":
-        c.update(ns=log_int(8, 40), precision=rng.choice(["fp64", "mixed"]), tuned=False)
+        c.update(ns=log_int(8, top), precision=rng.choice(["fp64", "mixed"]), tuned=False)
     elif kind == "project":
-        c.update(ns=log_int(40, min(top, 70)), tuned=False)
+        c.update(ns=log_int(40, top), tuned=False)
     else:  # forces, kpoint, rotate
-        c.update(ns=log_int(40, min(top, 70)))
+        c.update(ns=log_int(40, top))
     return c
 
 
@@ -471,7 +472,3 @@ def exact(case, seed):
         d, x = e.step(x, case["degree"], lo, cut, hi)
         lo, cut = float(d[0]), float(d[-1])
     return [d, lo, cut] if kind == "solve" else [d, None]  # an orbital's sign is free
-
-_all = listed
-def listed():
-    return _all()[:1]
