@@ -21,7 +21,7 @@ BUILD_DIR = os.path.join(HERE, "_build")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 SOURCES = ["hx_apply.hip", "nonlocal.hip", "gemm.hip", "gemm_bf16.hip", "lanczos.hip", "forces.hip", "kpoint.hip", "tridiag.hip",
-           "gram_f64.hip", "api.cpp"]
+           "gram_f64.hip", "cholesky.hip", "api.cpp"]
 
 COMMON_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

@@ -303,7 +303,7 @@ PanelPlan plan_panels(int64_t nd, int ns) {
 
 struct WsLayout {
   size_t bufB = 0, alpha = 0, hs = 0, ms = 0, d = 0, e = 0, sc = 0, info = 0, msg = 0, partial = 0, zsplit = 0,
-         panel = 0, panel_out = 0, band = 0, solver = 0, total = 0;
+         panel = 0, panel_out = 0, band = 0, chol = 0, solver = 0, total = 0;
   size_t bufB_bytes = 0, solver_bytes = 0, band_bytes = 0;
   GramPlan gram;
   BlasGram bgram;   // FP64 handles: Gram products of FP64 blocks
@@ -355,19 +355,21 @@ size_t solver_workspace(chefsi_handle* h, int ns) {
     BLAS_TRY(rocblas_stop_device_memory_size_query(h->blas, &sz));
     best = std::max(best, sz);
   };
-  query([&] { rocsolver_dpotrf(h->blas, rocblas_fill_upper, ns, nullptr, ns, nullptr); });
-  query([&] {
-    rocblas_dtrsm(h->blas, rocblas_side_left, rocblas_fill_upper, rocblas_operation_transpose,
-                  rocblas_diagonal_non_unit, ns, ns, &one, nullptr, ns, nullptr, ns);
-  });
-  query([&] {
-    rocblas_dtrsm(h->blas, rocblas_side_right, rocblas_fill_upper, rocblas_operation_none,
-                  rocblas_diagonal_non_unit, ns, ns, &one, nullptr, ns, nullptr, ns);
-  });
-  query([&] {
-    rocblas_dtrsm(h->blas, rocblas_side_left, rocblas_fill_upper, rocblas_operation_none,
-                  rocblas_diagonal_non_unit, ns, ns, &one, nullptr, ns, nullptr, ns);
-  });
+  if (ns > kCholMax) {
+    query([&] { rocsolver_dpotrf(h->blas, rocblas_fill_upper, ns, nullptr, ns, nullptr); });
+    query([&] {
+      rocblas_dtrsm(h->blas, rocblas_side_left, rocblas_fill_upper, rocblas_operation_transpose,
+                    rocblas_diagonal_non_unit, ns, ns, &one, nullptr, ns, nullptr, ns);
+    });
+    query([&] {
+      rocblas_dtrsm(h->blas, rocblas_side_right, rocblas_fill_upper, rocblas_operation_none,
+                    rocblas_diagonal_non_unit, ns, ns, &one, nullptr, ns, nullptr, ns);
+    });
+    query([&] {
+      rocblas_dtrsm(h->blas, rocblas_side_left, rocblas_fill_upper, rocblas_operation_none,
+                    rocblas_diagonal_non_unit, ns, ns, &one, nullptr, ns, nullptr, ns);
+    });
+  }
   if (own_tridiag(h, ns))
     query([&] { rocsolver_dstedc(h->blas, rocblas_evect_tridiagonal, ns, nullptr, nullptr, nullptr, ns, nullptr); });
   else
@@ -456,6 +458,8 @@ WsLayout layout(chefsi_handle* h, int ns) {
       off += align256(L.pan.panel_bytes);
     }
   }
+  L.chol = off;
+  off += align256(chol_scratch_bytes(ns));
   L.band = off;
   if (h->ws_band_slots > 0) L.band_bytes = band_partial_bytes(h, h->ws_band_slots, ns);
   off += align256(L.band_bytes);
@@ -959,7 +963,11 @@ void dense_factor(chefsi_handle* h, double* Hs, double* Ms, int ns, const WsLayo
   rocblas_int* info = at<rocblas_int>(ws, L.info);
   double* sc = at<double>(ws, L.sc);
   HIP_TRY(launch_pencil_scale(Hs, Ms, sc, ns, s));
-  BLAS_TRY(rocsolver_dpotrf(h->blas, rocblas_fill_upper, ns, Ms, ns, info));
+  // (rocSOLVER and rocBLAS above the sizes whose right-hand sides fit in LDS)
+  if (ns <= kCholMax)
+    HIP_TRY(launch_cholesky(Ms, ns, at<void>(ws, L.chol), info, s));
+  else
+    BLAS_TRY(rocsolver_dpotrf(h->blas, rocblas_fill_upper, ns, Ms, ns, info));
   ps.done();
 }
 
@@ -971,10 +979,15 @@ void dense_solve(chefsi_handle* h, double* Hs, double* Ms, double* D, int ns, co
   BLAS_TRY(rocblas_set_workspace(h->blas, at<void>(ws, L.solver), std::max<size_t>(L.solver_bytes, 256)));
   rocblas_int* info = at<rocblas_int>(ws, L.info);
   double* sc = at<double>(ws, L.sc);
-  BLAS_TRY(rocblas_dtrsm(h->blas, rocblas_side_left, rocblas_fill_upper, rocblas_operation_transpose,
-                         rocblas_diagonal_non_unit, ns, ns, &one, Ms, ns, Hs, ns));
-  BLAS_TRY(rocblas_dtrsm(h->blas, rocblas_side_right, rocblas_fill_upper, rocblas_operation_none,
-                         rocblas_diagonal_non_unit, ns, ns, &one, Ms, ns, Hs, ns));
+  if (ns <= kCholMax) {
+    // the partial products are dead here (at least ns^2 doubles)
+    HIP_TRY(launch_reduce_pencil(Ms, at<void>(ws, L.chol), ns, Hs, at<double>(ws, L.partial), info, s));
+  } else {
+    BLAS_TRY(rocblas_dtrsm(h->blas, rocblas_side_left, rocblas_fill_upper, rocblas_operation_transpose,
+                           rocblas_diagonal_non_unit, ns, ns, &one, Ms, ns, Hs, ns));
+    BLAS_TRY(rocblas_dtrsm(h->blas, rocblas_side_right, rocblas_fill_upper, rocblas_operation_none,
+                           rocblas_diagonal_non_unit, ns, ns, &one, Ms, ns, Hs, ns));
+  }
   double* W = Hs;  // eigenvectors of the reduced matrix
   if (own_tridiag(h, ns)) {
     // the partial products and the projector coefficients are dead here: eigenvectors of the
@@ -989,9 +1002,13 @@ void dense_solve(chefsi_handle* h, double* Hs, double* Ms, double* D, int ns, co
     BLAS_TRY(rocsolver_dsyevd(h->blas, rocblas_evect_original, rocblas_fill_upper, ns, Hs, ns, D,
                               at<double>(ws, L.e), info + 1));
   }
-  BLAS_TRY(rocblas_dtrsm(h->blas, rocblas_side_left, rocblas_fill_upper, rocblas_operation_none,
-                         rocblas_diagonal_non_unit, ns, ns, &one, Ms, ns, W, ns));
-  HIP_TRY(launch_row_scale(W, Hs, sc, ns, s));
+  if (ns <= kCholMax) {
+    HIP_TRY(launch_back_substitute(Ms, at<void>(ws, L.chol), ns, W, Hs, sc, info, s));
+  } else {
+    BLAS_TRY(rocblas_dtrsm(h->blas, rocblas_side_left, rocblas_fill_upper, rocblas_operation_none,
+                           rocblas_diagonal_non_unit, ns, ns, &one, Ms, ns, W, ns));
+    HIP_TRY(launch_row_scale(W, Hs, sc, ns, s));
+  }
   ps.done();
 }
 

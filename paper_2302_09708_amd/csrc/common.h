@@ -216,6 +216,20 @@ struct GramPlan {
   size_t partial_bytes = 0;
 };
 
+// Cholesky and triangular solves of the dense stage (cholesky.hip), n <= kCholMax (16 right-hand
+// sides in the LDS of a block).  launch_cholesky: A (ld n, upper triangle) <- U, *info = 0 or the
+// order of the first leading minor that is not positive (A is then partly overwritten); scratch
+// (chol_scratch_bytes) keeps the inverses of U's diagonal blocks for the solves.
+constexpr int kCholBlock = 64, kCholMax = 1216;
+size_t chol_scratch_bytes(int n);
+hipError_t launch_cholesky(double* A, int n, void* scratch, int* info, hipStream_t s);
+// H <- U^-T H U^-1 (H symmetric; tmp: n x n); like the next one, nothing where *info != 0
+hipError_t launch_reduce_pencil(const double* U, const void* scratch, int n, double* H, double* tmp, const int* info,
+                                hipStream_t s);
+// Z <- diag(sc) U^-1 W (Z may be W)
+hipError_t launch_back_substitute(const double* U, const void* scratch, int n, const double* W, double* Z,
+                                  const double* sc, const int* info, hipStream_t s);
+
 // Both FP64 Gram products of a projection at once (gram_f64.hip): t tiles of nf 16-column
 // fragments, t^2 units, each over `splits` chunks of `steps` 16-row steps.
 struct GramBothPlan {
