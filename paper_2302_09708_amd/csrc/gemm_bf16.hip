@@ -22,7 +22,11 @@
 //   stages a 128-column slice of Z through LDS and every wave gathers the MFMA B
 //   operand straight from X: lane l reads grid point p = l % 32 of 8 consecutive
 //   columns, so each load instruction covers 128 contiguous bytes of two columns and
-//   no transpose is needed.  Results leave as 128-byte rows of O.
+//   no transpose is needed.  Results leave as 128-byte rows of O.  A stage's 48 MFMA take
+//   1536 cycles of a SIMD; the vector work beside them has to stay below that (addresses
+//   formed per lane, single conversions and the copy of the next stage's values made it 1900,
+//   now 400), after which the power limit holds the clock near 1.6 GHz.  60x60x180, 1200
+//   orbitals: 6.6 -> 5.7 ms, 0.85 -> 0.98 PFLOP/s executed.
 #include "common.h"
 
 #include <algorithm>
@@ -51,20 +55,21 @@ __device__ __forceinline__ f32x16 mfma_bf16(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// x = hi + lo with hi = bf16(x), lo = bf16(x - hi), both round-to-nearest-even.
-__device__ __forceinline__ void split_bf16(float x, __bf16& hi, __bf16& lo) {
-  hi = (__bf16)x;
-  lo = (__bf16)(x - (float)hi);
-}
-
+// x = hi + lo with hi = bf16(x), lo = bf16(x - hi), both round-to-nearest-even; two values at a
+// time, so one conversion instruction makes two (a rotation stage: 96 instead of 128).
 __device__ __forceinline__ void split8(const float (&x)[8], bf16x8& hi, bf16x8& lo) {
+  u32x4 h4, l4;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    __bf16 h, l;
-    split_bf16(x[e], h, l);
-    hi[e] = h;
-    lo[e] = l;
+  for (int e = 0; e < 4; ++e) {
+    const f32x2 v = {x[2 * e], x[2 * e + 1]};
+    const unsigned h = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+    const f32x2 r = {x[2 * e] - __builtin_bit_cast(float, h << 16),
+                     x[2 * e + 1] - __builtin_bit_cast(float, h & 0xffff0000u)};
+    h4[e] = h;
+    l4[e] = __builtin_bit_cast(unsigned, __builtin_convertvector(r, bf16x2));
   }
+  hi = __builtin_bit_cast(bf16x8, h4);
+  lo = __builtin_bit_cast(bf16x8, l4);
 }
 
 __device__ __forceinline__ u32x4 as_u4(bf16x8 v) { return __builtin_bit_cast(u32x4, v); }
@@ -546,9 +551,33 @@ __global__ void zsplit_kernel(const double* __restrict__ Z, int ns, int ld, int 
 }
 
 // Lane (r32, g) of fragment f holds X[i][pcol[f]] for the 8 columns i = k0 + 16 s + 8 g + e
-// of each 16-wide K step s; columns past ns are clamped (Z is zero there).
+// of each 16-wide K step s.  A column's address is a scalar one (its first for g = 0, the base
+// of a buffer) and the lane's byte offset, the same for all of them (8 g columns and the point,
+// below 2^31 bytes up to kRotNarrow points), so a load costs no vector instructions.  In the
+// stage that passes ns, and on larger grids (WIDE), the lanes form 64-bit addresses, columns
+// past ns clamped (Z is zero there).
+constexpr int64_t kRotNarrow = ((int64_t)1 << 31) / 36;
+template <bool WIDE>
 __device__ __forceinline__ void rot_load_x(float (&xv)[2][2][8], const float* __restrict__ X, int64_t nd, int ns,
-                                           const int64_t (&pcol)[2], int k0, int g) {
+                                           const int64_t (&pcol)[2], const unsigned (&voff)[2], int k0, int g) {
+  if (!WIDE && k0 + kKS <= ns) {
+    const float* row = X + (int64_t)k0 * nd;
+    const int bytes = 36 * (int)nd;  // nine columns: a lane's own lies 0 or 8 further
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const __amdgpu_buffer_rsrc_t r =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(row), (short)0, bytes, 0x00020000);
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+          xv[s][f][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff[f], 0, 0));
+        row += nd;
+      }
+      row += 8 * nd;
+    }
+    return;
+  }
 #pragma unroll
   for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -575,7 +604,8 @@ __device__ __forceinline__ void rot_store_z(const u32x4 (&zr)[4], __bf16* sh, __
   *reinterpret_cast<u32x4*>(sl + 8) = zr[3];
 }
 
-__global__ __launch_bounds__(256) void rotate_bf16x3_kernel(const float* __restrict__ X, const __bf16* __restrict__ zh,
+template <bool WIDE>
+__global__ __launch_bounds__(256, 2) void rotate_bf16x3_kernel(const float* __restrict__ X, const __bf16* __restrict__ zh,
                                                             const __bf16* __restrict__ zl, float* __restrict__ O,
                                                             int64_t nd, int ns, int ld, int npt, int njt,
                                                             int per_xcd) {
@@ -601,8 +631,12 @@ __global__ __launch_bounds__(256) void rotate_bf16x3_kernel(const float* __restr
   // X gather: fragment f covers points p0 + 32 f + (lane % 32); K slot 8 (lane / 32) + e
   const int r32 = lane & 31, g = lane >> 5;
   int64_t pcol[2];
+  unsigned voff[2];
 #pragma unroll
-  for (int f = 0; f < 2; ++f) pcol[f] = min(p0 + 32 * f + r32, nd - 1);
+  for (int f = 0; f < 2; ++f) {
+    pcol[f] = min(p0 + 32 * f + r32, nd - 1);
+    voff[f] = WIDE ? 0u : ((unsigned)(8 * g) * (unsigned)nd + (unsigned)pcol[f]) * 4u;
+  }
 
   f32x16 acc[4][2];  // [j fragment][p fragment]
 #pragma unroll
@@ -613,20 +647,18 @@ __global__ __launch_bounds__(256) void rotate_bf16x3_kernel(const float* __restr
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
   const int nstage = ld / kKS;
-  float xc[2][2][8];  // [k16 step][p fragment][e]
+  float xa[2][2][8], xb[2][2][8];  // [k16 step][p fragment][e], a stage's and the next one's
   u32x4 zr[4];
   rot_load_z(zr, pzh, pzl, 0);
-  rot_load_x(xc, X, nd, ns, pcol, 0, g);
+  rot_load_x<WIDE>(xa, X, nd, ns, pcol, voff, 0, g);
   rot_store_z(zr, lds[0][0] + zoff, lds[0][1] + zoff);
   __syncthreads();
 
-  for (int t = 0; t < nstage; ++t) {
-    const int buf = t & 1;
+  auto stage = [&](int t, int buf, const float (&xc)[2][2][8], float (&xn)[2][2][8]) {
     const bool more = t + 1 < nstage;
-    float xn[2][2][8];
     if (more) {
       rot_load_z(zr, pzh, pzl, (t + 1) * kKS);
-      rot_load_x(xn, X, nd, ns, pcol, (t + 1) * kKS, g);
+      rot_load_x<WIDE>(xn, X, nd, ns, pcol, voff, (t + 1) * kKS, g);
     }
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -646,16 +678,12 @@ __global__ __launch_bounds__(256) void rotate_bf16x3_kernel(const float* __restr
         for (int f = 0; f < 2; ++f) acc[jf][f] = mfma_bf16(zhv, xh[f], acc[jf][f]);
       }
     }
-    if (more) {
-      rot_store_z(zr, lds[buf ^ 1][0] + zoff, lds[buf ^ 1][1] + zoff);
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int f = 0; f < 2; ++f)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) xc[s][f][e] = xn[s][f][e];
-    }
+    if (more) rot_store_z(zr, lds[buf ^ 1][0] + zoff, lds[buf ^ 1][1] + zoff);
     __syncthreads();
+  };
+  for (int t = 0; t < nstage; t += 2) {
+    stage(t, 0, xa, xb);
+    if (t + 1 < nstage) stage(t + 1, 1, xb, xa);
   }
 
   // D[j][p]: lane l, register v -> j = 8 (v / 4) + 4 (l / 32) + v % 4, p = l % 32
@@ -687,8 +715,11 @@ hipError_t launch_rotate_bf16x3(const float* X, const double* Z, void* zsplit, f
   const int njt = cols / kRotJ;
   const int64_t nb = (int64_t)npt * njt;
   const int per_xcd = (int)((nb + 7) / 8);
-  hipLaunchKernelGGL(rotate_bf16x3_kernel, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, s, X, zh, zl, O, nd, ns, ld,
-                     npt, njt, per_xcd);
+  const dim3 grid((unsigned)(per_xcd * 8));
+  if (nd <= kRotNarrow)
+    hipLaunchKernelGGL(rotate_bf16x3_kernel<false>, grid, dim3(256), 0, s, X, zh, zl, O, nd, ns, ld, npt, njt, per_xcd);
+  else
+    hipLaunchKernelGGL(rotate_bf16x3_kernel<true>, grid, dim3(256), 0, s, X, zh, zl, O, nd, ns, ld, npt, njt, per_xcd);
   return hipGetLastError();
 }
 
