@@ -1319,7 +1319,7 @@ void free_band_tables(chefsi_handle* h) {
 
 // Band-pass regions from a point-major projector table (cnt: nd + 1 entry offsets, col: the
 // projector column of every entry): regions of consecutive touched points (grid index
-// order), each closed before it would exceed kBandMaxPts points, kBandMaxSlots projectors or
+// order), each closed before it would exceed max_pts points, kBandMaxSlots projectors or
 // max_ent entries; each region lists its points with their entries, and its projector slots
 // (projector order) with their entries (point order); each projector lists its slots (region
 // order) for the reduction.  ent_src / gent_src name the table entry behind every scatter /
@@ -1329,7 +1329,7 @@ struct BandRegions {
       q_slot, ent_src, gent_src;
 };
 
-BandRegions band_regions(int64_t nd, const int* cnt, const int* col, int np_tot, int max_ent) {
+BandRegions band_regions(int64_t nd, const int* cnt, const int* col, int np_tot, int max_pts, int max_ent) {
   BandRegions R;
   const size_t nent = (size_t)cnt[nd];
   for (std::vector<int>* v : {&R.pt_idx, &R.pt_ent}) v->reserve(nent / 4 + 16);
@@ -1376,7 +1376,7 @@ BandRegions band_regions(int64_t nd, const int* cnt, const int* col, int np_tot,
     int fresh = 0;
     for (int e = cnt[i]; e < cnt[i + 1]; ++e) fresh += stamp[col[e]] != nreg;
     const int64_t open_pts = (int64_t)R.pt_idx.size() - first_pt;
-    if (open_pts > 0 && (open_pts + 1 > kBandMaxPts || (int)(R.ent_src.size() - first_ent) + n > max_ent ||
+    if (open_pts > 0 && (open_pts + 1 > max_pts || (int)(R.ent_src.size() - first_ent) + n > max_ent ||
                          (int)cols.size() + fresh > kBandMaxSlots))
       close_region();
     for (int e = cnt[i]; e < cnt[i + 1]; ++e) {
@@ -1410,7 +1410,7 @@ struct BandTables {
 
 BandTables band_tables(const chefsi_handle* h) {
   BandTables t;
-  t.r = band_regions(h->nd, h->pt_cnt.data(), h->pt_col.data(), h->np_tot, kBandMaxEnt);
+  t.r = band_regions(h->nd, h->pt_cnt.data(), h->pt_col.data(), h->np_tot, kBandMaxPts, kBandMaxEnt);
   t.ent_chi.resize(t.r.ent_src.size());
   t.gent_chi.resize(t.r.gent_src.size());
   for (size_t e = 0; e < t.ent_chi.size(); ++e) t.ent_chi[e] = h->pt_val[t.r.ent_src[e]];
@@ -2713,6 +2713,7 @@ struct chefsi_kpoint {
   double* gdv = nullptr;
   // band-pass tables (regions of touched points, complex chi~; the gather table conjugated)
   int nreg = 0;
+  int max_pts = 0, max_ent = 0, max_slots = 0;  // of the largest band-pass region
   int *reg_pt = nullptr, *pt_idx = nullptr, *pt_ent = nullptr, *ent_ls = nullptr, *reg_slot = nullptr,
       *slot_q = nullptr, *slot_ent = nullptr, *gent_loc = nullptr, *q_slot_ptr = nullptr, *q_slot = nullptr;
   double2 *ent_chi = nullptr, *gent_chi = nullptr, *partial = nullptr;
@@ -2869,6 +2870,9 @@ ZNbArgs zband_args(const chefsi_kpoint* h, double2* y, int ns, const double2* al
   b.alpha = alpha;
   b.sa = sa;
   b.partial = h->partial;
+  b.max_pts = h->max_pts;
+  b.max_ent = h->max_ent;
+  b.max_slots = h->max_slots;
   return b;
 }
 
@@ -3085,7 +3089,7 @@ int chefsi_kpoint_create(const chefsi_grid_t* grid, const double* veff_host, con
     h->veff = kupload(veff.data(), veff.size());
     if (h->np_tot > 0) {
       // band-pass regions of the touched points (the real path's tables with chi~ values)
-      const BandRegions R = band_regions(nd, cnt.data(), cols.data(), h->np_tot, kZBandMaxEnt);
+      const BandRegions R = band_regions(nd, cnt.data(), cols.data(), h->np_tot, kZBandThreads, kZBandMaxEnt);
       std::vector<double2> ent_chi(R.ent_src.size()), gent_chi(R.gent_src.size());
       for (size_t e = 0; e < ent_chi.size(); ++e) ent_chi[e] = vals[R.ent_src[e]];
       for (size_t e = 0; e < gent_chi.size(); ++e) {
@@ -3094,6 +3098,12 @@ int chefsi_kpoint_create(const chefsi_grid_t* grid, const double* veff_host, con
       }
       h->nreg = (int)R.reg_pt.size() - 1;
       h->n_pts = (int)R.pt_idx.size();
+      for (int i = 0; i < h->nreg; ++i) {
+        const int p0 = R.reg_pt[i], p1 = R.reg_pt[i + 1];
+        h->max_pts = std::max(h->max_pts, p1 - p0);
+        h->max_ent = std::max(h->max_ent, R.pt_ent[p1] - R.pt_ent[p0]);
+        h->max_slots = std::max(h->max_slots, R.reg_slot[i + 1] - R.reg_slot[i]);
+      }
       h->gdv = kupload(gdv.data(), gdv.size());
       h->reg_pt = kupload(R.reg_pt.data(), R.reg_pt.size());
       h->pt_idx = kupload(R.pt_idx.data(), R.pt_idx.size());

@@ -413,6 +413,7 @@ ZTiling plan_zhx(int nx, int ny, int nz, int ns, int radius);
 // complex band pass (the real band pass's regions and tables with chi~ values; the gather
 // table holds conj(chi~)); alpha projector-major: alpha[q * ns + v]
 constexpr int kZBandMaxEnt = 1024;  // projector entries of one region (complex tables in LDS)
+constexpr int kZBandThreads = 256;  // one thread per point: at most as many in a region
 struct ZNbArgs {
   double2* y;  // Nd x ns block (ld nd): scattered in place when scatter, read otherwise
   int64_t nd;
@@ -431,6 +432,7 @@ struct ZNbArgs {
   const double2* alpha;
   double sa;
   double2* partial;  // nslots x ns, slot major
+  int max_pts, max_ent, max_slots;     // of the largest region
   int ngroups, gpc, nchunks, per_xcd;  // set by the launcher
 };
 

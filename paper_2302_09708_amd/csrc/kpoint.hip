@@ -230,23 +230,31 @@ __global__ __launch_bounds__(kZMaxThreads) void zhx_kernel(ZHxArgs a, ZTiling t)
 
 // ---------------------------------------------------------------------------
 // zband: the complex counterpart of the real band pass.  One block per (region, run of
-// orbital groups of kZG orbitals), one thread per point; the region's entry tables sit in
-// LDS for the whole run; the next group's point values and staged coefficients are fetched
-// into registers while the current group is scattered and gathered.
+// orbital groups of G orbitals), one thread per point; the region's entry tables sit in LDS
+// for the whole run; the next group's point values and staged coefficients are fetched into
+// registers while the current group is scattered and gathered.
+//
+// What bounds it is how many values are in flight: a region is full at 1024 entries, about 230
+// points, so it has 256 threads with eight orbitals each (four where the tables leave no room
+// for two blocks on a CU), and a pass takes LDS only for what it does and for the largest region
+// there is: the scatter alone needs no point values.  72^3, 600 orbitals: the gather alone 0.94
+// -> 0.68 ms (512 threads and four orbitals before); the scatter alone stays at 0.95, the lines
+// its points share with others, both ways.  26x30x28, 60 atoms, 60 orbitals: H_k X 96 -> 79 us.
 // ---------------------------------------------------------------------------
-constexpr int kZG = 4;  // orbitals per group: 512 points x 4 x 16 B = 32 KB of LDS
-
-template <bool SCATTER>
-__global__ __launch_bounds__(kBandThreads) void zband_kernel(ZNbArgs a, int gather) {
-  constexpr int AJ = (kBandMaxSlots * kZG + kBandThreads - 1) / kBandThreads;
-  __shared__ double2 ys[kBandMaxPts * kZG];
-  __shared__ double2 as[kBandMaxSlots * kZG];
-  __shared__ double2 echi[kZBandMaxEnt];
-  __shared__ double2 gchi[kZBandMaxEnt];
-  __shared__ unsigned short els[kZBandMaxEnt];
-  __shared__ unsigned short gloc[kZBandMaxEnt];
-  __shared__ int sent[kBandMaxSlots + 1];
-  __shared__ int sq[kBandMaxSlots];
+template <bool SCATTER, bool GATHER, int G>
+__global__ __launch_bounds__(kZBandThreads) void zband_kernel(ZNbArgs a) {
+  constexpr int NT = kZBandThreads;
+  constexpr int AJ = (kBandMaxSlots * G + NT - 1) / NT;
+  extern __shared__ __align__(16) unsigned char zblds[];
+  // LDS: [point values][conj(chi~)] (gather) [coefficients][chi~] (scatter), the index tables
+  double2* ys = reinterpret_cast<double2*>(zblds);
+  double2* gchi = ys + (GATHER ? a.max_pts * G : 0);
+  double2* as = gchi + (GATHER ? a.max_ent : 0);
+  double2* echi = as + (SCATTER ? a.max_slots * G : 0);
+  int* sent = reinterpret_cast<int*>(echi + (SCATTER ? a.max_ent : 0));
+  int* sq = sent + (GATHER ? a.max_slots + 1 : 0);
+  unsigned short* els = reinterpret_cast<unsigned short*>(sq + (SCATTER ? a.max_slots : 0));
+  unsigned short* gloc = els + (SCATTER ? a.max_ent : 0);
   const int64_t logical = (int64_t)(blockIdx.x % 8) * a.per_xcd + blockIdx.x / 8;
   if (logical >= (int64_t)a.nreg * a.nchunks) return;
   const int reg = (int)(logical / a.nchunks);
@@ -259,21 +267,23 @@ __global__ __launch_bounds__(kBandThreads) void zband_kernel(ZNbArgs a, int gath
   const int eb = a.pt_ent[p0];
   if (SCATTER) {
     const int ne = a.pt_ent[p0 + np] - eb;
-    for (int e = tid; e < ne; e += kBandThreads) {
+    for (int e = tid; e < ne; e += NT) {
       echi[e] = a.ent_chi[eb + e];
       els[e] = (unsigned short)a.ent_ls[eb + e];
     }
   }
   const int gb = a.slot_ent[s0];
-  if (gather) {
+  if (GATHER) {
     const int ne = a.slot_ent[s0 + nslot] - gb;
-    for (int e = tid; e < ne; e += kBandThreads) {
+    for (int e = tid; e < ne; e += NT) {
       gchi[e] = a.gent_chi[gb + e];
       gloc[e] = (unsigned short)a.gent_loc[gb + e];
     }
   }
-  for (int sl = tid; sl <= nslot; sl += kBandThreads) sent[sl] = a.slot_ent[s0 + sl] - gb;
-  for (int sl = tid; sl < nslot; sl += kBandThreads) sq[sl] = a.slot_q[s0 + sl];
+  if (GATHER)
+    for (int sl = tid; sl <= nslot; sl += NT) sent[sl] = a.slot_ent[s0 + sl] - gb;
+  if (SCATTER)
+    for (int sl = tid; sl < nslot; sl += NT) sq[sl] = a.slot_q[s0 + sl];
   const bool own = tid < np;
   int64_t pi = 0;
   int e0 = 0, e1 = 0;
@@ -282,12 +292,12 @@ __global__ __launch_bounds__(kBandThreads) void zband_kernel(ZNbArgs a, int gath
     e0 = a.pt_ent[p0 + tid] - eb;
     e1 = a.pt_ent[p0 + tid + 1] - eb;
   }
-  const int nitem = nslot * kZG;
+  const int nitem = nslot * G;
   // register values as separate real and imaginary arrays (kept in registers)
-  auto load_y = [&](int g, double (&yr)[kZG], double (&yi)[kZG]) {
-    const int v0 = g * kZG;
+  auto load_y = [&](int g, double (&yr)[G], double (&yi)[G]) {
+    const int v0 = g * G;
 #pragma unroll
-    for (int u = 0; u < kZG; ++u) {
+    for (int u = 0; u < G; ++u) {
       double2 v = make_double2(0.0, 0.0);
       if (own && v0 + u < a.ns) v = a.y[(int64_t)(v0 + u) * a.nd + pi];
       yr[u] = v.x;
@@ -295,10 +305,10 @@ __global__ __launch_bounds__(kBandThreads) void zband_kernel(ZNbArgs a, int gath
     }
   };
   auto load_alpha = [&](int g, double (&ar)[AJ], double (&ai)[AJ]) {
-    const int v0 = g * kZG;
+    const int v0 = g * G;
 #pragma unroll
     for (int j = 0; j < AJ; ++j) {
-      const int it = tid + j * kBandThreads, ls = it / kZG, u = it % kZG;
+      const int it = tid + j * NT, ls = it / G, u = it % G;
       double2 v = make_double2(0.0, 0.0);
       if (it < nitem && v0 + u < a.ns) v = a.alpha[(int64_t)sq[ls] * a.ns + v0 + u];
       ar[j] = v.x;
@@ -308,12 +318,12 @@ __global__ __launch_bounds__(kBandThreads) void zband_kernel(ZNbArgs a, int gath
   auto stage_alpha = [&](const double (&ar)[AJ], const double (&ai)[AJ]) {
 #pragma unroll
     for (int j = 0; j < AJ; ++j) {
-      const int it = tid + j * kBandThreads;
+      const int it = tid + j * NT;
       if (it < nitem) as[it] = make_double2(ar[j], ai[j]);
     }
   };
   __syncthreads();  // slot columns staged
-  double ycr[kZG], yci[kZG], ynr[kZG], yni[kZG], anr[AJ], ani[AJ];
+  double ycr[G], yci[G], ynr[G], yni[G], anr[AJ], ani[AJ];
   load_y(g0, ycr, yci);
   if (SCATTER) {
     load_alpha(g0, anr, ani);
@@ -321,7 +331,7 @@ __global__ __launch_bounds__(kBandThreads) void zband_kernel(ZNbArgs a, int gath
   }
   __syncthreads();
   for (int g = g0; g < g1; ++g) {
-    const int v0 = g * kZG, nv = min(kZG, a.ns - v0);
+    const int v0 = g * G, nv = min(G, a.ns - v0);
     const bool more = g + 1 < g1;
     if (more) {
       load_y(g + 1, ynr, yni);
@@ -329,35 +339,37 @@ __global__ __launch_bounds__(kBandThreads) void zband_kernel(ZNbArgs a, int gath
     }
     if (own) {
       if (SCATTER) {
-        double tr[kZG], ti[kZG];
+        double tr[G], ti[G];
 #pragma unroll
-        for (int u = 0; u < kZG; ++u) tr[u] = ti[u] = 0.0;
+        for (int u = 0; u < G; ++u) tr[u] = ti[u] = 0.0;
         for (int e = e0; e < e1; ++e) {
           const double2 c = echi[e];
-          const double2* al = as + els[e] * kZG;
+          const double2* al = as + els[e] * G;
 #pragma unroll
-          for (int u = 0; u < kZG; ++u) {
+          for (int u = 0; u < G; ++u) {
             const double2 m = cmul(c, al[u]);
             tr[u] += m.x;
             ti[u] += m.y;
           }
         }
 #pragma unroll
-        for (int u = 0; u < kZG; ++u) {
+        for (int u = 0; u < G; ++u) {
           ycr[u] += a.sa * tr[u];
           yci[u] += a.sa * ti[u];
           if (u < nv) a.y[(int64_t)(v0 + u) * a.nd + pi] = make_double2(ycr[u], yci[u]);
         }
       }
+      if (GATHER) {
 #pragma unroll
-      for (int u = 0; u < kZG; ++u) ys[tid * kZG + u] = make_double2(ycr[u], yci[u]);
+        for (int u = 0; u < G; ++u) ys[tid * G + u] = make_double2(ycr[u], yci[u]);
+      }
     }
     __syncthreads();  // ys complete; the staged coefficients are no longer read
     if (SCATTER && more) stage_alpha(anr, ani);
-    if (gather) {
+    if (GATHER) {
       // slot partials: one thread per (slot, orbital), the slot's entries in index order
-      for (int it = tid; it < nitem; it += kBandThreads) {
-        const int sl = it / kZG, u = it % kZG;
+      for (int it = tid; it < nitem; it += NT) {
+        const int sl = it / G, u = it % G;
         if (u >= nv) continue;
         // four running sums over entries e = 4 m + c (independent LDS chains), added in a
         // fixed order
@@ -367,13 +379,13 @@ __global__ __launch_bounds__(kBandThreads) void zband_kernel(ZNbArgs a, int gath
         for (; e + 4 <= ee; e += 4) {
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            const double2 m = cmul(gchi[e + c], ys[gloc[e + c] * kZG + u]);
+            const double2 m = cmul(gchi[e + c], ys[gloc[e + c] * G + u]);
             sr[c] += m.x;
             si[c] += m.y;
           }
         }
         for (int c = 0; e < ee; ++e, ++c) {
-          const double2 m = cmul(gchi[e], ys[gloc[e] * kZG + u]);
+          const double2 m = cmul(gchi[e], ys[gloc[e] * G + u]);
           sr[c] += m.x;
           si[c] += m.y;
         }
@@ -383,7 +395,7 @@ __global__ __launch_bounds__(kBandThreads) void zband_kernel(ZNbArgs a, int gath
     }
     __syncthreads();  // ys free, next coefficients staged
 #pragma unroll
-    for (int u = 0; u < kZG; ++u) {
+    for (int u = 0; u < G; ++u) {
       ycr[u] = ynr[u];
       yci[u] = yni[u];
     }
@@ -489,22 +501,39 @@ hipError_t launch_zhx(const ZHxArgs& a, int ns, hipStream_t s) {
   }
 }
 
-hipError_t launch_zband(const ZNbArgs& a0, bool scatter, bool gather, hipStream_t s) {
-  if (a0.nreg <= 0 || a0.ns <= 0) return hipSuccess;
-  ZNbArgs a = a0;
-  a.ngroups = (a.ns + kZG - 1) / kZG;
+template <bool SCATTER, bool GATHER>
+static size_t zband_lds(const ZNbArgs& a, int g) {
+  size_t lds = 0;
+  if (GATHER) lds += ((size_t)a.max_pts * g + a.max_ent) * 16 + (a.max_slots + 1) * 4 + a.max_ent * 2;
+  if (SCATTER) lds += ((size_t)a.max_slots * g + a.max_ent) * 16 + a.max_slots * 4 + a.max_ent * 2;
+  return (lds + 15) / 16 * 16;
+}
+
+template <bool SCATTER, bool GATHER, int G>
+static hipError_t launch_zband_g(ZNbArgs a, hipStream_t s) {
+  a.ngroups = (a.ns + G - 1) / G;
   // runs of groups: about 4096 blocks in all, each run as long as that allows
   const int want = (int)std::min<int64_t>(a.ngroups, std::max<int64_t>(1, (4096 + a.nreg - 1) / a.nreg));
   a.gpc = (a.ngroups + want - 1) / want;
   a.nchunks = (a.ngroups + a.gpc - 1) / a.gpc;
   const int64_t nb = (int64_t)a.nreg * a.nchunks;
   a.per_xcd = (int)((nb + 7) / 8);
-  const dim3 grid((unsigned)(a.per_xcd * 8));
-  if (scatter)
-    hipLaunchKernelGGL(zband_kernel<true>, grid, dim3(kBandThreads), 0, s, a, gather ? 1 : 0);
-  else
-    hipLaunchKernelGGL(zband_kernel<false>, grid, dim3(kBandThreads), 0, s, a, 1);
+  hipLaunchKernelGGL((zband_kernel<SCATTER, GATHER, G>), dim3((unsigned)(a.per_xcd * 8)), dim3(kZBandThreads),
+                     (zband_lds<SCATTER, GATHER>(a, G)), s, a);
   return hipGetLastError();
+}
+
+template <bool SCATTER, bool GATHER>
+static hipError_t launch_zband_sg(const ZNbArgs& a, hipStream_t s) {
+  // four where eight leave no two blocks on a CU, or not four blocks for every CU in all
+  const bool eight = zband_lds<SCATTER, GATHER>(a, 8) <= 80 * 1024 && (int64_t)a.nreg * ((a.ns + 7) / 8) >= 1024;
+  return eight ? launch_zband_g<SCATTER, GATHER, 8>(a, s) : launch_zband_g<SCATTER, GATHER, 4>(a, s);
+}
+
+hipError_t launch_zband(const ZNbArgs& a, bool scatter, bool gather, hipStream_t s) {
+  if (a.nreg <= 0 || a.ns <= 0) return hipSuccess;
+  if (!scatter) return launch_zband_sg<false, true>(a, s);
+  return gather ? launch_zband_sg<true, true>(a, s) : launch_zband_sg<true, false>(a, s);
 }
 
 hipError_t launch_zband_reduce(const double2* partial, const int* q_slot_ptr, const int* q_slot, const double* gdv,
