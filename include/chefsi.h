@@ -216,8 +216,8 @@ int chefsi_spectral_bounds(const chefsi_handle_t* h, double* lam_lo, double* lam
  * v0: device vector of Nd elements in the handle's storage type (FP64 handle: double,
  * mixed handle: float), not modified; products with H and all sums in FP64, orbital
  * vectors stored in the storage type.  ws: caller-owned device memory of
- * chefsi_lanczos_workspace_bytes() bytes.  Synchronises the stream (the coefficients
- * steer the recurrence from the host).  alpha_host/beta_host (optional, `steps`
+ * chefsi_lanczos_workspace_bytes() bytes.  Synchronises the stream (once per 79 steps:
+ * the coefficients stay on the device in between).  alpha_host/beta_host (optional, `steps`
  * doubles each) receive the coefficients, zeros past an early stop (beta = 0).
  * Errors: ERR_INVALID_ARG (NULL pointers, steps outside 1..1000, zero or non-finite
  * v0), ERR_WORKSPACE, ERR_NONFINITE, ERR_HIP. */
