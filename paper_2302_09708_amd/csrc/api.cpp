@@ -1783,6 +1783,9 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
           if (!fits)
             throw Error{e.status,
                         "too many projectors for the stencil pass (alpha row does not fit in LDS), and " + e.msg};
+        } catch (const std::bad_alloc&) {
+          h->ws_band_slots = 0;
+          if (!fits) throw;
         }
       }
       build_hx_records(h, h->hx_plan);
@@ -1793,7 +1796,7 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
           h->ws_band_slots = std::max<int>(1, (int)t.r.slot_q.size());
           build_band_tables(h, t, true);
           h->filter_band = true;
-        } catch (const Error&) {  // a point in too many supports, or no memory: the records serve
+        } catch (...) {  // a point in too many supports, or no memory: the records serve
           h->ws_band_slots = 0;
           (void)hipGetLastError();
         }

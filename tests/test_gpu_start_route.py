@@ -76,6 +76,46 @@ def test_start_route(cs, prec, max_ns, n_atoms):
     h.close()
 
 
+def test_static_apply_on_the_band_pass(cs):
+    """100 orbitals: the call without a workspace forms the partial sums 64 orbitals at a time."""
+    print("start route static", flush=True)
+    prob = inputs.small_problem(n=(27, 30, 26), h=(0.3, 0.3, 0.3), bc=(0, 0, 1), n_atoms=20, nproj_per_atom=4, seed=17)
+    ns = 100
+    h = cs.Handle(prob, precision=cs.FP64, max_ns=ns)
+    X = torch.from_numpy(np.random.default_rng(6).standard_normal((ns, prob.nd))).cuda()
+    Y, Z = torch.zeros_like(X), torch.full_like(X, float("nan"))
+    h.chefsi_apply_h(X, Y, ns, cs.workspace(h, ns))
+    h.chefsi_apply_h_static(X, Z, ns)
+    torch.cuda.synchronize()
+    assert torch.equal(Y, Z)
+    h.close()
+
+
+def test_streams_share_nothing(cs):
+    """Filters of one FP64 handle on two streams, each with a workspace of its own: the band pass's
+    partial sums are the workspace's, so each block ends as it does alone."""
+    print("start route two streams", flush=True)
+    prob = inputs.small_problem(n=(27, 30, 26), h=(0.3, 0.3, 0.3), bc=(0, 0, 1), n_atoms=20, nproj_per_atom=4, seed=17)
+    ns, degree = 60, 12
+    lo, cut, hi = oc.spectral_bounds(prob)
+    h = cs.Handle(prob, precision=cs.FP64, max_ns=ns)
+    X = [torch.from_numpy(np.random.default_rng(k).standard_normal((ns, prob.nd))).cuda() for k in (1, 2)]
+    ws = [cs.workspace(h, ns) for _ in X]
+    alone = [x.clone() for x in X]
+    for a, w in zip(alone, ws):
+        h.chefsi_filter(a, ns, degree, lo, cut, hi, w)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in X]
+    both = [x.clone() for x in X]
+    torch.cuda.synchronize()
+    for b, w, s in zip(both, ws, streams):
+        h.chefsi_filter(b, ns, degree, lo, cut, hi, w, stream=s)
+    torch.cuda.synchronize()
+    for a, b in zip(alone, both):
+        assert torch.equal(a, b)
+    h.close()
+
+
 def test_runs_of_orbitals(cs):
     """More orbitals than the partial sums' buffer holds at once (256 MiB): the band pass goes by
     runs, and every orbital's result is that of a narrow handle."""
