@@ -16,8 +16,10 @@
 // The exchange carries its own validity: a double goes out as two 64-bit words of 32 payload
 // bits and the 32-bit number of the column, written and read with relaxed device-scope
 // atomics, so no fence, flag or cache maintenance is needed.  Slots alternate between two
-// sets: a workgroup writes a set again only after it has read the other one whole, which
-// needs every workgroup to be done with this one.
+// sets: a workgroup writes a set again only after it has read the other one whole.  That one
+// holds a slot from every workgroup that reads the first set (tridiag_exchange.h), so nobody
+// waits any more for what is written over; a workgroup without a row in the next column
+// publishes its last rows and leaves.
 // Measured (whole reduction / back transformation): n = 40 66 / 11 us, 130 0.35 / 0.04 ms,
 // 600 2.18 / 0.26 ms, 1200 6.25 / 0.84 ms; rocSOLVER's blocked reduction launches four to six
 // kernels a column: 9.0 / 1.2 ms at n = 600, 0.15 / 0.27 ms at n = 40.  Bound by a column's
@@ -26,6 +28,7 @@
 // backtransform_kernel: C <- Q C, a wave keeping two columns of C in registers, the
 // reflectors applied one after the other from LDS with the next ones already on the way.
 #include "common.h"
+#include "tridiag_exchange.h"
 
 #include <algorithm>
 
@@ -101,7 +104,8 @@ struct TdState {
   int n, groups, me, nrow, lane, wave, tid;
 };
 
-// Columns m1 down to m0 + 1, whose active rows and columns lie in the first AC chunks.
+// Columns m1 down to m0 + 1, whose active rows and columns lie in the first AC chunks.  False
+// when the workgroup is through: it has no row left, or a wait has failed.
 template <int NC, int AC>
 __device__ __forceinline__ bool td_columns(TdState<NC>& t, int m1, int m0) {
   constexpr int LD = 64 * NC;
@@ -109,7 +113,7 @@ __device__ __forceinline__ bool td_columns(TdState<NC>& t, int m1, int m0) {
   const int lane = t.lane, n = t.n;
   for (int m = m1; m > m0; --m) {
     const unsigned tag = (unsigned)(n - m);
-    const int set = tag & 1;
+    const int set = td_set(n, m);
     double* ps = t.pl + set * LD;
     double* as = t.al + set * LD;
     double* vs = t.vl + set * LD;
@@ -178,6 +182,7 @@ __device__ __forceinline__ bool td_columns(TdState<NC>& t, int m1, int m0) {
       }
     }
     if (t.groups > 1) {
+      if (!td_reads(t.me, m)) return false;
       // rows tid, tid + 512, ...: all of a thread's slots are asked for at once, and again
       // until every word carries this column's tag
       u32x4 w[RT][2];
@@ -256,14 +261,11 @@ __device__ __forceinline__ bool td_columns(TdState<NC>& t, int m1, int m0) {
 
 // The columns in stretches of shrinking row length: two chunks less each (three in long rows).
 template <int NC, int AC>
-__device__ __forceinline__ bool td_all(TdState<NC>& t, int m1) {
+__device__ __forceinline__ void td_all(TdState<NC>& t, int m1) {
   constexpr int NEXT = AC > 10 ? AC - 3 : (AC > 2 ? AC - 2 : 0);
   const int m0 = min(m1, 64 * NEXT);
-  if (!td_columns<NC, AC>(t, m1, m0)) return false;
-  if constexpr (NEXT > 0)
-    return td_all<NC, NEXT>(t, m0);
-  else
-    return true;
+  if (!td_columns<NC, AC>(t, m1, m0)) return;
+  if constexpr (NEXT > 0) td_all<NC, NEXT>(t, m0);
 }
 
 // NC: 64-wide chunks of a row (n <= 64 NC).  LDS: the workgroup's rows, then p, the next
@@ -314,9 +316,9 @@ __global__ __launch_bounds__(kTdThreads, 2) void tridiag_kernel(double* __restri
   t.alpha = A[n - 2 + (int64_t)(n - 1) * n];
   t.diag = A[n - 1 + (int64_t)(n - 1) * n];
   __syncthreads();
-  const bool ok = td_all<NC, NC>(t, n - 1);
+  td_all<NC, NC>(t, n - 1);
   if (t.me == 0 && t.tid == 0) D[0] = t.diag;
-  if (t.tid == 0 && (!ok || groups == 1)) *info = ok ? 0 : n + 1;
+  if (t.tid == 0 && (failed || groups == 1)) *info = failed ? n + 1 : 0;
 }
 
 // C <- Q C for the reflectors that tridiag_kernel left in A: column m holds v[0 .. m - 2],
