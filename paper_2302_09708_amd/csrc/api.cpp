@@ -1043,15 +1043,15 @@ void raise_info(chefsi_handle* h, const rocblas_int* info, int ns) {
     throw Error{CHEFSI_ERR_NOT_POSDEF, "Cholesky of the overlap matrix failed (leading minor " +
                                            std::to_string(info[0]) + ")"};
   }
-  if (info[1] > 0 || (own_tridiag(h, ns) && info[2] > 0)) {
-    h->last_info = info[1] > 0 ? info[1] : info[2];
+  if (info[1] > 0) {
+    h->last_info = info[1];
     throw Error{CHEFSI_ERR_EIG, "dense eigensolver did not converge"};
   }
 }
 
 void check_info(chefsi_handle* h, void* ws, const WsLayout& L, int ns, hipStream_t s) {
   rocblas_int* info = pinned_info(h);
-  HIP_TRY(hipMemcpyAsync(info, at<rocblas_int>(ws, L.info), 3 * sizeof(rocblas_int), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(info, at<rocblas_int>(ws, L.info), 2 * sizeof(rocblas_int), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   raise_info(h, info, ns);
 }
@@ -1106,7 +1106,7 @@ void ritz_to_host(chefsi_handle* h, const double* D, int ns, double* ritz_host, 
   double* d = h->pinned;
   rocblas_int* info = pinned_info(h);
   HIP_TRY(hipMemcpyAsync(d, D, (size_t)ns * 8, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(info, at<rocblas_int>(ws, L.info), 3 * sizeof(rocblas_int), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(info, at<rocblas_int>(ws, L.info), 2 * sizeof(rocblas_int), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   raise_info(h, info, ns);
   for (int i = 0; i < ns; ++i)

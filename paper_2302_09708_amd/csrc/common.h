@@ -270,11 +270,15 @@ hipError_t launch_copy_diag(const double* A, double* d, int ns, hipStream_t s);
 
 // Householder tridiagonalisation of the symmetric A (n x n, ld n, upper triangle read; its
 // columns receive the reflectors, D, E and tau the rest, as LAPACK's dsytrd leaves them with
-// uplo U) and C <- Q C.  tridiag_groups is 0 where n is outside the kernels' range; msg:
-// tridiag_msg_bytes(n) of scratch; info is set to n + 1 when the launch could not finish.
+// uplo U) and C <- Q C.  tridiag_groups is 0 where n is outside the kernels' range; msg and info:
+// tridiag_msg_bytes(n) of scratch and a word of it.  The lower triangle is read too where a wait
+// between workgroups ends unmet after max_polls looks (0.2 to 0.32 us each: about a second), and
+// one workgroup does the work again.
+constexpr unsigned kTdMaxPolls = 1u << 22;
 int tridiag_groups(int n);
 size_t tridiag_msg_bytes(int n);
-hipError_t launch_tridiag(double* A, int n, double* D, double* E, double* tau, void* msg, int* info, hipStream_t s);
+hipError_t launch_tridiag(double* A, int n, double* D, double* E, double* tau, void* msg, int* info, hipStream_t s,
+                          unsigned max_polls = kTdMaxPolls);
 hipError_t launch_backtransform(const double* A, const double* tau, int n, double* C, hipStream_t s);
 
 template <typename TX, typename TO>

@@ -20,6 +20,11 @@
 // holds a slot from every workgroup that reads the first set (tridiag_exchange.h), so nobody
 // waits any more for what is written over; a workgroup without a row in the next column
 // publishes its last rows and leaves.
+//   A cooperative launch has all its workgroups resident at once among the kernels of one
+// process.  Workgroups of another process' reduction may hold the compute units that some of
+// these need while they wait for each other, so the wait is bounded, and
+// tridiag_alone_kernel, one workgroup without an exchange, does the reduction again where it
+// was not met.
 // Measured (whole reduction / back transformation): n = 40 66 / 11 us, 130 0.35 / 0.04 ms,
 // 600 2.18 / 0.26 ms, 1200 6.25 / 0.84 ms; rocSOLVER's blocked reduction launches four to six
 // kernels a column: 9.0 / 1.2 ms at n = 600, 0.15 / 0.27 ms at n = 40.  Bound by a column's
@@ -44,7 +49,6 @@ constexpr int kTdMaxChunks = 22;        // 64-wide chunks of a row: n <= 1408
 constexpr int kBtThreads = 256;          // back transformation: two columns of C per wave
 constexpr int kBtWaves = kBtThreads / 64;
 constexpr int kBtRefl = 4;
-constexpr unsigned kTdMaxPolls = 1u << 24;  // a few seconds: ends a wait that cannot be met
 
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double dpp_add(double x) {
@@ -100,6 +104,7 @@ struct TdState {
   double *A, *D, *E, *tau;
   unsigned long long* msg;
   __amdgpu_buffer_rsrc_t rmsg;
+  unsigned max_polls;
   int* failed;
   int n, groups, me, nrow, lane, wave, tid;
 };
@@ -204,7 +209,7 @@ __device__ __forceinline__ bool td_columns(TdState<NC>& t, int m1, int m0) {
         for (int i = 0; i < RT; ++i)
           if (t.tid + i * kTdThreads < m)
             all = all && w[i][0][1] == tag && w[i][0][3] == tag && w[i][1][1] == tag && w[i][1][3] == tag;
-      } while (!all && ++polls < kTdMaxPolls);
+      } while (!all && ++polls < t.max_polls);
       if (!all) *t.failed = 1;
 #pragma unroll
       for (int i = 0; i < RT; ++i) {
@@ -275,7 +280,7 @@ __global__ __launch_bounds__(kTdThreads, 2) void tridiag_kernel(double* __restri
                                                                 double* __restrict__ D, double* __restrict__ E,
                                                                 double* __restrict__ tau_out,
                                                                 unsigned long long* __restrict__ msg,
-                                                                int* __restrict__ info) {
+                                                                int* __restrict__ info, unsigned max_polls) {
   extern __shared__ __align__(16) double td_lds[];
   __shared__ int failed;
   constexpr int LD = 64 * NC;
@@ -298,6 +303,7 @@ __global__ __launch_bounds__(kTdThreads, 2) void tridiag_kernel(double* __restri
   t.tau = tau_out;
   t.msg = msg;
   t.rmsg = __builtin_amdgcn_make_buffer_rsrc(msg, (short)0, groups > 1 ? 2 * n * 32 : 0, 0x00020000);
+  t.max_polls = max_polls;
   t.failed = &failed;
   if (t.tid == 0) failed = 0;
   for (int i = t.tid; i < 6 * LD; i += kTdThreads) t.pl[i] = 0.0;
@@ -318,7 +324,81 @@ __global__ __launch_bounds__(kTdThreads, 2) void tridiag_kernel(double* __restri
   __syncthreads();
   td_all<NC, NC>(t, n - 1);
   if (t.me == 0 && t.tid == 0) D[0] = t.diag;
-  if (t.tid == 0 && (failed || groups == 1)) *info = failed ? n + 1 : 0;
+  if (t.tid == 0 && failed) *info = n + 1;
+}
+
+// The same results from one workgroup, with A in memory: for a launch above that could not
+// finish (*info != 0) or was not possible (always).  What that launch wrote to A are reflectors
+// above the first superdiagonal, so the lower triangle is still whole; its values are those of
+// the upper one up to the rounding of the products that made them.  Row j of the symmetric
+// matrix is column j of A.  Two passes over the active block a column: n = 130 0.7 ms, 600 29 ms,
+// 1408 530 ms (the exchange: 0.35, 2.2, 8).
+constexpr int kTaThreads = 1024;
+constexpr int kTaWaves = kTaThreads / 64;
+
+__global__ __launch_bounds__(kTaThreads) void tridiag_alone_kernel(double* A, int n, double* __restrict__ D,
+                                                                   double* __restrict__ E, double* __restrict__ tau_out,
+                                                                   int* info, int always) {
+  __shared__ double v[64 * kTdMaxChunks], w[64 * kTdMaxChunks], part[kTaWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (!always && *info == 0) return;
+  auto block_total = [&](double x) {
+    x = wave_total(x);
+    __syncthreads();  // part may still be read from the sum before
+    if (lane == 0) part[wave] = x;
+    __syncthreads();
+    double s = part[0];
+    for (int i = 1; i < kTaWaves; ++i) s += part[i];
+    return s;
+  };
+  for (int j = wave; j < n; j += kTaWaves)
+    for (int k = lane; k < j; k += 64) A[k + (int64_t)j * n] = A[j + (int64_t)k * n];
+  __syncthreads();
+  for (int m = n - 1; m > 0; --m) {
+    double* col = A + (int64_t)m * n;
+    double xx = 0.0;
+    for (int k = tid; k < m - 1; k += kTaThreads) xx = fma(col[k], col[k], xx);
+    xx = block_total(xx);
+    const double alpha = col[m - 1];
+    double beta = alpha, tau = 0.0, scale = 0.0;
+    if (xx != 0.0) {
+      beta = -copysign(sqrt(fma(alpha, alpha, xx)), alpha);
+      tau = (beta - alpha) / beta;
+      scale = 1.0 / (alpha - beta);
+    }
+    for (int k = tid; k < m; k += kTaThreads) v[k] = k < m - 1 ? col[k] * scale : 1.0;
+    __syncthreads();
+    for (int j = wave; j < m; j += kTaWaves) {
+      double p = 0.0;
+      for (int k = lane; k < m; k += 64) p = fma(A[k + (int64_t)j * n], v[k], p);
+      p = wave_total(p);
+      if (lane == 0) w[j] = p;
+    }
+    __syncthreads();
+    double vp = 0.0;
+    for (int k = tid; k < m; k += kTaThreads) vp = fma(v[k], w[k], vp);
+    const double h = 0.5 * tau * tau * block_total(vp);
+    for (int k = tid; k < m; k += kTaThreads) {
+      w[k] = td_w(tau, w[k], h, v[k]);
+      if (k < m - 1) col[k] = v[k];
+    }
+    if (tid == 0) {
+      D[m] = col[m];
+      E[m - 1] = beta;
+      tau_out[m - 1] = tau;
+    }
+    __syncthreads();
+    for (int j = wave; j < m; j += kTaWaves)
+      for (int k = lane; k < m; k += 64) {
+        double* a = A + k + (int64_t)j * n;
+        *a = fma(-w[j], v[k], fma(-v[j], w[k], *a));
+      }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    D[0] = A[0];
+    *info = 0;
+  }
 }
 
 // C <- Q C for the reflectors that tridiag_kernel left in A: column m holds v[0 .. m - 2],
@@ -403,11 +483,12 @@ size_t tridiag_lds(int n, int groups) {
 
 template <int NC>
 hipError_t launch_td(double* A, int n, int groups, double* D, double* E, double* tau, void* msg, int* info,
-                     hipStream_t s) {
+                     hipStream_t s, unsigned max_polls) {
   unsigned long long* m = static_cast<unsigned long long*>(msg);
   const size_t lds = tridiag_lds(n, groups);
   if (groups == 1) {
-    hipLaunchKernelGGL(tridiag_kernel<NC>, dim3(1), dim3(kTdThreads), lds, s, A, n, groups, D, E, tau, m, info);
+    hipLaunchKernelGGL(tridiag_kernel<NC>, dim3(1), dim3(kTdThreads), lds, s, A, n, groups, D, E, tau, m, info,
+                       max_polls);
     return hipGetLastError();
   }
   const int words = 2 * n * 4;
@@ -415,9 +496,14 @@ hipError_t launch_td(double* A, int n, int groups, double* D, double* E, double*
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // the workgroups wait for each other: a cooperative launch, so all of them are resident
-  void* args[] = {&A, &n, &groups, &D, &E, &tau, &m, &info};
-  return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&tridiag_kernel<NC>), dim3(groups),
-                                    dim3(kTdThreads), args, (unsigned)lds, s);
+  void* args[] = {&A, &n, &groups, &D, &E, &tau, &m, &info, &max_polls};
+  e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&tridiag_kernel<NC>), dim3(groups), dim3(kTdThreads),
+                                 args, (unsigned)lds, s);
+  const int refused = e == hipErrorCooperativeLaunchTooLarge;  // fewer compute units than the device reports
+  if (refused) (void)hipGetLastError();
+  if (e != hipSuccess && !refused) return e;
+  hipLaunchKernelGGL(tridiag_alone_kernel, dim3(1), dim3(kTaThreads), 0, s, A, n, D, E, tau, info, refused);
+  return hipGetLastError();
 }
 
 template <int NC>
@@ -444,19 +530,20 @@ int tridiag_groups(int n) {
 
 size_t tridiag_msg_bytes(int n) { return (size_t)2 * n * 4 * sizeof(unsigned long long); }
 
-hipError_t launch_tridiag(double* A, int n, double* D, double* E, double* tau, void* msg, int* info, hipStream_t s) {
+hipError_t launch_tridiag(double* A, int n, double* D, double* E, double* tau, void* msg, int* info, hipStream_t s,
+                          unsigned max_polls) {
   const int g = tridiag_groups(n);
   if (g == 0) return hipErrorInvalidValue;
   switch (chunks_of(n)) {
-    case 2: return launch_td<2>(A, n, g, D, E, tau, msg, info, s);
-    case 4: return launch_td<4>(A, n, g, D, E, tau, msg, info, s);
-    case 6: return launch_td<6>(A, n, g, D, E, tau, msg, info, s);
-    case 8: return launch_td<8>(A, n, g, D, E, tau, msg, info, s);
-    case 10: return launch_td<10>(A, n, g, D, E, tau, msg, info, s);
-    case 13: return launch_td<13>(A, n, g, D, E, tau, msg, info, s);
-    case 16: return launch_td<16>(A, n, g, D, E, tau, msg, info, s);
-    case 19: return launch_td<19>(A, n, g, D, E, tau, msg, info, s);
-    case kTdMaxChunks: return launch_td<kTdMaxChunks>(A, n, g, D, E, tau, msg, info, s);
+    case 2: return launch_td<2>(A, n, g, D, E, tau, msg, info, s, max_polls);
+    case 4: return launch_td<4>(A, n, g, D, E, tau, msg, info, s, max_polls);
+    case 6: return launch_td<6>(A, n, g, D, E, tau, msg, info, s, max_polls);
+    case 8: return launch_td<8>(A, n, g, D, E, tau, msg, info, s, max_polls);
+    case 10: return launch_td<10>(A, n, g, D, E, tau, msg, info, s, max_polls);
+    case 13: return launch_td<13>(A, n, g, D, E, tau, msg, info, s, max_polls);
+    case 16: return launch_td<16>(A, n, g, D, E, tau, msg, info, s, max_polls);
+    case 19: return launch_td<19>(A, n, g, D, E, tau, msg, info, s, max_polls);
+    case kTdMaxChunks: return launch_td<kTdMaxChunks>(A, n, g, D, E, tau, msg, info, s, max_polls);
     default: return hipErrorInvalidValue;
   }
 }
