@@ -429,16 +429,32 @@ HxPlan plan_hx(int nx, int ny, int nz, int ns, int radius, int elem_bytes, int p
       }
     }
   }
-  // z chunks.  With 512 or more (tile, orbital) pairs: enough blocks to fill 256 CUs several
-  // times over, chunks no thinner than 2r planes (a chunk fetches 2r planes beside its own).
-  // With fewer the march itself is what takes the time (about 0.8 us a plane with one or two
-  // blocks on a CU), so chunks go down to 4 planes: 24^3, 40 orbitals FP64 at 12 / 4 planes
-  // 17.8 / 14.1 us, 72^3, one orbital 20.5 / 12.6 (2 planes 13.1, 1 18.9), 16 orbitals at 12 /
-  // 8 planes 64.7 / 64.0 (4 planes 75.5).
+  // z chunks: enough blocks to fill 256 CUs several times over, chunks no thinner than 2r planes
+  // (a chunk fetches 2r planes beside its own).  With fewer than 512 (tile, orbital) pairs a
+  // launch takes as long as the compute unit with most blocks: a block marches its planes and
+  // takes about two planes' time to start, and ten waves keep a unit busy, so more of them only
+  // share it.  Where a thickness of 3 to 24 planes makes (planes + 2) max(1, waves / 10) at
+  // least 7 % smaller it is taken.  H X (records) against the first rule alone, 169 cases of
+  // 24^3 to 120^3 grids, 1 to 64 orbitals, FP64 and FP32: 12.4 % less time in the geometric
+  // mean (with the best of eleven thicknesses in each case 13.2 %), none more than 1.5 %
+  // slower; 24^3, 40 orbitals FP64 17.8 -> 14.1 us, 72^3, one orbital 23.0 -> 15.9, 120^3, one
+  // orbital 66.9 -> 61.7 (in chunks of 4 planes 78).
   const int64_t xyblocks = (int64_t)best.nty * ns;
-  const int want = xyblocks >= 512 ? 2048 : 1536, thinnest = xyblocks >= 512 ? std::max(1, 2 * radius) : 4;
-  int nzc = (int)std::max<int64_t>(1, (want + xyblocks - 1) / xyblocks);
-  nzc = std::min(nzc, std::max(1, nz / thinnest));
+  int nzc = (int)std::max<int64_t>(1, (2048 + xyblocks - 1) / xyblocks);
+  nzc = std::min(nzc, std::max(1, nz / std::max(1, 2 * radius)));
+  if (xyblocks < 512) {
+    auto time = [&](int n) {
+      const int zc = (nz + n - 1) / n;
+      const int64_t per_cu = (xyblocks * ((nz + zc - 1) / zc) + 255) / 256;
+      return (zc + 2) * std::max(1.0, (double)(per_cu * (best.threads / 64)) / 10.0);
+    };
+    double least = 0.93 * time(nzc);
+    for (int n = (nz + 23) / 24; n <= nz / 3; ++n)
+      if (time(n) < least) {
+        least = time(n);
+        nzc = n;
+      }
+  }
   best.zc = (nz + nzc - 1) / nzc;
   best.nzc = (nz + best.zc - 1) / best.zc;
   return best;
