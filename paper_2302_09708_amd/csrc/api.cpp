@@ -40,6 +40,13 @@ struct Error {
   std::string msg;
 };
 
+// True where an allocation (or the copy into it) failed; the error is not left for the next
+// launch to report.
+bool no_memory(hipError_t e) {
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e != hipSuccess;
+}
+
 #define HIP_TRY(expr)                                                                         \
   do {                                                                                        \
     hipError_t e_ = (expr);                                                                   \
@@ -112,7 +119,29 @@ void* scratch_address(int dev) {
 }  // namespace
 
 
-struct chefsi_handle {
+// Band-pass tables on the device (built while rec_max == 0 or filter_band).
+struct BandDevice {
+  int nb_reg = 0, nb_pts = 0, nb_slots = 0;
+  int* nb_reg_pt = nullptr;
+  int* nb_pt_idx = nullptr;
+  int* nb_pt_ent = nullptr;
+  int* nb_ent_ls = nullptr;
+  int* nb_slot_q = nullptr;
+  double* nb_ent_chi64 = nullptr;
+  float* nb_ent_chi32 = nullptr;
+  int* nb_reg_slot = nullptr;
+  int* nb_slot_ent = nullptr;
+  int* nb_gent_loc = nullptr;
+  double* nb_gent_chi64 = nullptr;
+  float* nb_gent_chi32 = nullptr;
+  int* nb_q_slot_ptr = nullptr;
+  int* nb_q_slot = nullptr;
+  void* nb_partial = nullptr;     // nb_slots x (a run of orbitals) values
+  size_t nb_partial_bytes = 0;
+  size_t nb_bytes = 0;  // of all of them
+};
+
+struct chefsi_handle : BandDevice {
   int device = 0;
   int cus = 0;              // compute units of the device
   size_t device_bytes = 0;  // sum of the handle's own device arrays
@@ -171,28 +200,9 @@ struct chefsi_handle {
   // a mixed handle as created: filters take the band pass (FP32 tables only) beside the records
   // that single applications use
   bool filter_band = false;
-  // band-pass tables (built while rec_max == 0 or filter_band)
-  int nb_reg = 0, nb_pts = 0, nb_slots = 0;
-  int* nb_reg_pt = nullptr;
-  int* nb_pt_idx = nullptr;
-  int* nb_pt_ent = nullptr;
-  int* nb_ent_ls = nullptr;
-  int* nb_slot_q = nullptr;
-  double* nb_ent_chi64 = nullptr;
-  float* nb_ent_chi32 = nullptr;
-  int* nb_reg_slot = nullptr;
-  int* nb_slot_ent = nullptr;
-  int* nb_gent_loc = nullptr;
-  double* nb_gent_chi64 = nullptr;
-  float* nb_gent_chi32 = nullptr;
-  int* nb_q_slot_ptr = nullptr;
-  int* nb_q_slot = nullptr;
-  void* nb_partial = nullptr;     // nb_slots x (a run of orbitals) values
-  size_t nb_partial_bytes = 0;
   // slots of a handle that started on the band pass (0: it did not): its workspaces carry the
   // partials, nb_partial serves only the calls without one
   int ws_band_slots = 0;
-  size_t nb_bytes = 0;
 
   rocblas_handle blas = nullptr;
   std::map<int, size_t> solver_ws_cache;
@@ -657,6 +667,7 @@ NbArgs<TY, TC> band_args(const chefsi_handle* h, TY* y, int ns, const TC* alpha,
 template <typename TY, typename TC>
 void band_alpha(chefsi_handle* h, TY* y, int ns, TC* alpha, const TC* gdv, bool scatter, double sa,
                 bool want_alpha, hipStream_t s, BandScratch bs) {
+  if (h->nb_q_slot_ptr == nullptr) throw Error{CHEFSI_ERR_HIP, "the handle has no band-pass tables"};
   ProfScope ps(h, P_NL, s);
   int run = ns;
   if (want_alpha)
@@ -1204,11 +1215,12 @@ template <typename T>
 T* upload(chefsi_handle* h, const T* src, size_t n) {
   T* d = nullptr;
   if (n == 0) return nullptr;
+  if (no_memory(hipMalloc(&d, n * sizeof(T)))) throw Error{CHEFSI_ERR_OOM, "device allocation failed"};
   h->device_bytes += n * sizeof(T);
-  if (hipMalloc(&d, n * sizeof(T)) != hipSuccess) throw Error{CHEFSI_ERR_OOM, "device allocation failed"};
   hipError_t e = hipMemcpy(d, src, n * sizeof(T), hipMemcpyHostToDevice);
-  if (e != hipSuccess) {
+  if (no_memory(e)) {
     (void)hipFree(d);
+    h->device_bytes -= n * sizeof(T);
     throw Error{CHEFSI_ERR_HIP, std::string("upload: ") + hipGetErrorString(e)};
   }
   return d;
@@ -1277,6 +1289,7 @@ void build_hx_records(chefsi_handle* h, const HxPlan& hp) {
   int* nptr = nullptr;
   HxRec<double>* n64 = nullptr;
   HxRec<float>* n32 = nullptr;
+  const size_t before = h->device_bytes;
   try {
     if (nrec > 0) {
       nptr = upload(h, rptr.data(), rptr.size());
@@ -1286,6 +1299,7 @@ void build_hx_records(chefsi_handle* h, const HxPlan& hp) {
   } catch (...) {
     for (void* q : {(void*)nptr, (void*)n64, (void*)n32})
       if (q) (void)hipFree(q);
+    h->device_bytes = before;
     throw;
   }
   for (void* q : {(void*)h->hx_rec_ptr, (void*)h->hx_rec64, (void*)h->hx_rec32})
@@ -1301,20 +1315,18 @@ void build_hx_records(chefsi_handle* h, const HxPlan& hp) {
   h->hx_plan = hp;
 }
 
-void free_band_tables(chefsi_handle* h) {
-  void* ptrs[] = {h->nb_reg_pt,   h->nb_pt_idx,     h->nb_pt_ent,     h->nb_ent_ls,   h->nb_ent_chi64,
-                  h->nb_ent_chi32, h->nb_reg_slot,  h->nb_slot_ent,   h->nb_gent_loc, h->nb_gent_chi64,
-                  h->nb_gent_chi32, h->nb_q_slot_ptr, h->nb_q_slot,   h->nb_partial, h->nb_slot_q};
+void free_band(const BandDevice& b) {
+  void* ptrs[] = {b.nb_reg_pt,   b.nb_pt_idx,     b.nb_pt_ent,     b.nb_ent_ls,   b.nb_ent_chi64,
+                  b.nb_ent_chi32, b.nb_reg_slot,  b.nb_slot_ent,   b.nb_gent_loc, b.nb_gent_chi64,
+                  b.nb_gent_chi32, b.nb_q_slot_ptr, b.nb_q_slot,   b.nb_partial, b.nb_slot_q};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
-  h->nb_reg_pt = h->nb_pt_idx = h->nb_pt_ent = h->nb_ent_ls = h->nb_slot_q = nullptr;
-  h->nb_reg_slot = h->nb_slot_ent = h->nb_gent_loc = h->nb_q_slot_ptr = h->nb_q_slot = nullptr;
-  h->nb_ent_chi64 = h->nb_gent_chi64 = nullptr;
-  h->nb_ent_chi32 = h->nb_gent_chi32 = nullptr;
-  h->nb_partial = nullptr;
+}
+
+void free_band_tables(chefsi_handle* h) {
+  free_band(*h);
   h->device_bytes -= h->nb_bytes;
-  h->nb_bytes = 0;
-  h->nb_reg = h->nb_pts = h->nb_slots = 0;
+  static_cast<BandDevice&>(*h) = BandDevice();
 }
 
 // Band-pass regions from a point-major projector table (cnt: nd + 1 entry offsets, col: the
@@ -1418,10 +1430,12 @@ BandTables band_tables(const chefsi_handle* h) {
   return t;
 }
 
+// The handle's current tables are replaced, or kept where the new ones cannot be built.
 void build_band_tables(chefsi_handle* h, const BandTables& t, bool filter_only) {
-  free_band_tables(h);
   const BandRegions& R = t.r;
   const size_t before = h->device_bytes;
+  const BandDevice old = *h;
+  static_cast<BandDevice&>(*h) = BandDevice();
   try {
     h->nb_reg_pt = upload(h, R.reg_pt.data(), R.reg_pt.size());
     h->nb_pt_idx = upload(h, R.pt_idx.data(), R.pt_idx.size());
@@ -1444,18 +1458,21 @@ void build_band_tables(chefsi_handle* h, const BandTables& t, bool filter_only) 
     }
     const int own_ns = h->ws_band_slots > 0 ? std::min<int>(h->max_ns, kBandMinOrbitals) : h->max_ns;
     const size_t pbytes = band_partial_bytes(h, (int)R.slot_q.size(), own_ns);
-    if (hipMalloc(&h->nb_partial, pbytes) != hipSuccess) {
+    if (no_memory(hipMalloc(&h->nb_partial, pbytes))) {
       h->nb_partial = nullptr;
       throw Error{CHEFSI_ERR_OOM, "device allocation failed (band-pass partial sums)"};
     }
     h->nb_partial_bytes = pbytes;
     h->device_bytes += pbytes;
   } catch (...) {
-    h->nb_bytes = h->device_bytes - before;
-    free_band_tables(h);
+    free_band(*h);
+    static_cast<BandDevice&>(*h) = old;
+    h->device_bytes = before;
     throw;
   }
+  free_band(old);
   h->nb_bytes = h->device_bytes - before;
+  h->device_bytes -= old.nb_bytes;
   h->nb_reg = (int)R.reg_pt.size() - 1;
   h->nb_pts = (int)R.pt_idx.size();
   h->nb_slots = (int)R.slot_q.size();
@@ -1487,6 +1504,7 @@ void build_scatter_records(chefsi_handle* h) {
   int* col = nullptr;
   double* v64 = nullptr;
   float* v32 = nullptr;
+  const size_t before = h->device_bytes;
   try {
     if (!recs.empty()) {
       rec = upload(h, recs.data(), recs.size());
@@ -1498,6 +1516,7 @@ void build_scatter_records(chefsi_handle* h) {
   } catch (...) {
     for (void* q : {(void*)rec, (void*)col, (void*)v64, (void*)v32})
       if (q) (void)hipFree(q);
+    h->device_bytes = before;
     throw;
   }
   for (void* q : {(void*)h->rec, (void*)h->ent_col, (void*)h->ent_val64, (void*)h->ent_val32})
@@ -1699,7 +1718,7 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
     check(h->hx_plan.ok, "no stencil tiling fits this grid");
 
     const size_t pinned_doubles = std::max({(size_t)max_ns + 8, (size_t)h->n_atoms * 10, (size_t)kVecBlocks});
-    if (hipHostMalloc((void**)&h->pinned, pinned_doubles * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    if (no_memory(hipHostMalloc((void**)&h->pinned, pinned_doubles * sizeof(double), hipHostMallocDefault))) {
       h->pinned = nullptr;
       throw Error{CHEFSI_ERR_OOM, "pinned host allocation failed"};
     }
@@ -1777,9 +1796,8 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
           h->ws_band_slots = std::max<int>(1, (int)t.r.slot_q.size());
           build_band_tables(h, t, false);
           h->rec_max = 0;
-        } catch (const Error& e) {
+        } catch (const Error& e) {  // a point in too many supports, or no memory: the records serve
           h->ws_band_slots = 0;
-          (void)hipGetLastError();  // an allocation that failed: the records serve
           if (!fits)
             throw Error{e.status,
                         "too many projectors for the stencil pass (alpha row does not fit in LDS), and " + e.msg};
@@ -1798,7 +1816,6 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
           h->filter_band = true;
         } catch (...) {  // a point in too many supports, or no memory: the records serve
           h->ws_band_slots = 0;
-          (void)hipGetLastError();
         }
       }
       h->supp_off = upload(h, soff.data(), soff.size());
@@ -2493,29 +2510,35 @@ static float time_filter_launch(chefsi_handle* h, const T* X, T* B, int ns, T* a
 }
 }  // extern "C++"
 
-// Switch the projector route of a handle with projectors (mode 4: records in the stencil
-// pass, 0: band pass).  The band tables are built before anything else changes, so a
-// route that cannot be built (a point in more than kBandMaxSlots projector supports, or
-// records whose LDS does not fit the current tiling) throws and leaves the handle on its
-// current route.
 static void leave_filter_band(chefsi_handle* h) {
   if (!h->filter_band) return;
   h->filter_band = false;
   free_band_tables(h);
 }
 
+// Switch the projector route of a handle with projectors (mode 4: records in the stencil
+// pass, 0: band pass).  A route that cannot be built (a point in more than kBandMaxSlots
+// projector supports, records whose LDS does not fit the current tiling, no memory) throws and
+// leaves the handle on its current route: the new tables are complete before the old ones go.
 static void set_projector_route(chefsi_handle* h, int mode) {
   if (mode == 0) {
     build_band_tables(h, band_tables(h), false);
     h->filter_band = false;
     h->rec_max = 0;
-    build_hx_records(h, h->hx_plan);
+    build_hx_records(h, h->hx_plan);  // none: nothing is allocated
     build_scatter_records(h);
   } else {
     check(hx_records_fit(h, h->hx_plan), "too many projectors for the stencil pass (alpha row does not fit in LDS)");
+    const int was = h->rec_max;
     h->rec_max = mode;
-    build_hx_records(h, h->hx_plan);
-    build_scatter_records(h);
+    try {
+      build_hx_records(h, h->hx_plan);
+      build_scatter_records(h);
+    } catch (...) {
+      h->rec_max = was;
+      build_hx_records(h, h->hx_plan);  // none again
+      throw;
+    }
     h->filter_band = false;
     free_band_tables(h);
   }
@@ -2826,9 +2849,9 @@ template <typename T>
 T* kupload(const T* src, size_t n) {
   T* d = nullptr;
   if (n == 0) return nullptr;
-  if (hipMalloc(&d, n * sizeof(T)) != hipSuccess) throw Error{CHEFSI_ERR_OOM, "device allocation failed"};
+  if (no_memory(hipMalloc(&d, n * sizeof(T)))) throw Error{CHEFSI_ERR_OOM, "device allocation failed"};
   hipError_t e = hipMemcpy(d, src, n * sizeof(T), hipMemcpyHostToDevice);
-  if (e != hipSuccess) {
+  if (no_memory(e)) {
     (void)hipFree(d);
     throw Error{CHEFSI_ERR_HIP, std::string("upload: ") + hipGetErrorString(e)};
   }
@@ -3085,7 +3108,7 @@ int chefsi_kpoint_create(const chefsi_grid_t* grid, const double* veff_host, con
     BLAS_TRY(rocblas_create_handle(&h->blas));
     BLAS_TRY(rocblas_set_atomics_mode(h->blas, rocblas_atomics_not_allowed));
     const size_t pinned_doubles = std::max({(size_t)max_ns + 8, (size_t)h->n_atoms * 10, (size_t)kVecBlocks});
-    if (hipHostMalloc((void**)&h->pinned, pinned_doubles * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    if (no_memory(hipHostMalloc((void**)&h->pinned, pinned_doubles * sizeof(double), hipHostMallocDefault))) {
       h->pinned = nullptr;
       throw Error{CHEFSI_ERR_OOM, "pinned host allocation failed"};
     }
@@ -3120,8 +3143,8 @@ int chefsi_kpoint_create(const chefsi_grid_t* grid, const double* veff_host, con
       h->gent_chi = kupload(gent_chi.data(), gent_chi.size());
       h->q_slot_ptr = kupload(R.q_slot_ptr.data(), R.q_slot_ptr.size());
       h->q_slot = kupload(R.q_slot.data(), R.q_slot.size());
-      if (hipMalloc((void**)&h->partial, std::max<size_t>(1, R.slot_q.size()) * (size_t)max_ns * sizeof(double2)) !=
-          hipSuccess) {
+      if (no_memory(hipMalloc((void**)&h->partial,
+                              std::max<size_t>(1, R.slot_q.size()) * (size_t)max_ns * sizeof(double2)))) {
         h->partial = nullptr;
         throw Error{CHEFSI_ERR_OOM, "device allocation failed (band-pass partial sums)"};
       }
