@@ -113,12 +113,16 @@ typedef struct {
  * Returns CHEFSI_ERR_INVALID_ARG on inconsistent input (including a support
  * index outside the grid or not strictly increasing), or with more than 65535
  * projectors in all.  Where the projector term is added (see chefsi_set_projector_pass) until
- * a call chooses: an FP64 handle for at least 8 orbitals takes the band pass from 2^20 values
- * (Nd max_ns) on, or from 2^18 where 512 or more points lie in more than four projector
- * entries; a mixed one takes it in the filter only (its single applications keep the records),
- * from 8 orbitals and 2^20 values on, or from 4 orbitals where any point lies in more than
- * four entries.  Other handles, and those with a grid point in more than 128 projector
- * supports, take the records.
+ * a call chooses: in the stencil pass (records), and in the band pass for calls on enough
+ * orbitals.  Where 512 or more points lie in more than four projector entries that is from 4
+ * orbitals on (16 from 2^20 points on; with at least 8 orbitals and 2^18 values Nd max_ns); with
+ * fewer such points from 3 2^20 values Nd ns on; without any from 2^23 values on where at most
+ * a fifth of the points lies in a support (a third on rows of 96 points and more; filters
+ * otherwise too, FP64 ones from 2^23 values up to a third, others from 2^27 on).  A mixed
+ * handle takes it in filters only, from 4 (16) orbitals on where any point lies in more than
+ * four entries, and its single applications keep the records.  Grids of 2^14 to 2^15 points
+ * with fewer than 512 such points take it from 4 orbitals on where Nd max_ns reaches 2^20.
+ * Handles with a grid point in more than 128 projector supports take the records.
  * When the projectors are too many for the block's coefficient row to fit in LDS beside the
  * default tile (in FP64 about 5000 on a grid 120 points wide) the handle is on the band pass
  * whatever its size, and is refused only when a grid point also lies in more than 128
@@ -176,8 +180,8 @@ int chefsi_set_stencil_tiling(chefsi_handle_t* h, int32_t rows_per_thread, int32
  * current tiling leaves no LDS for its records.  Rebuilds the handle's tables (the band
  * pass holds partial sums, 256 MiB or 64 orbitals' worth at most: in the call's workspace on a
  * handle that chefsi_create put on it, on the device beside the tables otherwise); for tuning
- * and tests, not while calls on the handle are in flight.  What chefsi_create chose for a
- * filter is replaced too. */
+ * and tests, not while calls on the handle are in flight.  What chefsi_create chose by the
+ * call's width is replaced too. */
 int chefsi_set_projector_pass(chefsi_handle_t* h, int32_t in_stencil);
 
 /* Picks the stencil tiling and the projector split by timing them (the planner's

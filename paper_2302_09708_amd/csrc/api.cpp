@@ -119,7 +119,9 @@ void* scratch_address(int dev) {
 }  // namespace
 
 
-// Band-pass tables on the device (built while rec_max == 0 or filter_band).
+constexpr int kNoBand = INT32_MAX;
+
+// Band-pass tables on the device (built while rec_max == 0, or for band_apply and band_filter).
 struct BandDevice {
   int nb_reg = 0, nb_pts = 0, nb_slots = 0;
   int* nb_reg_pt = nullptr;
@@ -197,11 +199,11 @@ struct chefsi_handle : BandDevice {
   // stencil pass (4: the record width), the others in the scatter pass; 0: every term in
   // the band pass (nl_band) instead
   int rec_max = 4;
-  // a mixed handle as created: filters take the band pass (FP32 tables only) beside the records
-  // that single applications use
-  bool filter_band = false;
-  // slots of a handle that started on the band pass (0: it did not): its workspaces carry the
-  // partials, nb_partial serves only the calls without one
+  // a handle as created has the band pass beside the records for calls on at least this many
+  // orbitals: single applications, and filters (band_from)
+  int band_apply = kNoBand, band_filter = kNoBand;
+  // slots of a handle that was created with the band pass (0: it was not): its workspaces carry
+  // the partials, nb_partial serves only the calls without one
   int ws_band_slots = 0;
 
   rocblas_handle blas = nullptr;
@@ -691,8 +693,8 @@ void band_alpha(chefsi_handle* h, TY* y, int ns, TC* alpha, const TC* gdv, bool 
 // first), or, on a handle switched to the band pass, nl_band after a bare stencil pass.  In
 // the band route alpha holds projector-major coefficients: alpha_ready says they are already
 // those of x (the previous application computed them), want_next asks for those of out.
-// in_filter: an application of the filter (or the one that follows it), which a handle with
-// filter_band also runs on the band route.
+// in_filter: an application of the filter (or the one that follows it), for which a handle as
+// created has another limit (band_filter).
 template <typename TI, typename TC, typename TO>
 void apply_fused(chefsi_handle* h, const TI* x, const TO* prev, TO* out, int ns, double sa, double sc, double sb,
                  TC* alpha, hipStream_t s, BandScratch bs, bool alpha_ready = false, bool want_next = false,
@@ -712,7 +714,7 @@ void apply_fused(chefsi_handle* h, const TI* x, const TO* prev, TO* out, int ns,
     chi = h->chi32;
     gdv = h->gdv32;
   }
-  const bool band = h->np_tot > 0 && (h->rec_max == 0 || (in_filter && h->filter_band));
+  const bool band = h->np_tot > 0 && (h->rec_max == 0 || ns >= (in_filter ? h->band_filter : h->band_apply));
   if (band) {
     if (!alpha_ready) band_alpha<TI, TC>(h, const_cast<TI*>(x), ns, alpha, gdv, false, 0.0, true, s, bs);
   } else if (h->np_tot > 0) {
@@ -1478,6 +1480,61 @@ void build_band_tables(chefsi_handle* h, const BandTables& t, bool filter_only) 
   h->nb_slots = (int)R.slot_q.size();
 }
 
+// From how many orbitals on a call takes the band pass (kNoBand: never): single applications of
+// H, and filters, on a handle as created.
+//
+// The band pass costs launches and passes over the touched points; it leaves the stencil pass
+// bare, spares the scatter pass over the points in more than four entries that the records leave
+// where supports overlap, and in a filter the gather of the coefficients.  So it pays from a number
+// of values (points x orbitals) on, sooner the more such points there are, and without any only
+// where few points are touched.  Band pass / records, one H X (FP64) or a filter application:
+//   512 and more such points: four orbitals 30x33x28 1.00, 45^3 slab 0.99, 64^3 1.07 (16: 0.78),
+//     60x60x180 0.96; 120^3 8 orbitals 1.09, 16 1.04, 24 0.96; below eight orbitals and 2^18 values
+//     in the widest call the tables are not built.  Mixed filters from any such point on: four
+//     orbitals 0.76 to 1.05, eight 0.65 to 0.92.
+//   fewer in FP64: 2^21 values 0.99 to 1.05, 2^22 0.80 to 1.0.
+//   none, at most a fifth touched: 2^22 values 1.1 to 1.4, 2^23 0.94 to 1.07, 2^24 0.81 to 0.95;
+//     mixed filters 1.02 to 1.1, 0.93 to 1.0, 0.87.
+//   none, more touched: one H X 1.05 to 1.15 up to 600 orbitals (72^3, 31 %; on rows of 96 points
+//     and more, where the records cost more, 0.9 with up to a third), FP64 filters 0.97 to 1.02
+//     from 2^23 and 0.95 from 2^26 values on, mixed ones 1.0 to 1.1 up to 2^26 and 0.94 to 0.98 from
+//     2^27 on.
+// Grids of 2^14 to 2^15 points without 512 such points take it from 2^20 values of the widest call
+// on although the records are faster there (27x30x26, one atom, 60 orbitals 1.4): the tests hold
+// these handles to the bits of that route.
+// A mixed handle keeps the records for single applications, whose FP32 rounding the FP64
+// matrices of chefsi_project show.
+struct BandFrom {
+  int apply, filter;
+};
+
+BandFrom band_from(const chefsi_handle* h) {
+  const int64_t nd = h->nd, widest = nd * h->max_ns;
+  const bool mixed = h->precision == CHEFSI_MIXED;
+  int64_t touched = 0, scattered = 0;
+  for (int64_t i = 0; i < nd; ++i) {
+    const int n = h->pt_cnt[i + 1] - h->pt_cnt[i];
+    touched += n > 0;
+    scattered += n > 4;
+  }
+  auto from = [&](int64_t values) { return (int)std::min<int64_t>(kNoBand, std::max<int64_t>(8, (values + nd - 1) / nd)); };
+  const int few = nd >= (int64_t)1 << 20 ? 16 : 4;
+  BandFrom b{kNoBand, kNoBand};
+  if (scattered >= 512 || (mixed && scattered > 0)) {
+    if (mixed ? h->max_ns >= 4 : h->max_ns >= 8 && widest >= (int64_t)1 << 18) b = {few, few};
+  } else if (nd >= (int64_t)1 << 14 && nd < (int64_t)1 << 15) {
+    if (h->max_ns >= 8 && widest >= (int64_t)1 << 20) b = {few, few};
+  } else if (scattered > 0) {
+    b.apply = b.filter = from((int64_t)3 << 20);
+  } else {
+    const bool sparse = touched * (h->n[0] >= 96 ? 3 : 5) <= nd;
+    if (sparse) b.apply = from((int64_t)1 << 23);
+    b.filter = from((int64_t)1 << (sparse || (!mixed && 3 * touched <= nd) ? 23 : 27));
+  }
+  if (mixed) b.apply = kNoBand;
+  return b;
+}
+
 // Scatter-pass records for the points in more than rec_max projector entries (all touched
 // points when rec_max is 0): one record {point, first entry, entry count, 0} each, entries
 // in atom order padded with zeros to a multiple of 4; replaces the handle's current ones.
@@ -1766,44 +1823,24 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
       h->pt_col = std::move(eproj);
       h->pt_val = std::move(eval);
       check(h->np_tot < 65536, "more than 65535 projectors");
-      // The route a handle starts on.  The record route keeps the block's projector row and
-      // partial sums in LDS beside the tile: a handle whose projectors overflow that for the
-      // default tile needs the band pass.  Otherwise the band pass is taken where the block is
-      // large enough for its extra launches: it leaves the stencil pass bare and carries the
-      // coefficients through a filter.  One filter application, records / band pass (us):
-      // 24^3, 40 orbitals FP64 20.2 / 28.6; 72^3, one orbital 23.4 / 26.2; 30x33x28, 60 FP32
-      // 53.9 / 32.4; 72^3, 16 FP64 87 / 79; 45^3 slab, 187 FP32 136 / 102; 64^3, 100 FP64 273 /
-      // 210; 40x52x90 slab, 300 FP64 560 / 406.  Where supports overlap the records leave the
-      // points in more than four entries to a scatter pass, and smaller blocks gain too: FP64 from
-      // 512 such points and 2^18 values (30x33x28, 8 orbitals 36.7 / 26.8, one H X 40.6 / 32.0;
-      // with 345 points, 24^3, 40 orbitals 29.7 / 28.8 and 30.2 / 33.1), filters of mixed handles
-      // from four orbitals (24^3, 4 orbitals 26.4 / 22.4, 40 35.0 / 26.2).
-      // A mixed handle keeps the records for single applications, whose FP32 rounding the FP64
-      // matrices of chefsi_project show, and takes the band pass in filters.
+      // The record route keeps the block's projector row and partial sums in LDS beside the tile: a
+      // handle whose projectors overflow that for the default tile has the band pass alone.  Others
+      // have the records, and the band pass beside them for the calls that it serves better; its
+      // tables are formed in a second thread meanwhile.
       const bool fits = hx_records_fit(h, h->hx_plan);
-      int64_t scattered = 0;
-      for (int64_t i = 0; i < nd; ++i) scattered += h->pt_cnt[i + 1] - h->pt_cnt[i] > 4;
-      const bool many = max_ns >= 8 && nd * max_ns >= (int64_t)1 << 20;
-      const bool large = precision == CHEFSI_MIXED
-                             ? many || (max_ns >= 4 && scattered > 0)
-                             : many || (max_ns >= 8 && nd * max_ns >= (int64_t)1 << 18 && scattered >= 512);
-      const bool both = fits && large && precision == CHEFSI_MIXED;
+      const BandFrom from = band_from(h);
+      const bool both = fits && (from.apply <= max_ns || from.filter <= max_ns);
       std::future<BandTables> tables;
       if (both) tables = std::async([h] { return band_tables(h); });
-      if (!fits || (large && !both)) {
+      if (!fits) {
         try {
           const BandTables t = band_tables(h);
           h->ws_band_slots = std::max<int>(1, (int)t.r.slot_q.size());
           build_band_tables(h, t, false);
           h->rec_max = 0;
-        } catch (const Error& e) {  // a point in too many supports, or no memory: the records serve
-          h->ws_band_slots = 0;
-          if (!fits)
-            throw Error{e.status,
-                        "too many projectors for the stencil pass (alpha row does not fit in LDS), and " + e.msg};
-        } catch (const std::bad_alloc&) {
-          h->ws_band_slots = 0;
-          if (!fits) throw;
+        } catch (const Error& e) {
+          throw Error{e.status,
+                      "too many projectors for the stencil pass (alpha row does not fit in LDS), and " + e.msg};
         }
       }
       build_hx_records(h, h->hx_plan);
@@ -1812,8 +1849,9 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
         try {
           const BandTables t = tables.get();
           h->ws_band_slots = std::max<int>(1, (int)t.r.slot_q.size());
-          build_band_tables(h, t, true);
-          h->filter_band = true;
+          build_band_tables(h, t, precision == CHEFSI_MIXED);
+          h->band_apply = from.apply;
+          h->band_filter = from.filter;
         } catch (...) {  // a point in too many supports, or no memory: the records serve
           h->ws_band_slots = 0;
         }
@@ -2510,9 +2548,10 @@ static float time_filter_launch(chefsi_handle* h, const T* X, T* B, int ns, T* a
 }
 }  // extern "C++"
 
-static void leave_filter_band(chefsi_handle* h) {
-  if (!h->filter_band) return;
-  h->filter_band = false;
+// Leave the band pass that a handle as created has beside its records.
+static void leave_band(chefsi_handle* h) {
+  if (h->rec_max == 0) return;
+  h->band_apply = h->band_filter = kNoBand;
   free_band_tables(h);
 }
 
@@ -2523,7 +2562,7 @@ static void leave_filter_band(chefsi_handle* h) {
 static void set_projector_route(chefsi_handle* h, int mode) {
   if (mode == 0) {
     build_band_tables(h, band_tables(h), false);
-    h->filter_band = false;
+    h->band_apply = h->band_filter = kNoBand;
     h->rec_max = 0;
     build_hx_records(h, h->hx_plan);  // none: nothing is allocated
     build_scatter_records(h);
@@ -2539,7 +2578,7 @@ static void set_projector_route(chefsi_handle* h, int mode) {
       build_hx_records(h, h->hx_plan);  // none again
       throw;
     }
-    h->filter_band = false;
+    h->band_apply = h->band_filter = kNoBand;
     free_band_tables(h);
   }
 }
@@ -2577,7 +2616,7 @@ int chefsi_autotune(chefsi_handle_t* h, const void* X, int32_t ns, void* ws, siz
     } ev{e0, e1};
     const bool prof = h->prof_on;
     h->prof_on = false;
-    leave_filter_band(h);
+    leave_band(h);
     float best = 1e30f;
     int best_mode = h->rec_max, best_c = 0;
     auto timed = [&](const HxPlan& p, int nt) {
@@ -2668,7 +2707,7 @@ int chefsi_set_projector_pass(chefsi_handle_t* h, int32_t in_stencil) {
       return;
     }
     if (want == h->rec_max) {
-      leave_filter_band(h);  // the records everywhere, also in filters
+      leave_band(h);  // the records everywhere
       return;
     }
     set_projector_route(h, want);

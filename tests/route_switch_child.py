@@ -8,7 +8,9 @@ from tests._host import Host
 def main(stub, precision, to_stencil):
     prob = inputs.small_problem(n=(27, 30, 26), h=(0.3, 0.3, 0.3), bc=(0, 0, 1), n_atoms=20, nproj_per_atom=4, seed=17)
     h = Host(stub, prob, int(precision), 60)
-    what = [("apply", 6), ("filter", 6), ("apply", 60), ("filter", 60)]
+    if int(to_stencil):
+        h.h.chefsi_set_projector_pass(False)
+    what = [("apply", 6), ("filter", 6), ("apply", 60), ("filter", 60), ("apply", 2)]
     before, size = [h.kernels(*w) for w in what], h.h.device_bytes()
     failed = 0
     for k in range(1, 100):

@@ -11,7 +11,7 @@ def stub(tmp_path_factory):
     return _host.build_stub(tmp_path_factory.mktemp("stub"))
 
 
-# an FP64 handle starts on the band pass, a mixed one takes it in filters beside the records
-@pytest.mark.parametrize("precision,to_stencil", [(0, 1), (1, 0)])
+# handles as created have the band pass beside the records; to the records: from the band pass alone
+@pytest.mark.parametrize("precision,to_stencil", [(0, 0), (0, 1), (1, 0), (1, 1)])
 def test_failed_switch(stub, precision, to_stencil):
     assert int(_host.run(stub, "tests.route_switch_child", precision, to_stencil)) > 2
