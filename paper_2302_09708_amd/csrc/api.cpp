@@ -278,11 +278,19 @@ BlasGram plan_blas_gram(int64_t nd, int ns) {
 
 // gram_f64.hip forms both products in one launch and is the faster of the two everywhere but
 // on columns a multiple of 2 MiB apart: there the columns' lines of one row all fall into one
-// set of the L2, the 64-wide tiles lose their reuse, and rocBLAS's 128-wide ones win from
-// about 512 orbitals.  Both products, own / rocBLAS (us): 64^3 500 orbitals 2860 / 3053, 600
-// 4771 / 4343, 900 11.7 / 10.5 ms; 64x64x63 600 3617 / 4282; 72^3 600 5329 / 6239, 1200 20.9 /
-// 25.1 ms; 24^3 40 17 / 274.
-bool blas_gram_faster(int64_t nd, int ns) { return ns > 512 && nd % (1 << 18) == 0; }
+// set of the L2 and the 64-wide tiles lose their reuse.  rocBLAS's 128-wide ones win above 512
+// orbitals, and on strides of 4 MiB and more from 353 on where their last tile is more than seven
+// eighths full.  One projection, own / rocBLAS (ms): 64^3 (2 MiB) 500 orbitals 3.49 / 3.68, 600
+// 4.77 / 4.34 (products alone), 900 11.7 / 10.5; 64x128x64 (4 MiB) 300 3.35 / 3.94, 384 4.99 /
+// 4.44, 448 6.15 / 6.39, 500 7.63 / 6.94; 64x160x128 (10 MiB) 448 17.5 / 18.0, 460 20.9 / 18.0;
+// 96x128x64 (6 MiB) 384 8.10 / 8.08, 500 12.9 / 12.3; 128x128x64 (8 MiB) 400 12.7 / 12.5, 448 13.7
+// / 13.5, 500 17.3 / 15.8; strides of an odd multiple of 1 MiB 0.7 to 0.9; 72^3 600 5.3 / 6.2
+// (products alone), 24^3 40 17 / 274 us.
+bool blas_gram_faster(int64_t nd, int ns) {
+  const int64_t stride = 1 << 18;  // 2 MiB of doubles
+  if (nd % stride != 0) return false;
+  return ns > 512 || (nd > stride && ns > 352 && 8 * ns > 7 * ((ns + 127) / 128 * 128));
+}
 
 // FP64 products of the FP32 block of a mixed handle (its FP64 Rayleigh-Ritz pass): the
 // block is widened to FP64 one row panel at a time and each panel goes to rocBLAS dgemm.

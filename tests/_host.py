@@ -52,8 +52,14 @@ class Host:
         return 0
 
     def kernels(self, what, ns):
-        """Names of the kernels of one call ("apply" or "filter") on ns orbitals, in order."""
+        """Names of the kernels of one call ("apply", "filter" or "project") on ns orbitals, in order."""
         size = self.h.chefsi_workspace_bytes(ns)
+        if what == "project":  # launches alone: nothing reads or writes the blocks
+            a = C.c_void_p(1 << 20)
+            self.stub.stub_clear()
+            st = self.lib.chefsi_project(self.h.h, a, ns, a, a, a, C.c_size_t(size), None)
+            assert st == 0, st
+            return self.stub.stub_launches().decode().split()
         ws = np.zeros(size + 256, dtype=np.uint8)
         ws = ws[-ws.ctypes.data % 256:][:size]
         X, Y = (np.zeros((ns, self.prob.nd), dtype=self.dtype) for _ in range(2))

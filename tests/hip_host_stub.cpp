@@ -1,7 +1,7 @@
 // The HIP, rocBLAS and rocSOLVER entry points that libchefsi.so uses, on the host: loaded before
 // the library in a process without a GPU, they let its host code run.  "Device" memory is host
-// memory, kernels are not run: a launch appends the kernel's name to a list, and a null table
-// handed to a kernel that reads it is counted.  stub_fail(k): the k-th allocation from now on fails.
+// memory, kernels are not run: a launch appends the kernel's (or library call's) name to a list,
+// and a null table handed to a kernel that reads it is counted.  stub_fail(k): the k-th allocation from now on fails.
 #include <cstdlib>
 #include <cstring>
 #include <map>
@@ -123,6 +123,10 @@ int rocblas_stop_device_memory_size_query(void*, size_t* n) {
   *n = 0;
   return 0;
 }
+int rocblas_dgemm_strided_batched() {
+  launches += "rocblas_dgemm_strided_batched\n";
+  return 0;
+}
 const char* rocblas_status_to_string(int) { return "stub"; }
 ZERO(rocblas_destroy_handle)
 ZERO(rocblas_set_atomics_mode)
@@ -130,7 +134,6 @@ ZERO(rocblas_set_stream)
 ZERO(rocblas_set_workspace)
 ZERO(rocblas_start_device_memory_size_query)
 ZERO(rocblas_dgemm)
-ZERO(rocblas_dgemm_strided_batched)
 ZERO(rocblas_dtrsm)
 ZERO(rocblas_zgemm)
 ZERO(rocblas_zgemm_strided_batched)
