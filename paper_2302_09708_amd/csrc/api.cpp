@@ -11,6 +11,7 @@
 #include <cstring>
 #include <future>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -1256,46 +1257,53 @@ void build_hx_records(chefsi_handle* h, const HxPlan& hp) {
   const int64_t nd = h->nd;
   check(h->rec_max == 0 || hx_records_fit(h, hp),
         "too many projectors for the stencil pass (alpha row does not fit in LDS)");
-  const int64_t nkeys = h->rec_max > 0 ? (int64_t)hp.nty * nz : 0;
   const bool f32 = h->precision == CHEFSI_MIXED;
-  auto key_of = [&](int64_t i) {
-    const int y = (int)((i / nx) % ny), z = (int)(i / ((int64_t)nx * ny));
-    return (int64_t)(y / hp.ty) * nz + z;
-  };
+  const int planes = h->rec_max > 0 ? nz : 0;  // the band pass takes every term: no records
+  const int64_t nkeys = (int64_t)hp.nty * planes;
   const std::vector<int>& cnt = h->pt_cnt;
   std::vector<int> rptr(nkeys + 1, 0);
-  const int64_t np = h->rec_max > 0 ? nd : 0;  // the band pass takes every term: no records
-  for (int64_t i = 0; i < np; ++i) {
-    const int n = cnt[i + 1] - cnt[i];
-    if (n >= 1 && n <= h->rec_max) rptr[key_of(i) + 1] += 1;
-  }
+  for (int z = 0; z < planes; ++z)
+    for (int y = 0; y < ny; ++y) {
+      const int* c = cnt.data() + ((int64_t)z * ny + y) * nx;
+      int& count = rptr[(int64_t)(y / hp.ty) * nz + z + 1];
+      for (int x = 0; x < nx; ++x) {
+        const int n = c[x + 1] - c[x];
+        count += n >= 1 && n <= h->rec_max;
+      }
+    }
   for (int64_t k = 0; k < nkeys; ++k) rptr[k + 1] += rptr[k];
   const int nrec = rptr[nkeys];
-  std::vector<HxRec<double>> r64(std::max(nrec, 1));
-  std::vector<HxRec<float>> r32(f32 ? std::max(nrec, 1) : 0);
-  std::memset(r64.data(), 0, r64.size() * sizeof(HxRec<double>));
-  if (f32) std::memset(r32.data(), 0, r32.size() * sizeof(HxRec<float>));
+  std::unique_ptr<HxRec<double>[]> r64(new HxRec<double>[std::max(nrec, 1)]);
+  std::unique_ptr<HxRec<float>[]> r32(f32 ? new HxRec<float>[std::max(nrec, 1)] : nullptr);
   std::vector<int> rfill(rptr.begin(), rptr.end() - 1);
-  for (int64_t i = 0; i < np; ++i) {
-    const int b = cnt[i], n = cnt[i + 1] - b;
-    if (n < 1 || n > h->rec_max) continue;
-    const int r = rfill[key_of(i)]++;
-    const int x = (int)(i % nx), y = (int)((i / nx) % ny);
-    int col[4] = {0, 0, 0, 0};
-    for (int k = 0; k < n; ++k) {
-      col[k] = h->pt_col[b + k];
-      r64[r].val[k] = h->pt_val[b + k];
-      if (f32) r32[r].val[k] = (float)h->pt_val[b + k];
+  for (int z = 0; z < planes; ++z)
+    for (int y = 0; y < ny; ++y) {
+      const int* c = cnt.data() + ((int64_t)z * ny + y) * nx;
+      int& r = rfill[(int64_t)(y / hp.ty) * nz + z];
+      for (int x = 0; x < nx; ++x) {
+        const int b = c[x], n = c[x + 1] - b;
+        if (n < 1 || n > h->rec_max) continue;
+        HxRec<double> rec{};
+        int col[4] = {0, 0, 0, 0};
+        for (int k = 0; k < n; ++k) {
+          col[k] = h->pt_col[b + k];
+          rec.val[k] = h->pt_val[b + k];
+        }
+        rec.lidx = (y % hp.ty) * nx + x;
+        rec.c01 = col[0] | (col[1] << 16);
+        rec.c23 = col[2] | (col[3] << 16);
+        r64[r] = rec;
+        if (f32) {
+          HxRec<float> half{};
+          half.lidx = rec.lidx;
+          half.c01 = rec.c01;
+          half.c23 = rec.c23;
+          for (int k = 0; k < n; ++k) half.val[k] = (float)rec.val[k];
+          r32[r] = half;
+        }
+        ++r;
+      }
     }
-    r64[r].lidx = (y % hp.ty) * nx + x;
-    r64[r].c01 = col[0] | (col[1] << 16);
-    r64[r].c23 = col[2] | (col[3] << 16);
-    if (f32) {
-      r32[r].lidx = r64[r].lidx;
-      r32[r].c01 = r64[r].c01;
-      r32[r].c23 = r64[r].c23;
-    }
-  }
   int* nptr = nullptr;
   HxRec<double>* n64 = nullptr;
   HxRec<float>* n32 = nullptr;
@@ -1303,8 +1311,8 @@ void build_hx_records(chefsi_handle* h, const HxPlan& hp) {
   try {
     if (nrec > 0) {
       nptr = upload(h, rptr.data(), rptr.size());
-      n64 = upload(h, r64.data(), r64.size());
-      if (f32) n32 = upload(h, r32.data(), r32.size());
+      n64 = upload(h, r64.get(), nrec);
+      if (f32) n32 = upload(h, r32.get(), nrec);
     }
   } catch (...) {
     for (void* q : {(void*)nptr, (void*)n64, (void*)n32})
@@ -1315,8 +1323,8 @@ void build_hx_records(chefsi_handle* h, const HxPlan& hp) {
   for (void* q : {(void*)h->hx_rec_ptr, (void*)h->hx_rec64, (void*)h->hx_rec32})
     if (q) (void)hipFree(q);
   h->device_bytes -= h->hx_rec_bytes;
-  h->hx_rec_bytes = nrec > 0 ? rptr.size() * sizeof(int) + r64.size() * sizeof(HxRec<double>) +
-                                   r32.size() * sizeof(HxRec<float>)
+  h->hx_rec_bytes = nrec > 0 ? rptr.size() * sizeof(int) +
+                                   (size_t)nrec * (sizeof(HxRec<double>) + (f32 ? sizeof(HxRec<float>) : 0))
                              : 0;
   h->hx_rec_ptr = nptr;
   h->hx_rec64 = n64;
@@ -1428,20 +1436,29 @@ BandRegions band_regions(int64_t nd, const int* cnt, const int* col, int np_tot,
 struct BandTables {
   BandRegions r;
   std::vector<double> ent_chi, gent_chi;
+  std::vector<float> ent_chi32, gent_chi32;
 };
 
-BandTables band_tables(const chefsi_handle* h) {
+BandTables band_tables(const chefsi_handle* h, bool filter_only) {
   BandTables t;
   t.r = band_regions(h->nd, h->pt_cnt.data(), h->pt_col.data(), h->np_tot, kBandMaxPts, kBandMaxEnt);
-  t.ent_chi.resize(t.r.ent_src.size());
-  t.gent_chi.resize(t.r.gent_src.size());
-  for (size_t e = 0; e < t.ent_chi.size(); ++e) t.ent_chi[e] = h->pt_val[t.r.ent_src[e]];
-  for (size_t e = 0; e < t.gent_chi.size(); ++e) t.gent_chi[e] = h->pt_val[t.r.gent_src[e]];
+  auto values = [&](auto& v, const std::vector<int>& src) {
+    v.resize(src.size());
+    for (size_t e = 0; e < src.size(); ++e) v[e] = h->pt_val[src[e]];
+  };
+  if (!filter_only) {
+    values(t.ent_chi, t.r.ent_src);
+    values(t.gent_chi, t.r.gent_src);
+  }
+  if (h->precision == CHEFSI_MIXED) {
+    values(t.ent_chi32, t.r.ent_src);
+    values(t.gent_chi32, t.r.gent_src);
+  }
   return t;
 }
 
 // The handle's current tables are replaced, or kept where the new ones cannot be built.
-void build_band_tables(chefsi_handle* h, const BandTables& t, bool filter_only) {
+void build_band_tables(chefsi_handle* h, const BandTables& t) {
   const BandRegions& R = t.r;
   const size_t before = h->device_bytes;
   const BandDevice old = *h;
@@ -1457,15 +1474,10 @@ void build_band_tables(chefsi_handle* h, const BandTables& t, bool filter_only) 
     h->nb_gent_loc = upload(h, R.gent_loc.data(), R.gent_loc.size());
     h->nb_q_slot_ptr = upload(h, R.q_slot_ptr.data(), R.q_slot_ptr.size());
     h->nb_q_slot = upload(h, R.q_slot.data(), R.q_slot.size());
-    if (!filter_only) {
-      h->nb_ent_chi64 = upload(h, t.ent_chi.data(), t.ent_chi.size());
-      h->nb_gent_chi64 = upload(h, t.gent_chi.data(), t.gent_chi.size());
-    }
-    if (h->precision == CHEFSI_MIXED) {
-      const std::vector<float> f(t.ent_chi.begin(), t.ent_chi.end()), g(t.gent_chi.begin(), t.gent_chi.end());
-      h->nb_ent_chi32 = upload(h, f.data(), f.size());
-      h->nb_gent_chi32 = upload(h, g.data(), g.size());
-    }
+    h->nb_ent_chi64 = upload(h, t.ent_chi.data(), t.ent_chi.size());
+    h->nb_gent_chi64 = upload(h, t.gent_chi.data(), t.gent_chi.size());
+    h->nb_ent_chi32 = upload(h, t.ent_chi32.data(), t.ent_chi32.size());
+    h->nb_gent_chi32 = upload(h, t.gent_chi32.data(), t.gent_chi32.size());
     const int own_ns = h->ws_band_slots > 0 ? std::min<int>(h->max_ns, kBandMinOrbitals) : h->max_ns;
     const size_t pbytes = band_partial_bytes(h, (int)R.slot_q.size(), own_ns);
     if (no_memory(hipMalloc(&h->nb_partial, pbytes))) {
@@ -1602,28 +1614,38 @@ void build_scatter_records(chefsi_handle* h) {
 // r at both ends of a direction, exceed what the force kernel keeps in registers and LDS.
 std::vector<int> support_boxes(const chefsi_handle* h) {
   std::vector<int> box(6 * (size_t)h->n_atoms, 0);
-  std::vector<char> seen;
+  std::vector<char> seen[3];
   for (int J = 0; J < h->n_atoms; ++J) {
     const int64_t s0 = h->supp_ptr_h[J], s1 = h->supp_ptr_h[J + 1];
     if (s1 - s0 > kGradBoxPoints) return {};
     int* b = box.data() + 6 * (size_t)J;
+    for (int d = 0; d < 3; ++d) seen[d].assign(h->n[d], 0);
+    int64_t row = 0, row_end = 0;  // grid row of the last point (support indices increase)
+    for (int64_t s = s0; s < s1; ++s) {
+      const int64_t i = h->supp_idx_h[s];
+      if (i >= row_end) {
+        row = i / h->n[0];
+        row_end = (row + 1) * h->n[0];
+        seen[1][row % h->n[1]] = 1;
+        seen[2][row / h->n[1]] = 1;
+      }
+      seen[0][i - row * h->n[0]] = 1;
+    }
     for (int d = 0; d < 3; ++d) {
-      const int n = h->n[d], div = d == 0 ? 1 : (d == 1 ? h->n[0] : h->n[0] * h->n[1]);
-      seen.assign(n, 0);
-      for (int64_t s = s0; s < s1; ++s) seen[h->supp_idx_h[s] / div % n] = 1;
+      const int n = h->n[d];
       int first = 0, last = n - 1;
-      while (first < n && !seen[first]) ++first;
+      while (first < n && !seen[d][first]) ++first;
       if (first == n) {  // no points
         b[d] = 0;
         b[3 + d] = 1;
         continue;
       }
-      while (!seen[last]) --last;
+      while (!seen[d][last]) --last;
       b[d] = first;
       b[3 + d] = last - first + 1;
       if (h->bc[d] == 0) {  // the longest run of unseen points between two seen ones, if longer
         for (int i = first, gap = 0; i <= last; ++i) {
-          gap = seen[i] ? 0 : gap + 1;
+          gap = seen[d][i] ? 0 : gap + 1;
           if (gap > 0 && n - gap < b[3 + d]) {
             b[d] = i + 1;
             b[3 + d] = n - gap;
@@ -1839,12 +1861,12 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
       const BandFrom from = band_from(h);
       const bool both = fits && (from.apply <= max_ns || from.filter <= max_ns);
       std::future<BandTables> tables;
-      if (both) tables = std::async([h] { return band_tables(h); });
+      if (both) tables = std::async([h] { return band_tables(h, h->precision == CHEFSI_MIXED); });
       if (!fits) {
         try {
-          const BandTables t = band_tables(h);
+          const BandTables t = band_tables(h, false);
           h->ws_band_slots = std::max<int>(1, (int)t.r.slot_q.size());
-          build_band_tables(h, t, false);
+          build_band_tables(h, t);
           h->rec_max = 0;
         } catch (const Error& e) {
           throw Error{e.status,
@@ -1853,17 +1875,6 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
       }
       build_hx_records(h, h->hx_plan);
       build_scatter_records(h);
-      if (both) {
-        try {
-          const BandTables t = tables.get();
-          h->ws_band_slots = std::max<int>(1, (int)t.r.slot_q.size());
-          build_band_tables(h, t, precision == CHEFSI_MIXED);
-          h->band_apply = from.apply;
-          h->band_filter = from.filter;
-        } catch (...) {  // a point in too many supports, or no memory: the records serve
-          h->ws_band_slots = 0;
-        }
-      }
       h->supp_off = upload(h, soff.data(), soff.size());
       h->supp_idx = upload(h, h->supp_idx_h.data(), h->supp_idx_h.size());
       h->chi_off = upload(h, coff.data(), coff.size());
@@ -1877,6 +1888,17 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
       h->gdv64 = upload(h, gdv.data(), gdv.size());
       std::vector<float> gdv32(gdv.begin(), gdv.end());
       h->gdv32 = upload(h, gdv32.data(), gdv32.size());
+      if (both) {
+        try {
+          const BandTables t = tables.get();
+          h->ws_band_slots = std::max<int>(1, (int)t.r.slot_q.size());
+          build_band_tables(h, t);
+          h->band_apply = from.apply;
+          h->band_filter = from.filter;
+        } catch (...) {  // a point in too many supports, or no memory: the records serve
+          h->ws_band_slots = 0;
+        }
+      }
     }
     *out = h;
     return CHEFSI_OK;
@@ -2569,7 +2591,7 @@ static void leave_band(chefsi_handle* h) {
 // leaves the handle on its current route: the new tables are complete before the old ones go.
 static void set_projector_route(chefsi_handle* h, int mode) {
   if (mode == 0) {
-    build_band_tables(h, band_tables(h), false);
+    build_band_tables(h, band_tables(h, false));
     h->band_apply = h->band_filter = kNoBand;
     h->rec_max = 0;
     build_hx_records(h, h->hx_plan);  // none: nothing is allocated
