@@ -2565,16 +2565,15 @@ int chefsi_set_stencil_tiling(chefsi_handle_t* h, int32_t rows_per_thread, int32
 extern "C++" {
 template <typename T>
 static float time_filter_launch(chefsi_handle* h, const T* X, T* B, int ns, T* alpha, hipStream_t s,
-                                hipEvent_t e0, hipEvent_t e1, BandScratch bs) {
-  constexpr int kWarm = 1, kRuns = 3;
-  for (int i = 0; i < kWarm; ++i) apply_fused<T, T, T>(h, X, B, B, ns, 0.5, 0.25, -0.5, alpha, s, bs, false, true);
+                                hipEvent_t e0, hipEvent_t e1, BandScratch bs, int warm, int runs) {
+  for (int i = 0; i < warm; ++i) apply_fused<T, T, T>(h, X, B, B, ns, 0.5, 0.25, -0.5, alpha, s, bs, false, true);
   HIP_TRY(hipEventRecord(e0, s));
-  for (int i = 0; i < kRuns; ++i) apply_fused<T, T, T>(h, X, B, B, ns, 0.5, 0.25, -0.5, alpha, s, bs, true, true);
+  for (int i = 0; i < runs; ++i) apply_fused<T, T, T>(h, X, B, B, ns, 0.5, 0.25, -0.5, alpha, s, bs, true, true);
   HIP_TRY(hipEventRecord(e1, s));
   HIP_TRY(hipEventSynchronize(e1));
   float ms = 0.f;
   HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-  return ms / kRuns;
+  return ms / runs;
 }
 }  // extern "C++"
 
@@ -2649,16 +2648,16 @@ int chefsi_autotune(chefsi_handle_t* h, const void* X, int32_t ns, void* ws, siz
     leave_band(h);
     float best = 1e30f;
     int best_mode = h->rec_max, best_c = 0;
-    auto timed = [&](const HxPlan& p, int nt) {
+    auto timed = [&](const HxPlan& p, int nt, int warm, int runs) {
       if (h->np_tot > 0)
         build_hx_records(h, p);
       else
         h->hx_plan = p;
       return h->precision == CHEFSI_FP64
                  ? time_filter_launch<double>(h, (const double*)X, at<double>(ws, L.bufB), nt, at<double>(ws, L.alpha),
-                                              s, e0, e1, band_scratch(h, ws, L))
+                                              s, e0, e1, band_scratch(h, ws, L), warm, runs)
                  : time_filter_launch<float>(h, (const float*)X, at<float>(ws, L.bufB), nt, at<float>(ws, L.alpha), s,
-                                             e0, e1, band_scratch(h, ws, L));
+                                             e0, e1, band_scratch(h, ws, L), warm, runs);
     };
     struct Timed {
       float ms;
@@ -2684,7 +2683,7 @@ int chefsi_autotune(chefsi_handle_t* h, const void* X, int32_t ns, void* ws, siz
       }
       for (size_t c = 0; c < cands.size(); ++c) {
         if (h->np_tot > 0 && mode > 0 && !hx_records_fit(h, cands[c])) continue;  // tile too tall for the records
-        const float ms = timed(cands[c], nt);
+        const float ms = timed(cands[c], nt, 1, 3);
         seen.push_back({ms, mode, (int)c});
         if (ms < best) {
           best = ms;
@@ -2702,7 +2701,9 @@ int chefsi_autotune(chefsi_handle_t* h, const void* X, int32_t ns, void* ws, siz
     // first after them runs up to 20 % faster, and 1024 orbitals may happen to fill whole waves
     // of blocks where ns does not (60x60x180, 1200 FP32 orbitals: 32-row tiles 1.93 against
     // 2.40 ms, so that they won over 12-row ones; 71.8 against 69.7 ms a filter).
+    // One launch a round where it takes long enough to time (120^3, 1800 orbitals: 1.75 -> 1.10 s).
     constexpr int kFinal = 4;
+    const int runs = best > 1.5f ? 1 : 3;
     const int nf = std::min(ns, 2048);
     auto less = [](const Timed& a, const Timed& b) { return a.ms < b.ms; };
     seen.erase(std::remove_if(seen.begin(), seen.end(), [&](const Timed& t) { return t.mode != best_mode; }),
@@ -2711,7 +2712,7 @@ int chefsi_autotune(chefsi_handle_t* h, const void* X, int32_t ns, void* ws, siz
     if (seen.size() > kFinal) seen.resize(kFinal);
     for (int round = 0; round < 3 && seen.size() > 1; ++round)
       for (Timed& t : seen) {
-        const float ms = timed(cands[t.c], nf);
+        const float ms = timed(cands[t.c], nf, runs > 1 || round == 0, runs);
         t.ms = round > 1 ? t.ms + ms : ms;
       }
     best_c = std::min_element(seen.begin(), seen.end(), less)->c;
