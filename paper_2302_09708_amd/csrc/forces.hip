@@ -223,14 +223,16 @@ __global__ __launch_bounds__(kBoxThreads, 2) void nl_grad_box_kernel(NlGradArgs<
 #pragma unroll
   for (int t = 0; t < kBoxPts; ++t) {
     const int s = tid + t * kBoxThreads;
-    const int i = s < n ? a.supp_idx[s0 + s] : 0;
+    // past the end the last point again, with zero weights: no value is read that the sums do
+    // not contain (0 times a non-finite one would be NaN)
+    const int i = n > 0 ? a.supp_idx[s0 + min(s, n - 1)] : 0;
     const int z = i / str[2], yx = i - z * str[2], y = yx / a.nx;
     int c[3] = {yx - y * a.nx, y, z};
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
       c[b] -= lo[b];
       c[b] = c[b] < 0 ? c[b] + ext[b] : c[b];
-      place[t][b] = s < n ? c[b] : 0;
+      place[t][b] = n > 0 ? c[b] : 0;
       w[t][b] = STRESS && s < n ? a.disp[3 * (int64_t)(s0 + s) + b] : 0.0;
     }
   }
