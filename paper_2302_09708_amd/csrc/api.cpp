@@ -917,10 +917,13 @@ void panel_rotate(chefsi_handle* h, const float* X, const double* Z, float* O, i
 
 // The 256 x (128 + 128) units of the split-bf16 products run one block per CU; where they
 // leave more of the chip idle, or form more lower-triangle waste, than this allows, the
-// 128 x 128 tiles (two blocks per CU) are faster.  Both products measured, tiles / units, by
+// 128 x 128 tiles (two blocks per CU) are taken.  Both products measured, tiles / units, by
 // that share: 0.85 (60x60x180, Ns 1200) 11.95 / 6.83 ms; 0.68 (60^3, Ns 900) 2.30 / 1.73;
-// 0.67 (72^3, Ns 600) 1.94 / 1.62, (64^3, Ns 520) 1.27 / 1.22; 0.67 (60^3, Ns 400) 0.66 / 0.71;
-// 0.41 (60^3, Ns 257) 0.59 / 0.68; 0.09 (45^3, Ns 187) 0.21 / 0.58.
+// 0.67 (72^3, Ns 600) 1.94 / 1.62, (64^3, Ns 520) 1.27 / 1.22; 0.666 (60^3, Ns 400) 0.66 / 0.71;
+// 0.41 (60^3, Ns 257) 0.59 / 0.68; 0.09 (45^3, Ns 187) 0.21 / 0.58.  Many sizes lie close to the
+// line (whole rounds of six or twelve units: 0.665 to 0.674), where the share does not order
+// them; it is a safe side, not a fit: of 105 projections (45^3 to 90^3, Ns 200 to 800) the 44 above
+// it take 0.675 to 1.006 of the tiles' time, 0.669 (72^3, Ns 500) 0.857.
 constexpr double kPairMinFill = 0.668;
 
 // Hs = X^T Y, Ms = X^T X (full symmetric, FP64), via split-K partial tiles.
@@ -3177,8 +3180,7 @@ int chefsi_kpoint_create(const chefsi_grid_t* grid, const double* veff_host, con
     HIP_TRY(hipGetDevice(&h->device));
     BLAS_TRY(rocblas_create_handle(&h->blas));
     BLAS_TRY(rocblas_set_atomics_mode(h->blas, rocblas_atomics_not_allowed));
-    const size_t pinned_doubles = std::max({(size_t)max_ns + 8, (size_t)h->n_atoms * 10, (size_t)kVecBlocks});
-    if (no_memory(hipHostMalloc((void**)&h->pinned, pinned_doubles * sizeof(double), hipHostMallocDefault))) {
+    if (no_memory(hipHostMalloc((void**)&h->pinned, (size_t)max_ns * sizeof(double) + 64, hipHostMallocDefault))) {
       h->pinned = nullptr;
       throw Error{CHEFSI_ERR_OOM, "pinned host allocation failed"};
     }

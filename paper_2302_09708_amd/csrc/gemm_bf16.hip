@@ -553,14 +553,12 @@ __global__ void zsplit_kernel(const double* __restrict__ Z, int ns, int ld, int 
 // Lane (r32, g) of fragment f holds X[i][pcol[f]] for the 8 columns i = k0 + 16 s + 8 g + e
 // of each 16-wide K step s.  A column's address is a scalar one (its first for g = 0, the base
 // of a buffer) and the lane's byte offset, the same for all of them (8 g columns and the point,
-// below 2^31 bytes up to kRotNarrow points), so a load costs no vector instructions.  In the
-// stage that passes ns, and on larger grids (WIDE), the lanes form 64-bit addresses, columns
-// past ns clamped (Z is zero there).
-constexpr int64_t kRotNarrow = ((int64_t)1 << 31) / 36;
-template <bool WIDE>
+// below 2^31 bytes: a handle has at most 2^31 / 48 points), so a load costs no vector
+// instructions.  In the stage that passes ns the lanes form 64-bit addresses, columns past ns
+// clamped (Z is zero there).
 __device__ __forceinline__ void rot_load_x(float (&xv)[2][2][8], const float* __restrict__ X, int64_t nd, int ns,
                                            const int64_t (&pcol)[2], const unsigned (&voff)[2], int k0, int g) {
-  if (!WIDE && k0 + kKS <= ns) {
+  if (k0 + kKS <= ns) {
     const float* row = X + (int64_t)k0 * nd;
     const int bytes = 36 * (int)nd;  // nine columns: a lane's own lies 0 or 8 further
 #pragma unroll
@@ -604,7 +602,6 @@ __device__ __forceinline__ void rot_store_z(const u32x4 (&zr)[4], __bf16* sh, __
   *reinterpret_cast<u32x4*>(sl + 8) = zr[3];
 }
 
-template <bool WIDE>
 __global__ __launch_bounds__(256, 2) void rotate_bf16x3_kernel(const float* __restrict__ X, const __bf16* __restrict__ zh,
                                                             const __bf16* __restrict__ zl, float* __restrict__ O,
                                                             int64_t nd, int ns, int ld, int npt, int njt,
@@ -635,7 +632,7 @@ __global__ __launch_bounds__(256, 2) void rotate_bf16x3_kernel(const float* __re
 #pragma unroll
   for (int f = 0; f < 2; ++f) {
     pcol[f] = min(p0 + 32 * f + r32, nd - 1);
-    voff[f] = WIDE ? 0u : ((unsigned)(8 * g) * (unsigned)nd + (unsigned)pcol[f]) * 4u;
+    voff[f] = ((unsigned)(8 * g) * (unsigned)nd + (unsigned)pcol[f]) * 4u;
   }
 
   f32x16 acc[4][2];  // [j fragment][p fragment]
@@ -650,7 +647,7 @@ __global__ __launch_bounds__(256, 2) void rotate_bf16x3_kernel(const float* __re
   float xa[2][2][8], xb[2][2][8];  // [k16 step][p fragment][e], a stage's and the next one's
   u32x4 zr[4];
   rot_load_z(zr, pzh, pzl, 0);
-  rot_load_x<WIDE>(xa, X, nd, ns, pcol, voff, 0, g);
+  rot_load_x(xa, X, nd, ns, pcol, voff, 0, g);
   rot_store_z(zr, lds[0][0] + zoff, lds[0][1] + zoff);
   __syncthreads();
 
@@ -658,7 +655,7 @@ __global__ __launch_bounds__(256, 2) void rotate_bf16x3_kernel(const float* __re
     const bool more = t + 1 < nstage;
     if (more) {
       rot_load_z(zr, pzh, pzl, (t + 1) * kKS);
-      rot_load_x<WIDE>(xn, X, nd, ns, pcol, voff, (t + 1) * kKS, g);
+      rot_load_x(xn, X, nd, ns, pcol, voff, (t + 1) * kKS, g);
     }
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -716,10 +713,8 @@ hipError_t launch_rotate_bf16x3(const float* X, const double* Z, void* zsplit, f
   const int64_t nb = (int64_t)npt * njt;
   const int per_xcd = (int)((nb + 7) / 8);
   const dim3 grid((unsigned)(per_xcd * 8));
-  if (nd <= kRotNarrow)
-    hipLaunchKernelGGL(rotate_bf16x3_kernel<false>, grid, dim3(256), 0, s, X, zh, zl, O, nd, ns, ld, npt, njt, per_xcd);
-  else
-    hipLaunchKernelGGL(rotate_bf16x3_kernel<true>, grid, dim3(256), 0, s, X, zh, zl, O, nd, ns, ld, npt, njt, per_xcd);
+  if (nd > ((int64_t)1 << 31) / 48) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(rotate_bf16x3_kernel, grid, dim3(256), 0, s, X, zh, zl, O, nd, ns, ld, npt, njt, per_xcd);
   return hipGetLastError();
 }
 

@@ -87,11 +87,11 @@ __global__ __launch_bounds__(256) void nl_project_kernel(NlArgs<TI, TC> a) {
 
 // The same sums for few (atom, orbital) pairs: a block owns one atom and V orbitals, its
 // four waves every fourth 64 support points, kNlU of them fetched at once, so an atom's
-// serial chain of dependent gathers is 4 kNlU times shorter.  Used in FP64 below kNlFewBlocks
-// blocks of the other kernel, where those waves leave the chip idle (FP32 coefficients keep
-// the other kernel's order of summation: the split-bf16 projection built on them is compared
-// in FP64 with what it was): 24^3, 8 atoms, 40 orbitals 8.6
-// -> 4.1 us; 72^3, 128 atoms, one orbital 15.8 -> 4.6.
+// serial chain of dependent gathers is 4 kNlU times shorter.  Used below kNlFewBlocks blocks of
+// the other kernel, where those waves leave the chip idle, in FP64: 24^3, 8 atoms, 40 orbitals 8.6
+// -> 4.1 us; 72^3, 128 atoms, one orbital 15.8 -> 4.6.  Not in FP32, where a sum's order shows at
+// 1e-7 of it in the FP64 matrices that chefsi_project forms from the result: a block's matrices
+// would depend on its width.
 constexpr int kNlU = 4;
 constexpr int kNlFewBlocks = 512;
 
