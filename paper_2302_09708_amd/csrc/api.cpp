@@ -1355,30 +1355,30 @@ void free_band_tables(chefsi_handle* h) {
 // order), each closed before it would exceed max_pts points, kBandMaxSlots projectors or
 // max_ent entries; each region lists its points with their entries, and its projector slots
 // (projector order) with their entries (point order); each projector lists its slots (region
-// order) for the reduction.  ent_src / gent_src name the table entry behind every scatter /
-// gather entry, so the caller attaches values of its own type.
+// order) for the reduction.  The scatter entries are the table's, in its order; gent_src names the
+// table entry behind every gather entry, so the caller attaches values of its own type.
 struct BandRegions {
   std::vector<int> reg_pt{0}, pt_idx, pt_ent{0}, ent_ls, reg_slot{0}, slot_q, slot_ent{0}, gent_loc, q_slot_ptr{0},
-      q_slot, ent_src, gent_src;
+      q_slot, gent_src;
 };
 
 BandRegions band_regions(int64_t nd, const int* cnt, const int* col, int np_tot, int max_pts, int max_ent) {
   BandRegions R;
   const size_t nent = (size_t)cnt[nd];
   for (std::vector<int>* v : {&R.pt_idx, &R.pt_ent}) v->reserve(nent / 4 + 16);
-  for (std::vector<int>* v : {&R.ent_ls, &R.ent_src, &R.gent_loc, &R.gent_src}) v->reserve(nent);
+  for (std::vector<int>* v : {&R.ent_ls, &R.gent_loc, &R.gent_src}) v->reserve(nent);
   std::vector<int> stamp(np_tot, -1), local(np_tot, 0);  // region that last counted a projector, its slot there
   std::vector<int> cols, fill;                           // the open region's projectors
   int64_t first_pt = 0;                                  // places of the open region's first point and entry
-  size_t first_ent = 0;
+  int first_ent = 0;
   int nreg = 0;
   auto close_region = [&]() {
     std::sort(cols.begin(), cols.end());  // slots in projector order
     const int ns = (int)cols.size(), base = (int)R.gent_loc.size();
     for (int i = 0; i < ns; ++i) local[cols[i]] = i;
     fill.assign(ns + 1, 0);
-    for (size_t e = first_ent; e < R.ent_src.size(); ++e) {
-      const int ls = local[col[R.ent_src[e]]];
+    for (int e = first_ent; e < R.pt_ent.back(); ++e) {
+      const int ls = local[col[e]];
       R.ent_ls.push_back(ls);
       ++fill[ls + 1];
     }
@@ -1387,19 +1387,19 @@ BandRegions band_regions(int64_t nd, const int* cnt, const int* col, int np_tot,
       R.slot_q.push_back(cols[i]);
       R.slot_ent.push_back(base + fill[i + 1]);
     }
-    R.gent_loc.resize(R.ent_src.size());
-    R.gent_src.resize(R.ent_src.size());
+    R.gent_loc.resize(R.pt_ent.back());
+    R.gent_src.resize(R.pt_ent.back());
     for (int64_t p = first_pt; p < (int64_t)R.pt_idx.size(); ++p)  // each slot's entries in point order
       for (int e = R.pt_ent[p]; e < R.pt_ent[p + 1]; ++e) {
         const int g = base + fill[R.ent_ls[e]]++;
         R.gent_loc[g] = (int)(p - first_pt);
-        R.gent_src[g] = R.ent_src[e];
+        R.gent_src[g] = e;
       }
     R.reg_pt.push_back((int)R.pt_idx.size());
     R.reg_slot.push_back((int)R.slot_q.size());
     cols.clear();
     first_pt = (int64_t)R.pt_idx.size();
-    first_ent = R.ent_src.size();
+    first_ent = R.pt_ent.back();
     ++nreg;
   };
   for (int64_t i = 0; i < nd; ++i) {
@@ -1409,7 +1409,7 @@ BandRegions band_regions(int64_t nd, const int* cnt, const int* col, int np_tot,
     int fresh = 0;
     for (int e = cnt[i]; e < cnt[i + 1]; ++e) fresh += stamp[col[e]] != nreg;
     const int64_t open_pts = (int64_t)R.pt_idx.size() - first_pt;
-    if (open_pts > 0 && (open_pts + 1 > max_pts || (int)(R.ent_src.size() - first_ent) + n > max_ent ||
+    if (open_pts > 0 && (open_pts + 1 > max_pts || cnt[i] - first_ent + n > max_ent ||
                          (int)cols.size() + fresh > kBandMaxSlots))
       close_region();
     for (int e = cnt[i]; e < cnt[i + 1]; ++e) {
@@ -1417,10 +1417,9 @@ BandRegions band_regions(int64_t nd, const int* cnt, const int* col, int np_tot,
         stamp[col[e]] = nreg;
         cols.push_back(col[e]);
       }
-      R.ent_src.push_back(e);
     }
     R.pt_idx.push_back((int)i);
-    R.pt_ent.push_back((int)R.ent_src.size());
+    R.pt_ent.push_back(cnt[i + 1]);
   }
   if ((int64_t)R.pt_idx.size() > first_pt) close_region();
   // each projector's slots in region order
@@ -1433,29 +1432,28 @@ BandRegions band_regions(int64_t nd, const int* cnt, const int* col, int np_tot,
   return R;
 }
 
-// Band-pass tables of a real handle: the regions and the projector values of their entries
-// (host), then the device copies, FP32 values for mixed handles and FP64 ones unless the
+// Band-pass tables of a real handle (host): the regions and the projector values of their gather
+// entries (the scatter entries' are the table's), in FP32 for mixed handles and in FP64 unless the
 // band pass runs only in the filter of a mixed handle.
 struct BandTables {
   BandRegions r;
-  std::vector<double> ent_chi, gent_chi;
+  bool f64 = false;
+  std::vector<double> gent_chi;
   std::vector<float> ent_chi32, gent_chi32;
 };
 
 BandTables band_tables(const chefsi_handle* h, bool filter_only) {
   BandTables t;
   t.r = band_regions(h->nd, h->pt_cnt.data(), h->pt_col.data(), h->np_tot, kBandMaxPts, kBandMaxEnt);
-  auto values = [&](auto& v, const std::vector<int>& src) {
-    v.resize(src.size());
-    for (size_t e = 0; e < src.size(); ++e) v[e] = h->pt_val[src[e]];
+  t.f64 = !filter_only;
+  auto gather_values = [&](auto& v) {
+    v.resize(t.r.gent_src.size());
+    for (size_t e = 0; e < v.size(); ++e) v[e] = h->pt_val[t.r.gent_src[e]];
   };
-  if (!filter_only) {
-    values(t.ent_chi, t.r.ent_src);
-    values(t.gent_chi, t.r.gent_src);
-  }
+  if (t.f64) gather_values(t.gent_chi);
   if (h->precision == CHEFSI_MIXED) {
-    values(t.ent_chi32, t.r.ent_src);
-    values(t.gent_chi32, t.r.gent_src);
+    t.ent_chi32.assign(h->pt_val.begin(), h->pt_val.end());
+    gather_values(t.gent_chi32);
   }
   return t;
 }
@@ -1477,7 +1475,7 @@ void build_band_tables(chefsi_handle* h, const BandTables& t) {
     h->nb_gent_loc = upload(h, R.gent_loc.data(), R.gent_loc.size());
     h->nb_q_slot_ptr = upload(h, R.q_slot_ptr.data(), R.q_slot_ptr.size());
     h->nb_q_slot = upload(h, R.q_slot.data(), R.q_slot.size());
-    h->nb_ent_chi64 = upload(h, t.ent_chi.data(), t.ent_chi.size());
+    if (t.f64) h->nb_ent_chi64 = upload(h, h->pt_val.data(), h->pt_val.size());
     h->nb_gent_chi64 = upload(h, t.gent_chi.data(), t.gent_chi.size());
     h->nb_ent_chi32 = upload(h, t.ent_chi32.data(), t.ent_chi32.size());
     h->nb_gent_chi32 = upload(h, t.gent_chi32.data(), t.gent_chi32.size());
@@ -1797,29 +1795,18 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
       for (double v : h->gamma_h) check(std::isfinite(v), "gamma must be finite");
     }
 
-    HIP_TRY(hipGetDevice(&h->device));
-    HIP_TRY(hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device));
-    (void)scratch_address(h->device);  // the static scratch's device address, once per device
-    BLAS_TRY(rocblas_create_handle(&h->blas));
-    // the dense stage must give the same bits whatever else runs on the device (results of
-    // a request alone and among others are compared bit for bit): no atomics in rocBLAS
-    BLAS_TRY(rocblas_set_atomics_mode(h->blas, rocblas_atomics_not_allowed));
     h->hx_plan = plan_hx(h->n[0], h->n[1], h->n[2], 1, h->radius, precision == CHEFSI_FP64 ? 8 : 4, 0, 0);
     check(h->hx_plan.ok, "no stencil tiling fits this grid");
 
-    const size_t pinned_doubles = std::max({(size_t)max_ns + 8, (size_t)h->n_atoms * 10, (size_t)kVecBlocks});
-    if (no_memory(hipHostMalloc((void**)&h->pinned, pinned_doubles * sizeof(double), hipHostMallocDefault))) {
-      h->pinned = nullptr;
-      throw Error{CHEFSI_ERR_OOM, "pinned host allocation failed"};
-    }
-    h->veff64 = upload(h, h->veff_h.data(), nd);
-    std::vector<float> v32(h->veff_h.begin(), h->veff_h.end());
-    h->veff32 = upload(h, v32.data(), nd);
-
+    // point-major projector table, and the band pass's tables from it in a second thread
+    const int na = h->n_atoms;
+    std::vector<int> soff(na + 1), poff(na);
+    std::vector<int64_t> coff(na);
+    std::vector<double> gdv(h->np_tot);
+    bool fits = true, both = false;
+    BandFrom from{kNoBand, kNoBand};
+    std::future<BandTables> tables;
     if (h->np_tot > 0) {
-      const int na = h->n_atoms;
-      std::vector<int> soff(na + 1), poff(na);
-      std::vector<int64_t> coff(na);
       int64_t c = 0;
       int p = 0;
       for (int J = 0; J < na; ++J) {
@@ -1830,9 +1817,8 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
         p += h->nproj_h[J];
       }
       soff[na] = (int)h->supp_ptr_h[na];
-      std::vector<double> gdv(h->np_tot);
       for (int q = 0; q < h->np_tot; ++q) gdv[q] = h->gamma_h[q] * h->dv;
-      // point-major table: point i lists (projector column, chi value), atoms in order
+      // point i lists (projector column, chi value), atoms in order
       std::vector<int> cnt(nd + 1, 0);
       for (int J = 0; J < na; ++J)
         for (int64_t s = h->supp_ptr_h[J]; s < h->supp_ptr_h[J + 1]; ++s) cnt[h->supp_idx_h[s] + 1] += h->nproj_h[J];
@@ -1858,13 +1844,30 @@ int chefsi_create(const chefsi_grid_t* grid, const double* veff_host, const chef
       check(h->np_tot < 65536, "more than 65535 projectors");
       // The record route keeps the block's projector row and partial sums in LDS beside the tile: a
       // handle whose projectors overflow that for the default tile has the band pass alone.  Others
-      // have the records, and the band pass beside them for the calls that it serves better; its
-      // tables are formed in a second thread meanwhile.
-      const bool fits = hx_records_fit(h, h->hx_plan);
-      const BandFrom from = band_from(h);
-      const bool both = fits && (from.apply <= max_ns || from.filter <= max_ns);
-      std::future<BandTables> tables;
+      // have the records, and the band pass beside them for the calls that it serves better.
+      fits = hx_records_fit(h, h->hx_plan);
+      from = band_from(h);
+      both = fits && (from.apply <= max_ns || from.filter <= max_ns);
       if (both) tables = std::async([h] { return band_tables(h, h->precision == CHEFSI_MIXED); });
+    }
+
+    HIP_TRY(hipGetDevice(&h->device));
+    HIP_TRY(hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device));
+    (void)scratch_address(h->device);  // the static scratch's device address, once per device
+    BLAS_TRY(rocblas_create_handle(&h->blas));
+    // the dense stage must give the same bits whatever else runs on the device (results of
+    // a request alone and among others are compared bit for bit): no atomics in rocBLAS
+    BLAS_TRY(rocblas_set_atomics_mode(h->blas, rocblas_atomics_not_allowed));
+    const size_t pinned_doubles = std::max({(size_t)max_ns + 8, (size_t)h->n_atoms * 10, (size_t)kVecBlocks});
+    if (no_memory(hipHostMalloc((void**)&h->pinned, pinned_doubles * sizeof(double), hipHostMallocDefault))) {
+      h->pinned = nullptr;
+      throw Error{CHEFSI_ERR_OOM, "pinned host allocation failed"};
+    }
+    h->veff64 = upload(h, h->veff_h.data(), nd);
+    std::vector<float> v32(h->veff_h.begin(), h->veff_h.end());
+    h->veff32 = upload(h, v32.data(), nd);
+
+    if (h->np_tot > 0) {
       if (!fits) {
         try {
           const BandTables t = band_tables(h, false);
@@ -3188,8 +3191,7 @@ int chefsi_kpoint_create(const chefsi_grid_t* grid, const double* veff_host, con
     if (h->np_tot > 0) {
       // band-pass regions of the touched points (the real path's tables with chi~ values)
       const BandRegions R = band_regions(nd, cnt.data(), cols.data(), h->np_tot, kZBandThreads, kZBandMaxEnt);
-      std::vector<double2> ent_chi(R.ent_src.size()), gent_chi(R.gent_src.size());
-      for (size_t e = 0; e < ent_chi.size(); ++e) ent_chi[e] = vals[R.ent_src[e]];
+      std::vector<double2> gent_chi(R.gent_src.size());
       for (size_t e = 0; e < gent_chi.size(); ++e) {
         const double2 v = vals[R.gent_src[e]];
         gent_chi[e] = make_double2(v.x, -v.y);
@@ -3207,7 +3209,7 @@ int chefsi_kpoint_create(const chefsi_grid_t* grid, const double* veff_host, con
       h->pt_idx = kupload(R.pt_idx.data(), R.pt_idx.size());
       h->pt_ent = kupload(R.pt_ent.data(), R.pt_ent.size());
       h->ent_ls = kupload(R.ent_ls.data(), R.ent_ls.size());
-      h->ent_chi = kupload(ent_chi.data(), ent_chi.size());
+      h->ent_chi = kupload(vals.data(), vals.size());
       h->reg_slot = kupload(R.reg_slot.data(), R.reg_slot.size());
       h->slot_q = kupload(R.slot_q.data(), R.slot_q.size());
       h->slot_ent = kupload(R.slot_ent.data(), R.slot_ent.size());
