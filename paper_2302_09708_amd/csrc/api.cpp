@@ -119,6 +119,39 @@ void* scratch_address(int dev) {
 }
 }  // namespace
 
+namespace {
+// plans of the FP64 Gram products through rocBLAS, of the widened row panels, and a call's workspace
+// (see plan_blas_gram, plan_panels, layout)
+constexpr int kMaxGramBlocks = 8;
+
+struct BlasGram {
+  int splits = 1;
+  int64_t kc = 0, tail = 0;
+  int nparts = 1;
+  size_t bytes = 0;
+  int nblk = 1;                         // column blocks
+  int start[kMaxGramBlocks + 1] = {0};  // block b is columns [start[b], start[b+1])
+};
+
+struct PanelPlan {
+  int splits = 1;
+  int64_t kc = 0, rows = 0;
+  size_t part_bytes = 0;   // one set of Gram partials
+  size_t panel_bytes = 0;  // one rows x ns FP64 panel
+};
+
+struct WsLayout {
+  size_t bufB = 0, alpha = 0, hs = 0, ms = 0, d = 0, e = 0, sc = 0, info = 0, msg = 0, partial = 0, zsplit = 0,
+         panel = 0, panel_out = 0, band = 0, chol = 0, solver = 0, total = 0;
+  size_t bufB_bytes = 0, solver_bytes = 0, band_bytes = 0;
+  GramPlan gram;
+  BlasGram bgram;   // FP64 handles: Gram products of FP64 blocks
+  GramBothPlan both;  // the same in one launch
+  PanelPlan pan;    // mixed handles: FP64 products of the FP32 block
+  PairPlan pair;    // mixed handles: both split-bf16 Gram products at once
+};
+
+}  // namespace
 
 constexpr int kNoBand = INT32_MAX;
 
@@ -208,8 +241,7 @@ struct chefsi_handle : BandDevice {
   int ws_band_slots = 0;
 
   rocblas_handle blas = nullptr;
-  std::map<int, size_t> solver_ws_cache;
-  std::map<int, PairPlan> pair_cache;  // plans of the split-bf16 Gram units, by ns
+  std::map<int, WsLayout> layouts;  // by ns: the plans cost a small call more than its launches
   // point-major projector table (host): point i lists pt_col/pt_val[pt_cnt[i] .. pt_cnt[i+1]),
   // kept so the stencil-pass records can be rebuilt for another tiling
   std::vector<int> pt_cnt, pt_col;
@@ -234,17 +266,6 @@ namespace {
 // Only the upper triangle of the symmetric product is needed: the columns are cut into
 // blocks and block row i is formed against columns [start_i, ns) alone, which skips most
 // of the lower triangle's work.
-constexpr int kMaxGramBlocks = 8;
-
-struct BlasGram {
-  int splits = 1;
-  int64_t kc = 0, tail = 0;
-  int nparts = 1;
-  size_t bytes = 0;
-  int nblk = 1;                         // column blocks
-  int start[kMaxGramBlocks + 1] = {0};  // block b is columns [start[b], start[b+1])
-};
-
 // Column blocks of the upper-triangle Gram (split-K batches of rocBLAS dgemm, measured at
 // ns = 600 and 1200): up to ns = 1024, blocks of 128 columns (ns = 600: 2.6 vs 4.2 ms for
 // the full product); above, three blocks cut near 0.43 ns and 0.75 ns (ns = 1200 at 512
@@ -301,13 +322,6 @@ bool blas_gram_faster(int64_t nd, int ns) {
 // the FP32 result in the upper half of the FP64 scratch block.
 constexpr int64_t kPanelBytes = (int64_t)512 << 20;
 
-struct PanelPlan {
-  int splits = 1;
-  int64_t kc = 0, rows = 0;
-  size_t part_bytes = 0;   // one set of Gram partials
-  size_t panel_bytes = 0;  // one rows x ns FP64 panel
-};
-
 PanelPlan plan_panels(int64_t nd, int ns) {
   PanelPlan p;
   const int64_t tiles = ((int64_t)(ns + 127) / 128) * ((ns + 127) / 128);
@@ -321,17 +335,6 @@ PanelPlan plan_panels(int64_t nd, int ns) {
   p.panel_bytes = (size_t)p.rows * ns * sizeof(double);
   return p;
 }
-
-struct WsLayout {
-  size_t bufB = 0, alpha = 0, hs = 0, ms = 0, d = 0, e = 0, sc = 0, info = 0, msg = 0, partial = 0, zsplit = 0,
-         panel = 0, panel_out = 0, band = 0, chol = 0, solver = 0, total = 0;
-  size_t bufB_bytes = 0, solver_bytes = 0, band_bytes = 0;
-  GramPlan gram;
-  BlasGram bgram;   // FP64 handles: Gram products of FP64 blocks
-  GramBothPlan both;  // the same in one launch
-  PanelPlan pan;    // mixed handles: FP64 products of the FP32 block
-  PairPlan pair;    // mixed handles: both split-bf16 Gram products at once
-};
 
 // status words in the pinned staging buffer, after max_ns doubles
 rocblas_int* pinned_info(chefsi_handle* h) { return reinterpret_cast<rocblas_int*>(h->pinned + h->max_ns); }
@@ -366,8 +369,6 @@ size_t band_partial_bytes(const chefsi_handle* h, int slots, int ns) {
 // reduced matrix, symmetric eigensolve, back substitution); the calls run in sequence,
 // so the largest single request is enough.
 size_t solver_workspace(chefsi_handle* h, int ns) {
-  auto it = h->solver_ws_cache.find(ns);
-  if (it != h->solver_ws_cache.end()) return it->second;
   const double one = 1.0;
   size_t best = 0, sz = 0;
   auto query = [&](auto&& call) {
@@ -422,11 +423,12 @@ size_t solver_workspace(chefsi_handle* h, int ns) {
       rocblas_dgemm(h->blas, rocblas_operation_none, rocblas_operation_none, (rocblas_int)h->nd, ns, ns, &one,
                     nullptr, (rocblas_int)h->nd, nullptr, ns, &one, nullptr, (rocblas_int)h->nd);
     });
-  h->solver_ws_cache[ns] = best;
   return best;
 }
 
-WsLayout layout(chefsi_handle* h, int ns) {
+const WsLayout& layout(chefsi_handle* h, int ns) {
+  const auto known = h->layouts.find(ns);
+  if (known != h->layouts.end()) return known->second;
   WsLayout L;
   size_t off = 0;
   L.bufB = off;
@@ -460,10 +462,7 @@ WsLayout layout(chefsi_handle* h, int ns) {
                                             (size_t)ns * ns * sizeof(double)})
                                 : std::max(L.gram.partial_bytes, 2 * L.pan.part_bytes);
   if (h->precision == CHEFSI_MIXED) {
-    auto it = h->pair_cache.find(ns);
-    if (it == h->pair_cache.end())
-      it = h->pair_cache.emplace(ns, plan_gram_pair(h->nd, ns, L.gram, part_bytes)).first;
-    L.pair = it->second;
+    L.pair = plan_gram_pair(h->nd, ns, L.gram, part_bytes);
   }
   off += align256(part_bytes);
   L.zsplit = off;
@@ -488,7 +487,7 @@ WsLayout layout(chefsi_handle* h, int ns) {
   L.solver_bytes = solver_workspace(h, ns);
   off += align256(std::max<size_t>(L.solver_bytes, 256));
   L.total = off;
-  return L;
+  return h->layouts.emplace(ns, L).first->second;
 }
 
 template <typename T>
