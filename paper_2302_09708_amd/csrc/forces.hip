@@ -20,17 +20,18 @@ namespace chefsi {
 
 namespace {
 
-constexpr int kNgWaves = 4;  // waves per block: one atom, consecutive orbital groups
+constexpr int kNgWaves = 8;  // waves per block, sharing an atom's support
 constexpr int kNgP = 4;      // projectors per pass
 
-// One wave = one atom x V orbitals; a lane owns every 64th support point.  A point's 6r + 1
+// One block = one atom x V orbitals; a thread owns every 512th support point.  A point's 6r + 1
 // byte offsets are computed once and serve the V orbitals (Dirichlet ghosts are offsets
-// past the end, which load zero).  Bound by the 6r + 1 cached loads per (support point,
-// orbital), about 58 cycles of a CU each (eight to twelve lines, mostly from L2): 72^3, 128
-// atoms, 600 orbitals, order 12 measured 3.8 ms (forces) and 3.9 ms (stress) where writing
-// and re-reading whole gradients took 11.3 and 18.5 ms (three gradient passes of 2.6 ms,
-// four or ten gathers of 0.26 ms and 0.8 ms of sums after each).
-// The stress keeps 40 sums per orbital, so its waves own one orbital, the forces' two.
+// past the end, which load zero).  For supports too large for the kernel below.  Bound by the
+// 6r + 1 cached loads per (support point, orbital), about 58 cycles of a CU each (eight to twelve
+// lines, mostly from L2), and with few atoms and orbitals by the chain of a thread's points: 8
+// waves share it.  40x37x33, 4 atoms of 8200 points, order 12, forces of 1 / 10 / 40 orbitals
+// FP64 (us): whole gradients written and re-read 315 / 476 / 590, one wave for two orbitals of an
+// atom 768 / 948 / 1313, now 108 / 109 / 111.
+// The stress keeps 40 sums per orbital, so its blocks own one orbital, the forces' two.
 // XCD mapping: each XCD takes a contiguous run of (orbital group, atom), atom fastest, so
 // neighbouring atoms read an orbital's shared points through one L2.
 template <typename TV, int R, bool STRESS>
@@ -41,26 +42,23 @@ __global__ __launch_bounds__(64 * kNgWaves) void nl_grad_kernel(NlGradArgs<TV> a
   constexpr int NR = STRESS ? 32 : 16;       // power of two of the first reduction
   constexpr int NO = STRESS ? 10 : 3;        // results per (atom, orbital)
   constexpr int NA = kNgP + NS;              // 16 or 40 sums per orbital
-  __shared__ double red[kNgWaves][NA];
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  __shared__ double red[kNgWaves][V][NA];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t logical = (int64_t)(blockIdx.x % 8) * a.per_xcd + blockIdx.x / 8;
   if (logical >= (int64_t)a.n_atoms * a.ngroups) return;
   const int atom = (int)(logical % a.n_atoms);
-  const int v0 = ((int)(logical / a.n_atoms) * kNgWaves + wave) * V;
+  const int v0 = (int)(logical / a.n_atoms) * V;
   const int s0 = a.supp_off[atom];
   const int n = a.supp_off[atom + 1] - s0;
   const int npj = a.nproj[atom];
   const double* chi = a.chi + a.chi_off[atom];
   const int nx = a.nx, ny = a.ny, nz = a.nz, nplane = nx * ny;
-  const bool live = v0 < a.ns;  // waves past the block width only meet the barriers
   const int nbytes = (int)(a.nd * (int64_t)sizeof(TV));
   __amdgpu_buffer_rsrc_t rx[V];
 #pragma unroll
   for (int u = 0; u < V; ++u) rx[u] = make_rsrc(a.x + (int64_t)min(v0 + u, a.ns - 1) * a.nd, nbytes);
-  double tot[V];  // lane d < NO: result d of orbital u
-#pragma unroll
-  for (int u = 0; u < V; ++u) tot[u] = 0.0;
+  double tot = 0.0;  // thread u NO + d: result d of orbital u
+  const int ou = tid / NO, od = tid % NO;
 
   for (int a0 = 0; a0 < npj; a0 += kNgP) {
     double acc[V][NA];
@@ -68,51 +66,49 @@ __global__ __launch_bounds__(64 * kNgWaves) void nl_grad_kernel(NlGradArgs<TV> a
     for (int u = 0; u < V; ++u)
 #pragma unroll
       for (int k = 0; k < NA; ++k) acc[u][k] = 0.0;
-    if (live) {
-      for (int s = lane; s < n; s += 64) {
-        const int i = a.supp_idx[s0 + s];
-        const int z = i / nplane, yx = i - z * nplane, y = yx / nx, x = yx - y * nx;
-        unsigned off[3][2][R];
+    for (int s = tid; s < n; s += 64 * kNgWaves) {
+      const int i = a.supp_idx[s0 + s];
+      const int z = i / nplane, yx = i - z * nplane, y = yx / nx, x = yx - y * nx;
+      unsigned off[3][2][R];
 #pragma unroll
-        for (int p = 1; p <= R; ++p) {
-          const int cp[3] = {x + p, y + p, z + p}, cm[3] = {x - p, y - p, z - p};
-          const int ext[3] = {nx, ny, nz}, str[3] = {1, nx, nplane};
+      for (int p = 1; p <= R; ++p) {
+        const int cp[3] = {x + p, y + p, z + p}, cm[3] = {x - p, y - p, z - p};
+        const int ext[3] = {nx, ny, nz}, str[3] = {1, nx, nplane};
 #pragma unroll
-          for (int d = 0; d < 3; ++d) {  // n >= r in a periodic direction: one wrap
-            const int jp = i + p * str[d], jm = i - p * str[d];
-            const bool op = cp[d] >= ext[d], om = cm[d] < 0;
-            off[d][0][p - 1] = lane_off<TV>(!op ? jp : (a.periodic[d] ? jp - ext[d] * str[d] : -1));
-            off[d][1][p - 1] = lane_off<TV>(!om ? jm : (a.periodic[d] ? jm + ext[d] * str[d] : -1));
-          }
+        for (int d = 0; d < 3; ++d) {  // n >= r in a periodic direction: one wrap
+          const int jp = i + p * str[d], jm = i - p * str[d];
+          const bool op = cp[d] >= ext[d], om = cm[d] < 0;
+          off[d][0][p - 1] = lane_off<TV>(!op ? jp : (a.periodic[d] ? jp - ext[d] * str[d] : -1));
+          off[d][1][p - 1] = lane_off<TV>(!om ? jm : (a.periodic[d] ? jm + ext[d] * str[d] : -1));
         }
-        double c[kNgP];
+      }
+      double c[kNgP];
 #pragma unroll
-        for (int k = 0; k < kNgP; ++k) c[k] = a0 + k < npj ? chi[(int64_t)(a0 + k) * n + s] : 0.0;
-        double w[3] = {1.0, 1.0, 1.0};
-        if (STRESS) {
+      for (int k = 0; k < kNgP; ++k) c[k] = a0 + k < npj ? chi[(int64_t)(a0 + k) * n + s] : 0.0;
+      double w[3] = {1.0, 1.0, 1.0};
+      if (STRESS) {
 #pragma unroll
-          for (int b = 0; b < 3; ++b) w[b] = a.disp[3 * (int64_t)(s0 + s) + b];
-        }
+        for (int b = 0; b < 3; ++b) w[b] = a.disp[3 * (int64_t)(s0 + s) + b];
+      }
 #pragma unroll
-        for (int u = 0; u < V; ++u) {
-          const double yv = double(bload<TV>(rx[u], lane_off<TV>(i), 0u));
+      for (int u = 0; u < V; ++u) {
+        const double yv = double(bload<TV>(rx[u], lane_off<TV>(i), 0u));
 #pragma unroll
-          for (int k = 0; k < kNgP; ++k) acc[u][k] += c[k] * yv;
+        for (int k = 0; k < kNgP; ++k) acc[u][k] += c[k] * yv;
 #pragma unroll
-          for (int d = 0; d < 3; ++d) {
-            double g = 0.0;
+        for (int d = 0; d < 3; ++d) {
+          double g = 0.0;
 #pragma unroll
-            for (int p = 0; p < R; ++p)
-              g += a.c[d][p + 1] * (double(bload<TV>(rx[u], off[d][0][p], 0u)) - double(bload<TV>(rx[u], off[d][1][p], 0u)));
-            if (STRESS) {
+          for (int p = 0; p < R; ++p)
+            g += a.c[d][p + 1] * (double(bload<TV>(rx[u], off[d][0][p], 0u)) - double(bload<TV>(rx[u], off[d][1][p], 0u)));
+          if (STRESS) {
 #pragma unroll
-              for (int b = 0; b < 3; ++b)
+            for (int b = 0; b < 3; ++b)
 #pragma unroll
-                for (int k = 0; k < kNgP; ++k) acc[u][kNgP + (3 * d + b) * kNgP + k] += (c[k] * w[b]) * g;
-            } else {
+              for (int k = 0; k < kNgP; ++k) acc[u][kNgP + (3 * d + b) * kNgP + k] += (c[k] * w[b]) * g;
+          } else {
 #pragma unroll
-              for (int k = 0; k < kNgP; ++k) acc[u][kNgP + d * kNgP + k] += c[k] * g;
-            }
+            for (int k = 0; k < kNgP; ++k) acc[u][kNgP + d * kNgP + k] += c[k] * g;
           }
         }
       }
@@ -123,29 +119,32 @@ __global__ __launch_bounds__(64 * kNgWaves) void nl_grad_kernel(NlGradArgs<TV> a
 #pragma unroll
       for (int k = 0; k < NR; ++k) h[k] = acc[u][k];
       wave_sums(h, lane);
-      if (lane % (64 / NR) == 0) red[wave][lane / (64 / NR)] = h[0];
+      if (lane % (64 / NR) == 0) red[wave][u][lane / (64 / NR)] = h[0];
       if constexpr (STRESS) {  // the other eight of the forty
         double g[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) g[k] = acc[u][NR + k];
         wave_sums(g, lane);
-        if (lane % 8 == 0) red[wave][NR + lane / 8] = g[0];
+        if (lane % 8 == 0) red[wave][u][NR + lane / 8] = g[0];
       }
-      __syncthreads();
-      if (lane < NO) {
-        // result `lane`: the energy sum gamma a^2 (stress, lane 0), else sum gamma a b
-        const int b = STRESS ? (lane == 0 ? 0 : lane) : lane + 1;  // block of kNgP sums in red
-        for (int k = 0; k < kNgP && a0 + k < npj; ++k)
-          tot[u] += a.gdv[a.poff[atom] + a0 + k] * (red[wave][k] * red[wave][b * kNgP + k]);
-      }
-      __syncthreads();
     }
-  }
-  if (live && lane < NO) {
+    __syncthreads();
+    if (tid < V * NO) {
+      auto sum = [&](int k) {
+        double r = red[0][ou][k];
 #pragma unroll
-    for (int u = 0; u < V; ++u)  // gdv holds gamma dV: two factors dV, one taken from gdv
-      if (v0 + u < a.ns) a.part[((int64_t)atom * a.ns + v0 + u) * NO + lane] = a.occ[v0 + u] * tot[u] * a.dv;
+        for (int w = 1; w < kNgWaves; ++w) r += red[w][ou][k];
+        return r;
+      };
+      // the energy sum gamma a^2 (stress, result 0), else sum gamma a b
+      const int b = STRESS ? od : od + 1;  // block of kNgP sums in red
+      for (int k = 0; k < kNgP && a0 + k < npj; ++k)
+        tot += a.gdv[a.poff[atom] + a0 + k] * (sum(k) * sum(b * kNgP + k));
+    }
+    __syncthreads();
   }
+  if (tid < V * NO && v0 + ou < a.ns)  // gdv holds gamma dV: two factors dV, one taken from gdv
+    a.part[((int64_t)atom * a.ns + v0 + ou) * NO + od] = a.occ[v0 + ou] * tot * a.dv;
 }
 
 // The same results with the gradient's neighbourhood in LDS.  One block = one atom x kBoxOrb
@@ -572,7 +571,7 @@ template <typename TV>
 hipError_t launch_nl_grad(const NlGradArgs<TV>& a0, int radius, double* out, double scale, hipStream_t s) {
   if (a0.n_atoms <= 0 || a0.ns <= 0) return hipSuccess;
   NlGradArgs<TV> a = a0;
-  const int per_block = kNgWaves * (a.disp != nullptr ? 1 : 2);
+  const int per_block = a.disp != nullptr ? 1 : 2;
   const int no = a.disp != nullptr ? 10 : 3;
   a.ngroups = (a.ns + per_block - 1) / per_block;
   if (a.box != nullptr) {  // as many orbitals per block as leave about four blocks per CU
