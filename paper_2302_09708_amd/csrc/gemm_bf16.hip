@@ -602,11 +602,15 @@ __device__ __forceinline__ void rot_store_z(const u32x4 (&zr)[4], __bf16* sh, __
   *reinterpret_cast<u32x4*>(sl + 8) = zr[3];
 }
 
-__global__ __launch_bounds__(256, 2) void rotate_bf16x3_kernel(const float* __restrict__ X, const __bf16* __restrict__ zh,
-                                                            const __bf16* __restrict__ zl, float* __restrict__ O,
-                                                            int64_t nd, int ns, int ld, int npt, int njt,
-                                                            int per_xcd) {
-  __shared__ __attribute__((aligned(16))) __bf16 lds[2][2][kRotJ * kLd];  // [buffer][hi, lo][j][kLd]
+// JF: 32-wide fragments of a block's columns (4: kRotJ).  Up to 64 orbitals one block has them all,
+// and a narrower one needs fewer registers (90 and 204 against 256), so more blocks hide each
+// other's single or double stage: 120^3, 8 / 24 / 48 orbitals 75.7 / 97 / 186 us with four
+// fragments, 26.4 / 60.2 / 149 with one or two.
+template <int JF>
+__global__ __launch_bounds__(256, JF == 1 ? 4 : 2) void rotate_bf16x3_kernel(
+    const float* __restrict__ X, const __bf16* __restrict__ zh, const __bf16* __restrict__ zl, float* __restrict__ O,
+    int64_t nd, int ns, int ld, int npt, int njt, int per_xcd) {
+  __shared__ __attribute__((aligned(16))) __bf16 lds[2][2][32 * JF * kLd];  // [buffer][hi, lo][j][kLd]
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -620,7 +624,7 @@ __global__ __launch_bounds__(256, 2) void rotate_bf16x3_kernel(const float* __re
   const int64_t p0 = (int64_t)ptile * kRotP + wave * 64;
 
   // Z staging: thread t copies 16 bf16 of column j0 + t / 2 (hi and lo)
-  const int zrow = tid >> 1, zhalf = tid & 1;
+  const int zrow = min(tid >> 1, 32 * JF - 1), zhalf = tid & 1;  // (threads past the columns: the last one again)
   const __bf16* pzh = zh + (int64_t)(j0 + zrow) * ld + 16 * zhalf;
   const __bf16* pzl = zl + (int64_t)(j0 + zrow) * ld + 16 * zhalf;
   const int zoff = zrow * kLd + 16 * zhalf;
@@ -635,15 +639,15 @@ __global__ __launch_bounds__(256, 2) void rotate_bf16x3_kernel(const float* __re
     voff[f] = ((unsigned)(8 * g) * (unsigned)nd + (unsigned)pcol[f]) * 4u;
   }
 
-  f32x16 acc[4][2];  // [j fragment][p fragment]
+  f32x16 acc[JF][2];  // [j fragment][p fragment]
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < JF; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  const int nstage = ld / kKS;
+  const int nstage = JF == 1 ? 1 : ld / kKS;  // one fragment: at most 32 columns
   float xa[2][2][8], xb[2][2][8];  // [k16 step][p fragment][e], a stage's and the next one's
   u32x4 zr[4];
   rot_load_z(zr, pzh, pzl, 0);
@@ -663,7 +667,7 @@ __global__ __launch_bounds__(256, 2) void rotate_bf16x3_kernel(const float* __re
 #pragma unroll
       for (int f = 0; f < 2; ++f) split8(xc[s][f], xh[f], xl[f]);
 #pragma unroll
-      for (int jf = 0; jf < 4; ++jf) {
+      for (int jf = 0; jf < JF; ++jf) {
         const int o = (jf * 32 + r32) * kLd + 16 * s + 8 * g;
         const bf16x8 zhv = as_bf8(*reinterpret_cast<const u32x4*>(lds[buf][0] + o));
         const bf16x8 zlv = as_bf8(*reinterpret_cast<const u32x4*>(lds[buf][1] + o));
@@ -685,7 +689,7 @@ __global__ __launch_bounds__(256, 2) void rotate_bf16x3_kernel(const float* __re
 
   // D[j][p]: lane l, register v -> j = 8 (v / 4) + 4 (l / 32) + v % 4, p = l % 32
 #pragma unroll
-  for (int jf = 0; jf < 4; ++jf)
+  for (int jf = 0; jf < JF; ++jf)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int j = j0 + jf * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
@@ -714,7 +718,12 @@ hipError_t launch_rotate_bf16x3(const float* X, const double* Z, void* zsplit, f
   const int per_xcd = (int)((nb + 7) / 8);
   const dim3 grid((unsigned)(per_xcd * 8));
   if (nd > ((int64_t)1 << 31) / 48) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(rotate_bf16x3_kernel, grid, dim3(256), 0, s, X, zh, zl, O, nd, ns, ld, npt, njt, per_xcd);
+  if (ns <= 32)
+    hipLaunchKernelGGL(rotate_bf16x3_kernel<1>, grid, dim3(256), 0, s, X, zh, zl, O, nd, ns, ld, npt, njt, per_xcd);
+  else if (ns <= 64)
+    hipLaunchKernelGGL(rotate_bf16x3_kernel<2>, grid, dim3(256), 0, s, X, zh, zl, O, nd, ns, ld, npt, njt, per_xcd);
+  else
+    hipLaunchKernelGGL(rotate_bf16x3_kernel<4>, grid, dim3(256), 0, s, X, zh, zl, O, nd, ns, ld, npt, njt, per_xcd);
   return hipGetLastError();
 }
 
