@@ -1522,8 +1522,9 @@ void build_band_tables(chefsi_handle* h, const BandTables& t) {
 // Grids of 2^14 to 2^15 points without 512 such points take it from 2^20 values of the widest call
 // on although the records are faster there (27x30x26, one atom, 60 orbitals 1.4): the tests hold
 // these handles to the bits of that route.
-// A mixed handle keeps the records for single applications, whose FP32 rounding the FP64
-// matrices of chefsi_project show.
+// A mixed handle keeps the records for single applications: they add the projector term before
+// the result is rounded to FP32, where the band pass rounds the touched points a second time (in a
+// filter, too; there the result is FP32 at every step, while chefsi_project forms FP64 matrices).
 struct BandFrom {
   int apply, filter;
 };

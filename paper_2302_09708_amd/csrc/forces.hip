@@ -157,8 +157,8 @@ __global__ __launch_bounds__(64 * kNgWaves) void nl_grad_kernel(NlGradArgs<TV> a
 // larger than the registers hold, nl_grad_kernel above does the work.
 // The wave sums of all the block's orbitals wait in LDS and are combined at its end: combined
 // orbital by orbital they were a third of the time (2.36 and 2.95 ms).
-// 72^3, 128 atoms (905 points, a box of 13^3), 600 orbitals, order 12, FP64: forces 3.8 ->
-// 1.95 ms, stress 3.9 -> 2.5 ms; bound by latency at one block per CU (LDS busy 32 % of the
+// 72^3, 128 atoms (905 points, a box of 12^3), 600 orbitals, order 12, FP64: forces 3.8 ->
+// 1.95 ms, stress 3.9 -> 2.5 ms; bound by latency at one block per CU (LDS busy 31 % of the
 // cycles, VALU 30 %): the registers leave no room for a second.
 constexpr int kBoxThreads = 512;
 constexpr int kBoxWaves = kBoxThreads / 64;

@@ -265,12 +265,13 @@ hipError_t launch_gram_bf16x3(const float* A, const float* B, int64_t nd, int ns
 // busy 24 % of the cycles.  The unit stages 512 rows for 256 x 256 results where four of the
 // 128-wide tiles stage 1024, and splits each staged value half as often.
 //
-// One block per CU (512 threads, 128 KB of LDS, 256 registers a lane).  Wave (wm, wn) holds
+// One block per CU (512 threads, 128 KB of LDS, 256 registers a lane; 53 spill, which are read
+// back between K loops, where sums go out, and not inside one).  Wave (wm, wn) holds
 // 64 rows x 128 columns, wn = 0 the columns of X, wn = 1 those of Y.  A 32-wide K stage lies
 // in LDS as 64-byte rows of hi and of lo; 16-byte chunk c of row r sits at chunk
 // c ^ (r / 4) % 4, so the eight rows that a read covers at a time fall on distinct banks.
 // Measured, both products with their sums: 120^3, Ns 1800: 77.3 -> 36.7 ms (1185 TF/s executed
-// bf16, MFMA busy 68 % of the cycles at the 1.65 GHz the power limit leaves, L2 hits 67 %);
+// bf16, MFMA busy 69 % of the cycles at the 1.62 GHz the power limit leaves, L2 hits 65 %);
 // 60x60x180, Ns 1200: 11.95 -> 6.83 ms; 72^3, Ns 600: 1.94 -> 1.62 ms.
 // During stage t a thread splits its eight row pieces of stage t + 1 into the other buffer,
 // six MFMAs apart, and refetches each piece for stage t + 2 as soon as it is split: every

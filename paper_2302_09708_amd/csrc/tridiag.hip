@@ -30,6 +30,8 @@
 // kernels a column: 9.0 / 1.2 ms at n = 600, 0.15 / 0.27 ms at n = 40.  Bound by a column's
 // serial chain (two wave sums, a square root, two divisions, LDS round trips) and, with more
 // than one workgroup, the exchange: 2.7 us a column at n = 130, 3.6 at 600.
+// Above 1024 rows v, w and the rows under way outgrow the 256 registers (65 spilled up to 1216,
+// 162 up to 1408, read back in every column); 1200 columns still take 5.2 us each.
 // backtransform_kernel: C <- Q C, a wave keeping two columns of C in registers, the
 // reflectors applied one after the other from LDS with the next ones already on the way.
 #include "common.h"
