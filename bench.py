@@ -591,7 +591,7 @@ def main():
         # each other can differ from box to box)
         t = json.load(open(TRAFFIC_FILE))
         sc = main_run["stencil_choice"]
-        if t.get("source_sha256_16") == kernel_source_hash("hx_apply.hip", "common.h"):
+        if t.get("source_sha256_16") == kernel_source_hash("hx_apply.hip", "stencil.h", "common.h"):
             for e in t.get("entries", []):
                 if all(e["stencil_choice"].get(k) == sc[k]
                        for k in ("rows_per_thread", "row_groups", "projectors_in_stencil")):
